@@ -145,17 +145,24 @@ def _live_rows(case, m):
 
 
 # ---------------------------------------------------------------------------------------------
+def _inputs(case, seed):
+    """Cuts, weights, prompts and cached answers; the generator goes on to the rewards and the suffix tokens."""
+    mc = MODELS[case["model"]]
+    m, plen = _shapes(case)
+    rng = np.random.Generator(np.random.PCG64(seed))
+    weights = synth.make_weights(mc, seed=seed, device="cuda")
+    prompts = [rng.integers(0, mc.vocab, size=int(p), dtype=np.int32) for p in plen]
+    cached = [rng.integers(0, mc.vocab, size=case["answer"], dtype=np.int32) for _ in range(case["groups"])]
+    return m, plen, weights, prompts, cached, rng
+
+
 def prepare(case, seed):
     if case["kind"] == "sample":
         return _prepare_sample(case, seed)
     mc = MODELS[case["model"]]
     n, G = case["groups"], case["G"]
-    m, plen = _shapes(case)
-    rng = np.random.Generator(np.random.PCG64(seed))
-    weights = synth.make_weights(mc, seed=seed, device="cuda")
+    m, plen, weights, prompts, cached, rng = _inputs(case, seed)
     model = rpo.rpo_model_create(mc, weights)
-    prompts = [rng.integers(0, mc.vocab, size=int(p), dtype=np.int32) for p in plen]
-    cached = [rng.integers(0, mc.vocab, size=case["answer"], dtype=np.int32) for _ in range(n)]
     lens = plen + case["answer"] - m
     max_prefix, max_m = int(lens.max()), int(m.max())
     max_rows = max(min(MAX_ROWS, int(lens.sum())), max_prefix, n * G, max_m)
@@ -281,6 +288,103 @@ def _sample(st):
                    case["temperature"], st["seed"], st["seq_ids"], 7, st["drawn"], st["drawn_lp"], None, -1, None,
                    None, st["row_max"])
     return dict(tokens=st["drawn"], logprobs=st["drawn_lp"])
+
+
+# ---------------------------------------------------------------------------------------------
+def exact(case, seed):
+    """The outputs of run in 64 bits, without the library.  Draws have no such value (and neither has what follows
+    from them); None for the sampler alone and for a batch whose forward in 64 bits would take too long."""
+    if case["kind"] == "sample":
+        return None
+    mc, n, G = MODELS[case["model"]], case["groups"], case["G"]
+    if case["kind"] != "train_step" and _exact_flops(case) > 4e14:
+        return None
+    m, plen, w, prompts, cached, rng = _inputs(case, seed)
+    rewards = (rng.random((n, G)) < 0.5).astype(np.float32).astype(np.float64)
+    centred, std = rewards - rewards.mean(axis=1, keepdims=True), rewards.std(axis=1, keepdims=True)
+    adv = torch.from_numpy(np.where(std > 0, centred / np.where(std > 0, std, 1.0), 0.0))
+    if case["kind"] == "train_step":
+        return dict(tokens=None, sample_logprobs=None, logprobs=None, advantages=adv, token_values=None)
+    max_m = int(m.max())
+    forced = rng.integers(0, mc.vocab, size=(max_m, n * G), dtype=np.int32)
+    prefix = [np.concatenate([p, a[: case["answer"] - k]]) for p, a, k in zip(prompts, cached, m)]
+    if case["kind"] == "score":
+        rows = list(range(n * G))
+        last, own = _forward(mc, w, prefix, [(r // G, forced[: max(int(m[r // G]) - 1, 0), r]) for r in rows])
+        out = []
+        for r, z in zip(rows, own):
+            k = int(m[r // G])
+            z = torch.cat([last[r // G][None], z])[:k] / case["temperature"]
+            token = torch.from_numpy(forced[:k, r].astype(np.int64)).cuda()
+            out.append(torch.log_softmax(z, dim=1).gather(1, token[:, None])[:, 0])
+        res = dict(prefix_logits=last, logprobs=torch.cat(out))
+        return res if G == 1 else dict(res, advantages=adv)
+    alive = _lengths(case, m) if case["kind"] == "compact" else np.repeat(m, G)
+    rows = np.flatnonzero(alive > max_m - 1)
+    last, own = _forward(mc, w, prefix, [(int(r) // G, forced[: max_m - 1, r]) for r in rows], last_only=True)
+    return dict(prefix_logits=last, step_logits=torch.cat(own))
+
+
+def _exact_flops(case):
+    mc = MODELS[case["model"]]
+    m, plen = _shapes(case)
+    params = mc.n_layers * (mc.qkv_rows + mc.n_q_heads * mc.head_dim + 3 * mc.d_ffn) * mc.d_model
+    own = m.sum() * case["G"] if case["kind"] == "score" else 2 * m.max() * case["G"]
+    return 2.0 * params * float((plen + case["answer"] - m).sum() + own)
+
+
+def _forward(mc, w, prefix, suffixes, last_only=False):
+    """Logits after every prefix, and after every (or the last) token of suffixes [(prefix index, tokens)]."""
+    seqs = [np.asarray(t) for t in prefix] + [np.asarray(t) for _, t in suffixes]
+    base = [0] * len(prefix) + [len(prefix[g]) for g, _ in suffixes]
+    cu = np.concatenate([[0], np.cumsum([len(t) for t in seqs])]).astype(np.int64)
+    pos = torch.from_numpy(np.concatenate([b + np.arange(len(t)) for b, t in zip(base, seqs)])).cuda()
+    tokens = torch.from_numpy(np.concatenate(seqs).astype(np.int64)).cuda()
+    Hq, Hkv, dh = mc.n_q_heads, mc.n_kv_heads, mc.head_dim
+    theta = mc.rope_base ** (-2.0 * torch.arange(dh // 2, dtype=torch.float64, device="cuda") / dh)
+    ang = pos.double()[:, None] * theta
+    cos, sin = ang.cos()[:, None], ang.sin()[:, None]
+
+    def norm(x, gain):
+        return x * torch.rsqrt((x * x).mean(dim=1, keepdim=True) + mc.rms_eps) * gain.double()
+
+    def rotate(x):
+        a, b = x[..., : dh // 2], x[..., dh // 2:]
+        return torch.cat([a * cos - b * sin, b * cos + a * sin], dim=-1)
+
+    def attend(q, k, v):                      # q [t, Hq, dh] are the last t positions of k, v [T, Hkv, dh]
+        t, T = q.shape[0], k.shape[0]
+        k, v = (x.repeat_interleave(Hq // Hkv, dim=1).transpose(0, 1).contiguous() for x in (k, v))
+        hidden = torch.ones(t, T, dtype=torch.bool, device="cuda").triu(T - t + 1)
+        s = torch.matmul(q.transpose(0, 1).contiguous(), k.transpose(1, 2).contiguous()) / math.sqrt(dh)
+        p = torch.softmax(s.masked_fill_(hidden, -math.inf), dim=-1)
+        return torch.matmul(p, v).transpose(0, 1).reshape(t, Hq * dh)
+
+    x = w["embed"][tokens].double()
+    for lw in w["layers"]:
+        qkv = (norm(x, lw["attn_norm"]) @ lw["wqkv"].double().t()).view(-1, Hq + 2 * Hkv, dh)
+        q, k, v = rotate(qkv[:, :Hq]), rotate(qkv[:, Hq:Hq + Hkv]), qkv[:, Hq + Hkv:]
+        o = torch.empty(x.shape[0], Hq * dh, dtype=torch.float64, device="cuda")
+        for i in range(len(seqs)):
+            own = slice(int(cu[i]), int(cu[i + 1]))
+            if own.start == own.stop:
+                continue
+            parts = [own]
+            if i >= len(prefix):
+                g = suffixes[i - len(prefix)][0]
+                parts = [slice(int(cu[g]), int(cu[g + 1])), own]
+            o[own] = attend(q[own], torch.cat([k[p] for p in parts]), torch.cat([v[p] for p in parts]))
+        x = x + o @ lw["wo"].double().t()
+        gate_up, down = lw["w_gate_up"].double().t(), lw["w_down"].double().t()
+        for c in range(0, x.shape[0], 16384):
+            gu = norm(x[c:c + 16384], lw["ffn_norm"]) @ gate_up
+            x[c:c + 16384] += (torch.nn.functional.silu(gu[:, : mc.d_ffn]) * gu[:, mc.d_ffn:]) @ down
+    x, head = norm(x, w["final_norm"]), w["lm_head"].double().t()
+    ends = torch.from_numpy(cu[1:] - 1).cuda()
+    last = x[ends[: len(prefix)]] @ head
+    own = [x[int(cu[i + 1]) - 1 if last_only else int(cu[i]):int(cu[i + 1])] @ head
+           for i in range(len(prefix), len(seqs))]
+    return last, own
 
 
 # ---------------------------------------------------------------------------------------------
