@@ -1247,6 +1247,16 @@ bool rope_direct(const GemmArgs& a) {
            a.N == (a.rope->Hq + 2 * a.rope->Hkv) * 128 && a.path != 2;
 }
 
+// What gemm_dma2_kernel needs beyond whole 64-deep slabs: at least as many slabs as stages in every K split, and
+// the weight rows (from the matrix start) and a tile's activation rows within reach of a 32-bit byte offset.
+bool dma2_ok(const GemmArgs& a, int splits, int stages = 2) {
+    const int k_per_split = ceil_div(ceil_div(a.K, splits), kBK) * kBK;
+    return a.K % kBK == 0 && a.path != 2 && k_per_split >= stages * kBK &&
+           a.K - (splits - 1) * k_per_split >= stages * kBK &&
+           (uint64_t)a.N * (uint64_t)a.ldw * sizeof(bf16) < (1ull << 32) &&
+           (uint64_t)256 * (uint64_t)a.lda * sizeof(bf16) < (1ull << 32);  // a tile's activation rows as well
+}
+
 TileCfg pick_tile(const GemmArgs& a) {
     if (a.path >= 16) {  // tuning aid: a fixed tile shape
         switch (a.path - 16) {
@@ -1255,11 +1265,11 @@ TileCfg pick_tile(const GemmArgs& a) {
             case kKidGemm32: return TileCfg{kKidGemm32, 32, 128};
             case kKidGemm64x64: return TileCfg{kKidGemm64x64, 64, 64};
             case kKidGemm256x160:  // fused gate/up only
-                if (a.epilogue == kEpiSwiglu && a.K % kBK == 0 && (a.N / 2) % 16 == 0)
+                if (a.epilogue == kEpiSwiglu && dma2_ok(a, 1, 3) && (a.N / 2) % 16 == 0)
                     return TileCfg{kKidGemm256x160, 256, 160};
                 return TileCfg{kKidGemm256, 256, 256};
             case kKidGemm256x192:  // its fused gate/up epilogue exists on the direct-to-LDS kernel only
-                if (a.epilogue != kEpiSwiglu || (a.K % kBK == 0 && (a.N / 2) % 16 == 0))
+                if (a.epilogue != kEpiSwiglu || (dma2_ok(a, 1) && (a.N / 2) % 16 == 0))
                     return TileCfg{kKidGemm256x192, 256, 192};
                 return TileCfg{kKidGemm256, 256, 256};
             default: return TileCfg{kKidGemm64, 64, 128};
@@ -1271,14 +1281,16 @@ TileCfg pick_tile(const GemmArgs& a) {
     // four-deep load pipeline beat wider tiles whose K-split partial sums need a second kernel;
     // with a deep K, 128x128 tiles split along K.
     const int t256 = ceil_div(a.M, 256) * ceil_div(a.N, 256);
+    // The two narrower tiles interleave gate and up rows as only gemm_dma2_kernel does: what it does not take
+    // (a single K slab, for one) stays with the tiles whose register-staged form is right.
     // The gate/up projection of a decode step: one round of fewer 256x256 tiles than CUs; 256x192
     // tiles still fit one round and each is a quarter cheaper.
-    if (a.epilogue == kEpiSwiglu && a.M > 128 && t256 >= 128 && t256 <= 256 && a.K % kBK == 0 && a.path != 2 &&
+    if (a.epilogue == kEpiSwiglu && a.M > 128 && t256 >= 128 && t256 <= 256 && dma2_ok(a, 1) &&
         (a.N / 2) % 16 == 0 && ceil_div(a.M, 256) * ceil_div(a.N, 192) <= 256) {
         // 256x160 tiles (four waves of 64x160, three stages) still fit one round and put work on more CUs.
         // Measured with weights streamed from HBM: K = 1536, N = 17920, 512 rows: 39.2 -> 34.3 us;
         // K = 3584, N = 37888, 256 rows: 87.5 -> 78.8 us.
-        if (a.K >= 3 * kBK && ceil_div(a.M, 256) * ceil_div(a.N, 160) <= 256) return TileCfg{kKidGemm256x160, 256, 160};
+        if (dma2_ok(a, 1, 3) && ceil_div(a.M, 256) * ceil_div(a.N, 160) <= 256) return TileCfg{kKidGemm256x160, 256, 160};
         return TileCfg{kKidGemm256x192, 256, 192};
     }
     // up to 128 rows a 256-row tile multiplies mostly padding
@@ -1336,16 +1348,6 @@ bool rope_fusable(const GemmArgs& a) {
 bool norm_fusable(const GemmArgs& a) {
     return a.norm_out && a.N <= 8192 && a.N % 4 == 0 && a.ldc % 4 == 0 && ((uintptr_t)a.C % 16 == 0) &&
            ((uintptr_t)a.norm_out % 8 == 0) && ((uintptr_t)a.norm_gain % 8 == 0);
-}
-
-// What gemm_dma2_kernel needs beyond whole 64-deep slabs: at least as many slabs as stages in every K split, and
-// the weight rows (from the matrix start) and a tile's activation rows within reach of a 32-bit byte offset.
-bool dma2_ok(const GemmArgs& a, int splits, int stages = 2) {
-    const int k_per_split = ceil_div(ceil_div(a.K, splits), kBK) * kBK;
-    return a.K % kBK == 0 && a.path != 2 && k_per_split >= stages * kBK &&
-           a.K - (splits - 1) * k_per_split >= stages * kBK &&
-           (uint64_t)a.N * (uint64_t)a.ldw * sizeof(bf16) < (1ull << 32) &&
-           (uint64_t)256 * (uint64_t)a.lda * sizeof(bf16) < (1ull << 32);  // a tile's activation rows as well
 }
 
 template <int BM, int BN, int WM, int WN, int EPI, int SWIGLU, int DST = kDmaStages, int DBK = kDmaBK>
