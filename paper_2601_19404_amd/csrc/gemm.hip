@@ -23,6 +23,7 @@
 //    the MFMA operands swapped, which leaves a lane with one row and runs of four columns.
 //  * gemm_mfma_kernel: the same tiling with register-staged LDS fills, for K that is not a
 //    multiple of 64 (and selectable for comparison).
+//  * skinny.hip: up to 64 rows, K a multiple of 64.
 //  * gemm_generic_kernel: any dtype on the vector ALUs (fp32 tiny model, shapes the
 //    MFMA kernels do not take).
 #include "kernels.hpp"
@@ -31,9 +32,6 @@ namespace rpo {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
-
-// g * sigmoid(g); the hardware reciprocal (1 ulp) replaces the IEEE division sequence
-__device__ inline float silu_f(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
 // ---------------------------------------------------------------------------
 // generic kernel: 64x64 tile, 16-deep slabs, 256 threads, 4x4 outputs per thread
@@ -1257,6 +1255,15 @@ bool dma2_ok(const GemmArgs& a, int splits, int stages = 2) {
            (uint64_t)256 * (uint64_t)a.lda * sizeof(bf16) < (1ull << 32);  // a tile's activation rows as well
 }
 
+// A handful of rows: the weight-streaming kernel of skinny.hip (figures there; at 64 rows it is ahead of the
+// 64-row tiles on every projection, by 1.1x (down) to 1.6x (QKV)).
+constexpr int kSkinnyRows = 64;
+bool skinny_ok(const GemmArgs& a) {
+    return a.path == 0 && a.M <= kSkinnyRows && a.K % kBK == 0 && !a.lse && mfma_ok(a) &&
+           (uint64_t)a.N * (uint64_t)a.ldw * sizeof(bf16) < (1ull << 32) &&  // 32-bit load offsets
+           (uint64_t)a.M * (uint64_t)a.lda * sizeof(bf16) < (1ull << 32);
+}
+
 TileCfg pick_tile(const GemmArgs& a) {
     if (a.path >= 16) {  // tuning aid: a fixed tile shape
         switch (a.path - 16) {
@@ -1423,6 +1430,39 @@ hipError_t launch_one(const GemmArgs& a, int splits, void* out, hipStream_t s) {
     }
 }
 
+// Sum the partial sums in a.ws and apply the epilogue (with the rotary embedding or the RMSNorm that follows,
+// where rope_fusable / norm_fusable say so).
+hipError_t launch_splitk_reduce(const GemmArgs& a, int splits, hipStream_t s) {
+    const int64_t n_out = a.epilogue == kEpiSwiglu ? (int64_t)a.M * (a.N / 2) : (int64_t)a.M * a.N;
+    const unsigned blocks = (unsigned)ceil_div64(n_out, 256);
+    const float* P = (const float*)a.ws;
+    switch (a.epilogue) {
+        case kEpiStore:
+            if (rope_fusable(a)) {
+                gemm_splitk_reduce_rope_kernel<<<a.M, 256, (size_t)a.N * 4, s>>>(P, splits, a.M, a.N, *a.rope);
+                return hipGetLastError();
+            }
+            gemm_splitk_reduce_kernel<kEpiStore><<<blocks, 256, 0, s>>>(P, splits, a.M, a.N, a.C, a.ldc);
+            break;
+        case kEpiStoreF32:
+            gemm_splitk_reduce_kernel<kEpiStoreF32><<<blocks, 256, 0, s>>>(P, splits, a.M, a.N, a.C, a.ldc);
+            break;
+        case kEpiAddF32:
+            if (norm_fusable(a)) {
+                gemm_splitk_reduce_norm_kernel<<<a.M, 256, 0, s>>>(P, splits, a.M, a.N, (float*)a.C, a.ldc,
+                                                                    (const bf16*)a.norm_gain, a.norm_eps,
+                                                                    (bf16*)a.norm_out);
+                return hipGetLastError();
+            }
+            gemm_splitk_reduce_kernel<kEpiAddF32><<<blocks, 256, 0, s>>>(P, splits, a.M, a.N, a.C, a.ldc);
+            break;
+        default:
+            gemm_splitk_reduce_kernel<kEpiSwiglu><<<blocks, 256, 0, s>>>(P, splits, a.M, a.N, a.C, a.ldc);
+            break;
+    }
+    return hipGetLastError();
+}
+
 template <int BM, int BN, int WM, int WN, int DST = kDmaStages, int DBK = kDmaBK>
 hipError_t launch_tile(const GemmArgs& a, int splits, hipStream_t s) {
     const bool sw = a.epilogue == kEpiSwiglu;
@@ -1437,34 +1477,7 @@ hipError_t launch_tile(const GemmArgs& a, int splits, hipStream_t s) {
             e = launch_one<BM, BN, WM, WN, kEpiPartial, false, DST, DBK>(a, splits, a.ws, s);
         }
         if (e != hipSuccess) return e;
-        const int64_t n_out = sw ? (int64_t)a.M * (a.N / 2) : (int64_t)a.M * a.N;
-        const unsigned blocks = (unsigned)ceil_div64(n_out, 256);
-        const float* P = (const float*)a.ws;
-        switch (a.epilogue) {
-            case kEpiStore:
-                if (rope_fusable(a)) {
-                    gemm_splitk_reduce_rope_kernel<<<a.M, 256, (size_t)a.N * 4, s>>>(P, splits, a.M, a.N, *a.rope);
-                    return hipGetLastError();
-                }
-                gemm_splitk_reduce_kernel<kEpiStore><<<blocks, 256, 0, s>>>(P, splits, a.M, a.N, a.C, a.ldc);
-                break;
-            case kEpiStoreF32:
-                gemm_splitk_reduce_kernel<kEpiStoreF32><<<blocks, 256, 0, s>>>(P, splits, a.M, a.N, a.C, a.ldc);
-                break;
-            case kEpiAddF32:
-                if (norm_fusable(a)) {
-                    gemm_splitk_reduce_norm_kernel<<<a.M, 256, 0, s>>>(P, splits, a.M, a.N, (float*)a.C, a.ldc,
-                                                                        (const bf16*)a.norm_gain, a.norm_eps,
-                                                                        (bf16*)a.norm_out);
-                    return hipGetLastError();
-                }
-                gemm_splitk_reduce_kernel<kEpiAddF32><<<blocks, 256, 0, s>>>(P, splits, a.M, a.N, a.C, a.ldc);
-                break;
-            default:
-                gemm_splitk_reduce_kernel<kEpiSwiglu><<<blocks, 256, 0, s>>>(P, splits, a.M, a.N, a.C, a.ldc);
-                break;
-        }
-        return hipGetLastError();
+        return launch_splitk_reduce(a, splits, s);
     }
     switch (a.epilogue) {
         case kEpiStore:
@@ -1518,6 +1531,7 @@ int gemm_fuses_lse(const GemmArgs& a) {
 }
 
 int gemm_fuses_max(const GemmArgs& a) {
+    if (skinny_ok(a)) return (a.epilogue != kEpiStoreF32 || a.N % 4 != 0) ? 0 : ceil_div(a.N, 64);
     if (gemm_fuses_lse(a) == 0) return 0;  // same kernel shape
     // the transposed epilogue stores 16-byte column quads
     if (a.N % 4 != 0 || a.ldc % 4 != 0 || (uintptr_t)a.C % 16 != 0) return 0;
@@ -1535,6 +1549,7 @@ size_t gemm_splitk_scratch_bytes(const GemmArgs& a) {
 
 int gemm_kernel_id(const GemmArgs& a) {
     if (!mfma_ok(a)) return kKidGemmGeneric;
+    if (skinny_ok(a)) return kKidNone;
     const int id = pick_tile(a).id;
     // the heaviest instantiation of a rollout step is reported on its own
     return (id == kKidGemm256 && a.epilogue == kEpiSwiglu) ? (int)kKidGemm256Swiglu : id;
@@ -1577,6 +1592,21 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
     bool norm_done = false, rope_done = false;
     if (!mfma_ok(a)) {
         e = a.dtype == kF32 ? launch_generic<float>(a, s) : launch_generic<bf16>(a, s);
+    } else if (skinny_ok(a)) {
+        int epi = a.epilogue;
+        if (rope_direct(a)) {
+            epi = kEpiRope;
+            rope_done = true;
+        } else if (a.block_max && gemm_fuses_max(a) > 0) {
+            epi = kEpiLogitsMax;
+            a.block_max->blocks = gemm_fuses_max(a);
+        }
+        const int splits = gemm_skinny_splits(a);
+        e = launch_gemm_skinny(a, epi, splits, s);
+        if (e == hipSuccess && splits > 1) {
+            e = launch_splitk_reduce(a, splits, s);
+            norm_done = want_norm && norm_fusable(a);
+        }
     } else {
         const TileCfg t = pick_tile(a);
         const int splits = (a.ws && a.ws_bytes) ? pick_splits(a, t) : 1;

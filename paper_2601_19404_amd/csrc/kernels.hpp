@@ -6,6 +6,9 @@
 
 namespace rpo {
 
+// g * sigmoid(g); the hardware reciprocal (1 ulp) replaces the IEEE division sequence
+__device__ inline float silu_f(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
+
 enum DType : int { kF32 = 0, kBF16 = 1 };
 
 inline size_t dtype_size(int dt) { return dt == kF32 ? 4 : 2; }
@@ -71,6 +74,12 @@ struct GemmArgs {
     LseFuse* block_max = nullptr;
 };
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
+// The weight-streaming kernel for up to 64 rows (bf16, K a multiple of 64, 16-byte aligned rows: checked by
+// launch_gemm).  epi: kEpiStore / kEpiStoreF32 / kEpiAddF32 / kEpiSwiglu, kEpiRope (a.rope, head_dim 128) or
+// kEpiLogitsMax (a.block_max: row maxima per 64 columns).
+// splits > 1: fp32 partial sums of that many K ranges to a.ws[splits][M][N] instead.
+hipError_t launch_gemm_skinny(const GemmArgs& a, int epi, int splits, hipStream_t s);
+int gemm_skinny_splits(const GemmArgs& a);
 // Whether launch_gemm would honour GemmArgs::lse for these arguments, and with how many column
 // blocks per row (0 = it would write C as usual).
 int gemm_fuses_lse(const GemmArgs& a);

@@ -1,0 +1,394 @@
+// C[M,N] (op)= A[M,K] * W[N,K]^T for a handful of rows (bf16 operands, fp32 accumulation): the
+// contractions of a decode step of a small batch.
+//
+// What bounds them is how fast a CU can be fed: 64 rows use a weight 64 times, far from what the matrix
+// cores need to be the limit, and every weight byte comes from HBM once per decode step (the layers
+// together are larger than every cache).  Measured on this chip, all CUs reading: loads of whole
+// 128-byte lines into LDS reach 120 GB/s per CU from L2 and 7.5 TB/s from HBM; the fragment layout
+// loaded straight into registers (16 rows x 64 bytes per instruction) reaches 38 GB/s per CU from L2
+// whatever is in flight, and a kernel built on it lost to the 64-row tiles from 16 rows on.  Hence:
+//   * weights and activations go to LDS in pieces of 8 rows x 128 bytes, and every wave has a ring of
+//     its own that only it reads: the main loop has no barrier, a wave waits for its own loads only;
+//   * K is split over the NW waves of a workgroup (wave w takes slabs w, w + NW, ...), so a narrow
+//     projection still puts every CU to work; the partial sums meet in LDS, in a fixed order;
+//   * 8 rows of activations move 8 rows, not a padded tile of 64: the loads are what is paid for;
+//   * the weight rows are the A operand of v_mfma_f32_16x16x32_bf16 and the activations the B operand:
+//     a lane then holds one activation row and four consecutive columns of the result.
+// Against the 32x128 / 64x64 / 64x128 tiles of gemm.hip, weights streamed from HBM, 8 / 32 / 64 rows, us:
+//   K = 1536: N = 2048 (QKV) 8.1 / 8.3 / 8.3 -> 3.4 / 4.1 / 5.2; N = 17920 (gate/up) 15.3 / 16.7 / 18.7 ->
+//   11.7 / 13.1 / 15.1; K = 8960, N = 1536 (down, with its reduction) 15.3 / 16.0 / 17.2 -> 12.0 / 13.3 / 14.3;
+//   K = 3584: N = 3584 (O) 12.7 / 13.5 / 14.9 -> 7.6 / 11.0 / 12.8; N = 37888 (gate/up) 61.9 / 63.5 / 68.7 ->
+//   49.8 / 51.3 / 57.4 (5.5 TB/s of weights at 8 rows).
+#include "kernels.hpp"
+
+namespace rpo {
+
+namespace {
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x4_t __attribute__((ext_vector_type(4)));
+
+// 16 bytes per lane from global memory (uniform base + 32-bit lane offset) straight into LDS at
+// lds_byte_addr + 16 * lane.  The compiler does not see the load: every wait for it is written out.
+__device__ inline void dma_load16_s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr) {
+    asm volatile(
+        "s_mov_b32 m0, %2\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %0, %1\n\t"
+        :
+        : "v"(voff), "s"(sbase), "s"(lds_byte_addr)
+        : "memory");
+}
+template <int N>
+__device__ inline void wait_loads() {  // all but the newest N loads of this wave have landed
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// MA 8-row blocks of activations, NB 16-row blocks of weights per workgroup, NW waves (K split), rings of S
+// slabs of 64 K values.  The weight rows of block t:
+//   kEpiSwiglu: gate rows 8 q .. 8 q + 7, then up rows F + 8 q .. F + 8 q + 7, q = NB blockIdx.x + t
+//   kEpiRope:   of head u / 8 the channels i0 .. i0 + 7 and 64 + i0 .. 64 + i0 + 7, u = NB blockIdx.x + t,
+//               i0 = 8 (u % 8): the rotation pairs sit in one block (head_dim 128)
+//   otherwise:  16 (NB blockIdx.x + t) ..
+// kEpiPartial: workgroup (b, z) multiplies K slabs [z slabs_per_split, ...) only and stores fp32 partial sums to
+// Cv[z][M][N] (ldc is not used).
+template <int MA, int NB, int NW, int S, int EPI>
+__global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __restrict__ A, int64_t lda,
+                                                              const bf16* __restrict__ W, int64_t ldw,
+                                                              void* __restrict__ Cv, int64_t ldc, int M, int N,
+                                                              int K, int slabs_per_split, RopeKvArgs rk,
+                                                              LseFuse lf) {
+    static_assert(EPI != kEpiLogitsMax || NB == 4, "row maxima are kept per 64 columns");
+    constexpr int MB = (MA + 1) / 2;  // 16-column MFMA blocks of activations (MA = 1: rows 0 .. 7 twice)
+    constexpr int ROWS = MB * 16, COLS = NB * 16;
+    constexpr int LD = COLS + 4;      // fp32 row of the partial sums, 16-byte pieces
+    constexpr int INST = 2 * NB + MA;  // loads per slab; each fills 1 KiB of LDS (8 rows x 128 bytes)
+    constexpr int STAGE = INST * 1024;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // rings [NW][S][STAGE], then partial sums
+    float* part = (float*)smem;                                          // [NW][ROWS][LD]
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int b = blockIdx.x;
+    const int F = N / 2;
+
+    // Load addressing: an instruction fills 8 rows; lane l stores piece position l % 8 of row l / 8 and fetches
+    // piece (l % 8) ^ swizzle(row), which spreads the fragment reads over the LDS banks.
+    uint32_t off[INST];
+#pragma unroll
+    for (int j = 0; j < INST; ++j) {
+        const int l8 = lane >> 3;                   // row in the 8-row group
+        const int half = j < 2 * NB ? (j & 1) : ((j - 2 * NB) & 1);  // which half of a 16-row block
+        const int piece = (lane & 7) ^ l8 ^ half;
+        if (j < 2 * NB) {
+            const int t = j >> 1;
+            int row;
+            if (EPI == kEpiSwiglu)
+                row = half * F + min((b * NB + t) * 8 + l8, F - 1);
+            else if (EPI == kEpiRope)
+                row = ((b * NB + t) >> 3) * 128 + half * 64 + ((b * NB + t) & 7) * 8 + l8;
+            else
+                row = min((b * NB + t) * 16 + half * 8 + l8, N - 1);
+            off[j] = (uint32_t)(((int64_t)row * ldw + piece * 8) * 2);
+        } else {
+            off[j] = (uint32_t)(((int64_t)min((j - 2 * NB) * 8 + l8, M - 1) * lda + piece * 8) * 2);
+        }
+    }
+    const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + wave * (S * STAGE);
+    const unsigned char* ring_p = smem + wave * (S * STAGE);
+
+    f32x4_t acc[MB][NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int t = 0; t < NB; ++t) acc[i][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    // this wave's slabs: wave + i * NW, i < n_my, counted from the workgroup's own first slab: every workgroup
+    // reads the same activations, and those running together then ask the L2 for different lines
+    const int slab0 = EPI == kEpiPartial ? (int)blockIdx.y * slabs_per_split : 0;
+    const int n_slabs = EPI == kEpiPartial ? min(slabs_per_split, (K >> 6) - slab0) : K >> 6;
+    const int n_my = n_slabs > wave ? (n_slabs - wave + NW - 1) / NW : 0;
+    const int rot = (int)((unsigned)b * 5u % (unsigned)n_slabs);
+    auto issue = [&](int i, int st) __attribute__((always_inline)) {
+        int sl = wave + i * NW + rot;
+        sl = sl >= n_slabs ? sl - n_slabs : sl;
+        sl += slab0;
+        const bf16* wb = W + sl * 64;
+        const bf16* ab = A + sl * 64;
+#pragma unroll
+        for (int j = 0; j < INST; ++j) dma_load16_s(j < 2 * NB ? wb : ab, off[j], ring + st * STAGE + j * 1024);
+    };
+    const int sw = (r & 7) ^ (r >> 3);
+    const int ar = MA == 1 ? (r & 7) : r, asw = MA == 1 ? (r & 7) : sw;
+    auto multiply = [&](int st) __attribute__((always_inline)) {
+        const unsigned char* base = ring_p + st * STAGE;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            bf16x8_t wf[NB], af[MB];
+#pragma unroll
+            for (int t = 0; t < NB; ++t)
+                wf[t] = *(const bf16x8_t*)(base + t * 2048 + r * 128 + (((4 * h + g) ^ sw) << 4));
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+                af[m] = *(const bf16x8_t*)(base + NB * 2048 + m * 2048 + ar * 128 + (((4 * h + g) ^ asw) << 4));
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                for (int t = 0; t < NB; ++t)
+                    acc[m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[t], af[m], acc[m][t], 0, 0, 0);
+        }
+    };
+    // No barrier in the loop: a wave loads and reads its own ring only.
+#pragma unroll
+    for (int i = 0; i < S - 1; ++i)
+        if (i < n_my) issue(i, i);
+    int st = 0;
+#pragma clang loop unroll(disable)
+    for (int i = 0; i < n_my; ++i) {
+        const int ahead = n_my - 1 - i;  // slabs after this one
+        if (ahead >= S - 1) {
+            // the stage that slab i - 1 has left: its reads are done before new data can arrive
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            issue(i + S - 1, st == 0 ? S - 1 : st - 1);
+            wait_loads<(S - 1) * INST>();
+        } else if (S > 3 && ahead == 2) {
+            wait_loads<2 * INST>();
+        } else if (S > 2 && ahead == 1) {
+            wait_loads<INST>();
+        } else {
+            wait_loads<0>();
+        }
+        multiply(st);
+        st = st + 1 == S ? 0 : st + 1;
+    }
+    __syncthreads();  // the rings are free: the partial sums take their place
+    {
+        float* dst = part + ((size_t)wave * ROWS + r) * LD + 4 * g;
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int t = 0; t < NB; ++t) *(f32x4_t*)(dst + m * 16 * LD + t * 16) = acc[m][t];
+    }
+    __syncthreads();
+
+    // four consecutive columns of row m, summed over the waves in order
+    auto total = [&](int m, int c) __attribute__((always_inline)) {
+        f32x4_t v = *(const f32x4_t*)(part + m * LD + c);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v += *(const f32x4_t*)(part + (w * ROWS + m) * LD + c);
+        return v;
+    };
+
+    if constexpr (EPI == kEpiSwiglu) {
+        const bool vec = (ldc & 3) == 0 && ((uintptr_t)Cv & 7) == 0;
+        for (int it = tid; it < ROWS * NB * 2; it += NW * 64) {
+            const int m = it / (NB * 2), q = it % (NB * 2);
+            const int c = (q >> 1) * 16 + (q & 1) * 4, oc = (b * NB + (q >> 1)) * 8 + (q & 1) * 4;
+            if (m >= M) continue;
+            const f32x4_t gate = total(m, c), up = total(m, 8 + c);
+            u16x4_t o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16(silu_f(gate[e]) * up[e]).bits;
+            bf16* dst = (bf16*)Cv + (int64_t)m * ldc + oc;
+            if (vec && oc + 3 < F) {
+                *(u16x4_t*)dst = o;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (oc + e < F) dst[e].bits = o[e];
+            }
+        }
+    } else if constexpr (EPI == kEpiRope) {
+        const int pt = rk.geom.page_tokens;
+        for (int it = tid; it < ROWS * NB * 2; it += NW * 64) {
+            const int m = it / (NB * 2), q = it % (NB * 2);
+            const int unit = b * NB + (q >> 1), head = unit >> 3;
+            const int c = (q >> 1) * 16 + (q & 1) * 4, ch = (unit & 7) * 8 + (q & 1) * 4;
+            if (m >= M) continue;
+            const f32x4_t x1 = total(m, c), x2 = total(m, 8 + c);
+            int pos = -1;
+            int64_t page = 0;
+            const int seq = rk.row_seq ? rk.row_seq[m] : m;
+            if (seq >= 0 && !(rk.active && !rk.active[m])) {
+                const SeqDesc sd = rk.seqs[seq];
+                pos = sd.pos0 + (rk.single_row ? 0 : m - sd.row_start) + rk.pos_add;
+                page = rk.tables[sd.table_off + pos / pt];
+            }
+            bf16* pool = (bf16*)rk.kv_pool;
+            if (head >= rk.Hq + rk.Hkv) {
+                if (pos < 0) continue;
+                bf16* v = pool + rk.geom.v_block(rk.layer, page, head - rk.Hq - rk.Hkv);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[rk.geom.v_elem(pos % pt, ch + e)] = f32_to_bf16(x1[e]);
+                    v[rk.geom.v_elem(pos % pt, ch + e + 64)] = f32_to_bf16(x2[e]);
+                }
+                continue;
+            }
+            u16x4_t y1, y2;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float a1 = x1[e], a2 = x2[e];
+                if (pos >= 0) {  // a finished rollout keeps an unrotated q
+                    const float2 cs = *(const float2*)(rk.rope + ((int64_t)pos * 64 + ch + e) * 2);
+                    a1 = x1[e] * cs.x - x2[e] * cs.y;
+                    a2 = x2[e] * cs.x + x1[e] * cs.y;
+                }
+                y1[e] = f32_to_bf16(a1).bits;
+                y2[e] = f32_to_bf16(a2).bits;
+            }
+            bf16* dst;
+            if (head < rk.Hq) {
+                dst = (bf16*)Cv + (int64_t)m * ldc + head * 128 + ch;
+            } else {
+                if (pos < 0) continue;
+                dst = pool + rk.geom.k_block(rk.layer, page, head - rk.Hq) + (int64_t)(pos % pt) * 128 + ch;
+            }
+            *(u16x4_t*)dst = y1;
+            *(u16x4_t*)(dst + 64) = y2;
+        }
+    } else {
+        constexpr int QPR = COLS / 4;  // column quads per row
+        if constexpr (EPI == kEpiPartial) {
+            Cv = (float*)Cv + (int64_t)blockIdx.y * M * N;
+            ldc = N;
+        }
+        const bool vec = EPI == kEpiStore ? (ldc & 3) == 0 && ((uintptr_t)Cv & 7) == 0
+                                          : (ldc & 3) == 0 && ((uintptr_t)Cv & 15) == 0;
+        for (int it = tid; it < ROWS * QPR; it += NW * 64) {
+            const int m = it / QPR, c = (it % QPR) * 4, n = b * COLS + c;
+            if (m >= M) continue;  // all lanes of a row's quads together
+            const f32x4_t v = total(m, c);
+            if constexpr (EPI == kEpiStore) {
+                bf16* dst = (bf16*)Cv + (int64_t)m * ldc + n;
+                u16x4_t o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16(v[e]).bits;
+                if (vec && n + 3 < N) {
+                    *(u16x4_t*)dst = o;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (n + e < N) dst[e].bits = o[e];
+                }
+            } else {
+                float* dst = (float*)Cv + (int64_t)m * ldc + n;
+                if (vec && n + 3 < N) {
+                    *(f32x4_t*)dst = EPI == kEpiAddF32 ? *(const f32x4_t*)dst + v : v;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (n + e < N) dst[e] = EPI == kEpiAddF32 ? dst[e] + v[e] : v[e];
+                }
+                if constexpr (EPI == kEpiLogitsMax) {  // N is a multiple of 4 (checked by the launcher): whole quads
+                    float mx = n < N ? fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])) : -INFINITY;
+#pragma unroll
+                    for (int o = 1; o < QPR; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+                    if (c == 0) lf.part[(int64_t)m * lf.blocks + b] = mx;
+                }
+            }
+        }
+    }
+}
+
+// LDS of one workgroup: the rings, or the partial sums that follow them.
+template <int MA, int NB, int NW, int S>
+constexpr size_t skinny_lds() {
+    constexpr size_t rings = (size_t)NW * S * (2 * NB + MA) * 1024;
+    constexpr size_t sums = (size_t)NW * ((MA + 1) / 2) * 16 * (NB * 16 + 4) * sizeof(float);
+    return rings > sums ? rings : sums;
+}
+
+// PER_CU workgroups share a CU's 160 KiB of LDS; the ring is as deep as that allows, at most four slabs.
+template <int MA, int NB, int NW, int PER_CU, int EPI>
+hipError_t launch_one(const GemmArgs& a, int blocks, hipStream_t s, int splits = 1, void* out = nullptr) {
+    constexpr int kFit = 160 / PER_CU / (NW * (2 * NB + MA));
+    constexpr int S = kFit < 4 ? kFit : 4;
+    static_assert(S >= 2, "the ring needs two slabs");
+    constexpr size_t lds = skinny_lds<MA, NB, NW, S>();
+    static_assert(lds * PER_CU <= 160 * 1024, "LDS");
+    auto kern = gemm_skinny_kernel<MA, NB, NW, S, EPI>;
+    static bool attr_set = false;  // one flag per template instance
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    kern<<<dim3((unsigned)blocks, (unsigned)splits), dim3(NW * 64), lds, s>>>(
+        (const bf16*)a.A, a.lda, (const bf16*)a.W, a.ldw, out ? out : a.C, a.ldc, a.M, a.N, a.K,
+        ceil_div(a.K / 64, splits),
+        (EPI == kEpiRope && a.rope) ? *a.rope : RopeKvArgs{},
+        (EPI == kEpiLogitsMax && a.block_max) ? *a.block_max : LseFuse{});
+    return hipGetLastError();
+}
+
+template <int MA, int EPI>
+hipError_t launch_rows(const GemmArgs& a, int splits, hipStream_t s) {
+    if constexpr (EPI == kEpiSwiglu) {
+        // 40 outputs per workgroup put F = 8960 on 224 CUs in one round.  More blocks than CUs: two smaller
+        // workgroups per CU, so that one's loads cover the other's reduction.
+        const int blocks = ceil_div(a.N / 2, 8 * 5);
+        if (blocks <= 256) return launch_one<MA, 5, 4, 1, EPI>(a, blocks, s);
+        return launch_one<MA, 5, 2, 2, EPI>(a, blocks, s);
+    } else if constexpr (EPI == kEpiRope) {
+        // from 16 rows on the activations weigh as much as a block's weights: two blocks share them where that
+        // still leaves half the CUs a workgroup
+        if (MA >= 2 && a.N >= 4096) return launch_one<MA, 2, MA <= 2 ? 8 : 4, 1, EPI>(a, a.N / 32, s);
+        return launch_one<MA, 1, MA <= 2 ? 8 : 4, 2, EPI>(a, a.N / 16, s);
+    } else if constexpr (EPI == kEpiPartial) {
+        return launch_one<MA, 4, 4, 1, EPI>(a, ceil_div(a.N, 64), s, splits, a.ws);
+    } else if constexpr (EPI == kEpiLogitsMax) {
+        return launch_one<MA, 4, 2, 2, EPI>(a, ceil_div(a.N, 64), s);
+    } else {
+        if constexpr (EPI == kEpiStoreF32) {
+            if (a.N >= 16384) return launch_one<MA, 4, 2, 2, EPI>(a, ceil_div(a.N, 64), s);
+        }
+        const int blocks = ceil_div(a.N, 16);
+        if (blocks <= 256) return launch_one<MA, 1, 8, 1, EPI>(a, blocks, s);
+        return launch_one<MA, 1, MA <= 2 ? 8 : 4, 2, EPI>(a, blocks, s);
+    }
+}
+
+template <int EPI>
+hipError_t launch_epi(const GemmArgs& a, hipStream_t s, int splits = 1) {
+    if (a.M <= 8) return launch_rows<1, EPI>(a, splits, s);
+    if (a.M <= 16) return launch_rows<2, EPI>(a, splits, s);
+    if (a.M <= 32) return launch_rows<4, EPI>(a, splits, s);
+    if (a.M <= 64) return launch_rows<8, EPI>(a, splits, s);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// A deep K over a narrow N (the down projection): one workgroup per 16 columns would read all activations K deep
+// in each of them (N = 1536, K = 8960: 12.5 us at 8 rows but 25 us at 64).  Blocks of 64 columns and a K range
+// per workgroup instead, about one workgroup per CU; the sums go through memory to the reduction that also takes
+// the residual and the RMSNorm (12.0 / 14.3 us with that reduction).  A shallow K stays unsplit: its workgroups
+// would get less than eight slabs.
+int gemm_skinny_splits(const GemmArgs& a) {
+    if (a.epilogue != kEpiAddF32 || !a.ws || a.K < 4096) return 1;
+    const int tiles = ceil_div(a.N, 64), slabs = a.K / 64;
+    int splits = 256 / tiles;
+    splits = splits < slabs / 8 ? splits : slabs / 8;
+    splits = splits < 16 ? splits : 16;
+    while (splits > 1 && (size_t)splits * a.M * a.N * sizeof(float) > a.ws_bytes) --splits;
+    if (splits < 2) return 1;
+    return ceil_div(slabs, ceil_div(slabs, splits));  // every split has slabs of its own
+}
+
+hipError_t launch_gemm_skinny(const GemmArgs& a, int epi, int splits, hipStream_t s) {
+    if (splits > 1) return launch_epi<kEpiPartial>(a, s, splits);
+    switch (epi) {
+        case kEpiStore: return launch_epi<kEpiStore>(a, s);
+        case kEpiStoreF32: return launch_epi<kEpiStoreF32>(a, s);
+        case kEpiAddF32: return launch_epi<kEpiAddF32>(a, s);
+        case kEpiSwiglu: return launch_epi<kEpiSwiglu>(a, s);
+        case kEpiRope: return launch_epi<kEpiRope>(a, s);
+        case kEpiLogitsMax: return launch_epi<kEpiLogitsMax>(a, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace rpo

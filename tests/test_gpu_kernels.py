@@ -66,6 +66,16 @@ def test_gemm_mfma_bf16_model_shapes(rpo, shape, ws_mb):
         _gemm_case(rpo, *shape, torch.bfloat16, epi, path=0, seed=3, ws_mb=ws_mb)
 
 
+@pytest.mark.parametrize("M", [1, 8, 9, 16, 17, 31, 33, 64])
+@pytest.mark.parametrize("N,K", [(5, 64), (200, 192), (1536, 1536), (4100, 320), (80, 8960), (16390, 128)])
+def test_gemm_skinny_row_and_column_edges(rpo, M, N, K):
+    """The few-row kernel: edges of its 8-row loads and 16 / 64-column blocks, fewer K slabs than waves, slabs that
+    do not divide among the waves or the K ranges, padded strides, with and without a K-split workspace."""
+    for epi in (0, 1, 2):
+        for ws_mb, pad in ((0, 0), (64, 8)):
+            _gemm_case(rpo, M, N, K, torch.bfloat16, epi, path=0, seed=7, ws_mb=ws_mb, pad=pad)
+
+
 @pytest.mark.parametrize("path", [17, 19, 20, 21, 22, 27])
 @pytest.mark.parametrize("shape", [(300, 520, 1536), (77, 1536, 4480)])
 def test_gemm_mfma_bf16_every_tile_shape(rpo, shape, path):
@@ -77,7 +87,8 @@ def test_gemm_mfma_bf16_every_tile_shape(rpo, shape, path):
 
 @pytest.mark.parametrize("path,ws_mb", [(0, 0), (0, 64), (1, 0), (27, 0)])
 @pytest.mark.parametrize("M,F,K", [(512, 8960, 1536), (40, 1024, 768), (700, 256, 2048), (130, 96, 1024),
-                                   (1, 32, 64), (512, 8960, 64), (300, 18944, 3584), (264, 8032, 512), (100, 18944, 512), (200, 18944, 512)])
+                                   (1, 32, 64), (512, 8960, 64), (8, 8960, 192), (17, 416, 128), (64, 18944, 576), (33, 2592, 448),
+                                   (300, 18944, 3584), (264, 8032, 512), (100, 18944, 512), (200, 18944, 512)])
 def test_gemm_swiglu(rpo, M, F, K, path, ws_mb):
     """Fused gate/up projection: C = silu(A Wg^T) * (A Wu^T), W = [gate rows; up rows].  Path 27 forces
     the 256x192 tile (gate / up rows interleaved in blocks of 16), which path 0 picks for decode batches."""
