@@ -291,6 +291,16 @@ def test_bf16_many_rows_wide_rotary_tile(rpo):
     run_case(rpo, BF16_2KV, p, a, m, G=16)
 
 
+@pytest.mark.parametrize("d_model,lens", [(2056, (70, 33)), (1000, (20, 41)), (132, (20, 41)), (768, (1101, 990))])
+def test_rmsnorm_row_widths_and_row_counts(rpo, d_model, lens):
+    """Row norms: widths that leave a remainder in the workgroup-per-row kernel (one past 2048), and a prefill
+    chunk of more rows than it takes (one wave per row).  fp32, where the logits are held to 1e-4: with bf16
+    operands the rounding of the projections at these widths would hide an error of the norm."""
+    mcfg = synth.ModelCfg("norm-edges", 2, d_model, 4, 2, 32, 256, 512, "f32")
+    p, a, m = bf16_workload(mcfg, lens=lens, ms=(3, 5), seed=9)
+    run_case(rpo, mcfg, p, a, m, G=3, page=16)
+
+
 def long_suffix_workload(mcfg, prompt_len, lens, ms, seed):
     rng = np.random.default_rng(seed)
     prompts = [rng.integers(0, mcfg.vocab, size=prompt_len).astype(np.int32) for _ in lens]
