@@ -58,25 +58,70 @@ __device__ inline uint64_t weight_u64(float z, float zmax, float inv_t) {
     return sh >= 0 ? ((uint64_t)m << sh) : (uint64_t)(m >> (-sh));
 }
 
-// Sum over the wave of values < 2^45: two 32-bit sums (low 22 bits, high bits) so each
-// cross-lane step moves one register.
-__device__ inline uint64_t wave_sum_u45(uint64_t v) {
-    uint32_t lo = (uint32_t)v & 0x3fffffu, hi = (uint32_t)(v >> 22);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        lo += __shfl_xor(lo, o, kWave);
-        hi += __shfl_xor(hi, o, kWave);
-    }
-    return ((uint64_t)hi << 22) + lo;
+// The same weight added to a sum of weights, in fewer instructions (the sweep over a row is bound by them).
+// p 2^n is one integer operation on the bits of p (n sits in the low bits of x + 1.5 * 2^23, whose sum also
+// rounds x to the nearest integer), and the floor is the rounding of the sum itself: a double in [2^12, 2^13)
+// has a last place of 2^-40, so adding p 2^n with rounding toward zero adds floor(p 2^n * 2^40) * 2^-40, and the
+// mantissa's bits are the integer sum.  Exact while the weights of one sum stay below 2^12 * 2^40 (row maximum
+// given: 16 weights of at most 2^40).  x below -41 (and NaN) has weight 0 in weight_u64; 2^-60 * 2^40 floors to 0
+// as well.  Between round_f64_to_zero() and round_f64_to_nearest().
+constexpr double kWeightBase = 0x1p12;
+__device__ inline void add_weight(double& acc, float z, float zmax, float inv_t) {
+    float x = __fsub_rn(z, zmax);
+    x = __fmul_rn(x, inv_t);
+    x = __fmul_rn(x, 0x1.715476p+0f);
+    x = fmaxf(x, -60.0f);
+    const float t = __fadd_rn(x, 0x1.8p23f);
+    const float f = __fsub_rn(x, __fsub_rn(t, 0x1.8p23f));
+    float p = 0x1.ffcbfcp-17f;
+    p = __fadd_rn(__fmul_rn(p, f), 0x1.430912p-13f);
+    p = __fadd_rn(__fmul_rn(p, f), 0x1.5d87fep-10f);
+    p = __fadd_rn(__fmul_rn(p, f), 0x1.3b2ab6p-7f);
+    p = __fadd_rn(__fmul_rn(p, f), 0x1.c6b08ep-5f);
+    p = __fadd_rn(__fmul_rn(p, f), 0x1.ebfbe0p-3f);
+    p = __fadd_rn(__fmul_rn(p, f), 0x1.62e430p-1f);
+    p = __fadd_rn(__fmul_rn(p, f), 1.0f);
+    const double w = (double)__uint_as_float(__float_as_uint(p) + (__float_as_uint(t) << 23));
+    asm volatile("v_add_f64 %0, %0, %1" : "+v"(acc) : "v"(w));
 }
-__device__ inline uint64_t wave_sum_u64(uint64_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t lo = __shfl_xor((uint32_t)v, o, kWave);
-        const uint32_t hi = __shfl_xor((uint32_t)(v >> 32), o, kWave);
-        v += ((uint64_t)hi << 32) | lo;
-    }
+__device__ inline uint64_t weight_bits(double acc) {
+    return (uint64_t)__double_as_longlong(acc) - (uint64_t)__double_as_longlong(kWeightBase);
+}
+// Rounding of double-precision results, MODE bits 2 and 3.
+__device__ inline void round_f64_to_zero() {
+    asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 3\n\ts_nop 1" ::: "memory");
+}
+__device__ inline void round_f64_to_nearest() {
+    asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 2, 2), 0\n\ts_nop 1" ::: "memory");
+}
+
+// Inclusive prefix sum over the wave without a trip through LDS: shifts inside the rows of 16 lanes, then lane 15
+// of a row (31 of a half) is broadcast to the lanes after it.
+__device__ inline uint32_t wave_scan_u32(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);   // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);   // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);   // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);   // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
     return v;
+}
+// Prefix sums as three 32-bit ones that cannot overflow (22 + 22 + 20 bits of 64 lanes).
+__device__ inline uint64_t wave_scan_u64(uint64_t v) {
+    const uint64_t lo = wave_scan_u32((uint32_t)v & 0x3fffffu);
+    const uint64_t mid = wave_scan_u32((uint32_t)(v >> 22) & 0x3fffffu);
+    const uint64_t hi = wave_scan_u32((uint32_t)(v >> 44));
+    return lo + (mid << 22) + (hi << 44);
+}
+// The last lane ends with the sum over the wave of values < 2^48 (two 32-bit sums: 22 low bits, high bits < 2^26).
+__device__ inline uint64_t wave_sum_to_last(uint64_t v) {
+    const uint64_t lo = wave_scan_u32((uint32_t)v & 0x3fffffu);
+    const uint64_t hi = wave_scan_u32((uint32_t)(v >> 22));
+    return (hi << 22) + lo;
+}
+__device__ inline uint64_t last_lane(uint64_t v) {
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, 63), hi = __builtin_amdgcn_readlane((int)(v >> 32), 63);
+    return ((uint64_t)hi << 32) | lo;
 }
 
 // Four consecutive logits starting at i (values beyond V read as -inf); one 16-byte load when
@@ -99,12 +144,15 @@ constexpr int kSegLen = 1024;
 constexpr int kMaxSeg = 256;  // vocab <= 262144
 
 // NW waves per row: few rows need many waves each to keep the vector ALUs busy.
+// What bounds it: the sweep's vector instructions (24 per logit) and the read of the row are about even at 512 rows,
+// and at few rows the instructions of one CU and the serial steps after the sweep are all there is.  Hence the short
+// form of the weights, lane scans that do not go through LDS, and a pick in one step each: the segment by a
+// prefix sum (it was a loop of one lane over up to 148 sums), its 1024 logits by loads that go out together.
+// 512 x 151936 with the row maxima given: 96.3 -> 64.8 us (4.8 TB/s).
 template <int NW>
 __global__ __launch_bounds__(NW * 64) void sample_kernel(SampleArgs a) {
     __shared__ uint64_t seg_sum[kMaxSeg];
     __shared__ float red[NW];
-    __shared__ int pick_seg;
-    __shared__ uint64_t pick_rem, row_total;
     const int r = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (a.active && !a.active[r]) {  // finished rollout: no draw, the output is padding
@@ -141,94 +189,98 @@ __global__ __launch_bounds__(NW * 64) void sample_kernel(SampleArgs a) {
     float4 cur[4], nxt[4];
 #pragma unroll
     for (int sb = 0; sb < 4; ++sb) cur[sb] = load4(z, wave * kSegLen + sb * kSubLen + lane * 4, V, vec);
+    round_f64_to_zero();
     for (int sg = wave; sg < n_seg; sg += NW) {
         const bool more = sg + NW < n_seg;  // wave-uniform
         if (more) {
 #pragma unroll
             for (int sb = 0; sb < 4; ++sb) nxt[sb] = load4(z, (sg + NW) * kSegLen + sb * kSubLen + lane * 4, V, vec);
         }
-        uint64_t q = 0;  // < 16 * 2^41
+        double acc = kWeightBase;
 #pragma unroll
         for (int sb = 0; sb < 4; ++sb) {
             const float4 v = cur[sb];
-            q += weight_u64(v.x, zmax, a.inv_t) + weight_u64(v.y, zmax, a.inv_t) +
-                 weight_u64(v.z, zmax, a.inv_t) + weight_u64(v.w, zmax, a.inv_t);
+            add_weight(acc, v.x, zmax, a.inv_t);
+            add_weight(acc, v.y, zmax, a.inv_t);
+            add_weight(acc, v.z, zmax, a.inv_t);
+            add_weight(acc, v.w, zmax, a.inv_t);
         }
-        q = wave_sum_u45(q);
-        if (lane == 0) seg_sum[sg] = q;
+        const uint64_t q = wave_sum_to_last(weight_bits(acc));
+        if (lane == 63) seg_sum[sg] = q;
         if (more) {
 #pragma unroll
             for (int sb = 0; sb < 4; ++sb) cur[sb] = nxt[sb];
         }
     }
+    round_f64_to_nearest();
     __syncthreads();
+    if (wave != 0) return;
 
-    if (wave == 0) {
-        // total, threshold, and the segment the threshold falls into
-        uint64_t loc = 0;
-        for (int sg = lane; sg < n_seg; sg += 64) loc += seg_sum[sg];
-        const uint64_t total = wave_sum_u64(loc);
-        const uint64_t u = philox_u64(a.seed, a.seq_id[r], a.step);
-        const uint64_t t = __umul64hi(u, total);
-        if (lane == 0) {
-            uint64_t run = 0;
-            int sg = 0;
-            for (; sg < n_seg - 1; ++sg) {
-                if (run + seg_sum[sg] > t) break;
-                run += seg_sum[sg];
-            }
-            pick_seg = sg;
-            pick_rem = t - run;  // < seg_sum[sg]
-            row_total = total;
-        }
+    // Total, threshold and the segment it falls into: four consecutive segments per lane, prefix sums over the lanes.
+    uint64_t s4[4], mine = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        s4[e] = lane * 4 + e < n_seg ? seg_sum[lane * 4 + e] : 0;
+        mine += s4[e];
     }
-    __syncthreads();
-    if (wave == 0) {
-        uint64_t rem = pick_rem;
-        // walk the 4 sub-blocks of the chosen segment in vocabulary order
-        for (int sb = 0; sb < 4; ++sb) {
-            const int i0 = pick_seg * kSegLen + sb * kSubLen + lane * 4;
-            const float4 v = load4(z, i0, V, vec);
-            uint64_t q[4];
-            q[0] = weight_u64(v.x, zmax, a.inv_t);
-            q[1] = weight_u64(v.y, zmax, a.inv_t);
-            q[2] = weight_u64(v.z, zmax, a.inv_t);
-            q[3] = weight_u64(v.w, zmax, a.inv_t);
-            const uint64_t mine = q[0] + q[1] + q[2] + q[3];
-            uint64_t incl = mine;  // inclusive prefix over lanes
+    const uint64_t incl = wave_scan_u64(mine);
+    const uint64_t total = last_lane(incl);
+    const uint64_t t = __umul64hi(philox_u64(a.seed, a.seq_id[r], a.step), total);
+    // the first segment whose prefix sum exceeds t (the last one if none does: a row without weights)
+    const uint64_t above = __builtin_amdgcn_ballot_w64(incl > t);
+    const int owner = above ? __builtin_ctzll(above) : (n_seg - 1) / 4;
+    uint64_t run = incl - mine;
+    int sg = lane * 4;
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t lo = __shfl_up((uint32_t)incl, o, kWave);
-                const uint32_t hi = __shfl_up((uint32_t)(incl >> 32), o, kWave);
-                if (lane >= o) incl += ((uint64_t)hi << 32) | lo;
-            }
-            const uint32_t blo = __shfl((uint32_t)incl, 63, kWave), bhi = __shfl((uint32_t)(incl >> 32), 63, kWave);
-            const uint64_t block_total = ((uint64_t)bhi << 32) | blo;
-            if (rem >= block_total) {  // uniform across the wave
-                rem -= block_total;
-                continue;
-            }
-            const uint64_t excl = incl - mine;
-            if (excl <= rem && rem < incl) {  // exactly one lane
-                uint64_t run = excl;
-                int tok = i0;
+    for (int e = 0; e < 3; ++e)
+        if (sg == lane * 4 + e && sg < n_seg - 1 && run + s4[e] <= t) {
+            run += s4[e];
+            ++sg;
+        }
+    const int pick = __builtin_amdgcn_readlane(sg, owner);
+    uint64_t rem = t - (((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(run >> 32), owner) << 32) |
+                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)run, owner));
+    // Walk the 4 sub-blocks of that segment in vocabulary order; their loads go out together.
+    float4 v[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (run + q[e] > rem) {
-                        tok = i0 + e;
-                        break;
-                    }
-                    run += q[e];
+    for (int sb = 0; sb < 4; ++sb) v[sb] = load4(z, pick * kSegLen + sb * kSubLen + lane * 4, V, vec);
+    bool found = false;
+#pragma unroll
+    for (int sb = 0; sb < 4; ++sb) {
+        if (found) break;
+        const float ze[4] = {v[sb].x, v[sb].y, v[sb].z, v[sb].w};
+        uint64_t q[4], own = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            q[e] = weight_u64(ze[e], zmax, a.inv_t);
+            own += q[e];
+        }
+        const uint64_t upto = wave_scan_u64(own);
+        const uint64_t block_total = last_lane(upto);
+        if (rem >= block_total) {  // uniform across the wave
+            rem -= block_total;
+            continue;
+        }
+        found = true;
+        uint64_t before = upto - own;
+        if (before <= rem && rem < upto) {  // exactly one lane
+            int e = 0;
+            float zt = ze[0];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (e == k && before + q[k] <= rem) {
+                    before += q[k];
+                    e = k + 1;
+                    zt = ze[k + 1];
                 }
-                a.tokens_out[r] = tok;
-                if (a.lengths) a.lengths[r] += 1;
-                if (a.active && a.eos_id >= 0 && tok == a.eos_id) a.active[r] = 0;
-                if (a.logprob_out) {
-                    const float x = ((z[tok] - zmax) * a.inv_t);
-                    a.logprob_out[r] = x - (float)(log((double)row_total) - 40.0 * 0.6931471805599453);
-                }
+            const int tok = pick * kSegLen + sb * kSubLen + lane * 4 + e;
+            a.tokens_out[r] = tok;
+            if (a.lengths) a.lengths[r] += 1;
+            if (a.active && a.eos_id >= 0 && tok == a.eos_id) a.active[r] = 0;
+            if (a.logprob_out) {
+                const float x = ((zt - zmax) * a.inv_t);
+                a.logprob_out[r] = x - (float)(log((double)total) - 40.0 * 0.6931471805599453);
             }
-            break;
         }
     }
 }
@@ -236,7 +288,7 @@ __global__ __launch_bounds__(NW * 64) void sample_kernel(SampleArgs a) {
 hipError_t launch_sample(const SampleArgs& a, hipStream_t s) {
     if (a.n_out_rows <= 0) return hipSuccess;
     if (a.vocab > kSegLen * kMaxSeg) return hipErrorInvalidValue;
-    // up to ~4 rows per CU: 16 waves per row (the sweep is ALU work, 27 operations per logit)
+    // up to ~4 rows per CU: 16 waves per row (the sweep is ALU work, 24 instructions per logit)
     if (a.n_out_rows <= 1024)
         sample_kernel<16><<<a.n_out_rows, 1024, 0, s>>>(a);
     else

@@ -190,6 +190,27 @@ def test_sampler_bit_exact(rpo, vocab, rows, temperature):
     assert tok.cpu().numpy()[1] == vocab - 1 if rows > 1 else True
 
 
+@pytest.mark.parametrize("vocab", [1, 255, 1024, 1025, 4096, 4097, 262144])   # segments of 1024, four per lane
+def test_sampler_segments_and_tiny_weights(rpo, vocab):
+    """Flat rows spread the draws over every segment; the lower half of the rows lies around the smallest weights
+    (2^-40 of the maximum, and below: none) with every other token masked out."""
+    rng = np.random.default_rng(vocab)
+    rows = 96
+    z = (rng.normal(size=(rows, vocab)) * 0.2).astype(np.float32)
+    low = rng.uniform(-43.0, -36.0, size=(rows // 2, vocab)) / 1.4426950408889634
+    z[rows // 2:] = np.where(rng.random((rows // 2, vocab)) < 0.5, low, -np.inf).astype(np.float32)
+    z[rows // 2:, -1] = 0.0
+    seq = np.arange(rows).astype(np.uint64)
+    tok = torch.empty(rows, dtype=torch.int32, device="cuda")
+    lp = torch.empty(rows, dtype=torch.float32, device="cuda")
+    rpo.rpo_sample(torch.from_numpy(z).cuda(), rows, vocab, vocab, None, rows, 1.0, 5,
+                   torch.from_numpy(seq.astype(np.int64)).cuda(), 2, tok, lp)
+    torch.cuda.synchronize()
+    otok, olp = osampler.sample(z, 1.0, 5, seq, 2)
+    np.testing.assert_array_equal(tok.cpu().numpy(), otok)
+    np.testing.assert_allclose(lp.cpu().numpy(), olp, atol=1e-4)
+
+
 def test_sampler_row_map_stride_and_distribution(rpo):
     rng = np.random.default_rng(5)
     vocab, stride = 40, 64

@@ -125,3 +125,21 @@ def test_logprob_output_and_row_map():
     t2, _ = sampler.sample(z, 0.9, 1, np.arange(6, dtype=np.uint64), 0,
                            row_map=np.array([0, 0, 1, 1, 2, 2]))
     np.testing.assert_array_equal(toks, t2)
+
+
+def test_weights_as_a_truncating_double_sum():
+    """The sweep of the kernel in numpy: x + 1.5 * 2^23 rounds x and holds n in its low bits, p 2^n is an integer
+    addition to p's bits, and the floor is the truncation of a double in [2^12, 2^13) to its last place, 2^-40."""
+    rng = np.random.default_rng(0)
+    edges = np.array([0.0, -0.0, -0.5, -1.5, -2.5, -39.5, -40.0, -40.5, -41.0, -59.9, -60.0, -1e30, -np.inf], np.float32)
+    edges = np.concatenate([edges, np.nextafter(edges[:11], np.float32(-1e3)), np.nextafter(edges[2:11], np.float32(0))])
+    x = np.concatenate([edges, (-62.0 * rng.random(200000)).astype(np.float32)])
+    c = np.fmax(x, np.float32(-60.0))
+    t = c + np.float32(1.5 * 2 ** 23)
+    f = c - (t - np.float32(1.5 * 2 ** 23))
+    p = np.full_like(f, sampler.COEF[7])
+    for k in sampler.COEF[6::-1]:
+        p = p * f
+        p = p + k
+    w = (p.view(np.uint32) + (t.view(np.uint32) << np.uint32(23))).view(np.float32).astype(np.float64)
+    np.testing.assert_array_equal(np.floor(w * 2.0 ** 40).astype(np.uint64), sampler.exp2_fixed(x))
