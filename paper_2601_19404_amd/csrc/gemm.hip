@@ -1256,10 +1256,10 @@ bool dma2_ok(const GemmArgs& a, int splits, int stages = 2) {
 }
 
 // A handful of rows: the weight-streaming kernel of skinny.hip (figures there; at 64 rows it is ahead of the
-// 64-row tiles on every projection, by 1.1x (down) to 1.6x (QKV)).
+// 64-row tiles on every projection, by 1.1x (down) to 1.6x (QKV)), or narrow projections of more rows.
 constexpr int kSkinnyRows = 64;
 bool skinny_ok(const GemmArgs& a) {
-    return a.path == 0 && a.M <= kSkinnyRows && a.K % kBK == 0 && !a.lse && mfma_ok(a) &&
+    return a.path == 0 && (a.M <= kSkinnyRows || gemm_skinny_groups(a) > 0) && a.K % kBK == 0 && !a.lse && mfma_ok(a) &&
            (uint64_t)a.N * (uint64_t)a.ldw * sizeof(bf16) < (1ull << 32) &&  // 32-bit load offsets
            (uint64_t)a.M * (uint64_t)a.lda * sizeof(bf16) < (1ull << 32);
 }

@@ -74,12 +74,14 @@ struct GemmArgs {
     LseFuse* block_max = nullptr;
 };
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
-// The weight-streaming kernel for up to 64 rows (bf16, K a multiple of 64, 16-byte aligned rows: checked by
+// The weight-streaming kernel for few rows (bf16, K a multiple of 64, 16-byte aligned rows: checked by
 // launch_gemm).  epi: kEpiStore / kEpiStoreF32 / kEpiAddF32 / kEpiSwiglu, kEpiRope (a.rope, head_dim 128) or
 // kEpiLogitsMax (a.block_max: row maxima per 64 columns).
 // splits > 1: fp32 partial sums of that many K ranges to a.ws[splits][M][N] instead.
 hipError_t launch_gemm_skinny(const GemmArgs& a, int epi, int splits, hipStream_t s);
 int gemm_skinny_splits(const GemmArgs& a);
+// More than 64 rows: whether that kernel takes the problem in groups of 64 rows (> 0) or not at all (0).
+int gemm_skinny_groups(const GemmArgs& a);
 // Whether launch_gemm would honour GemmArgs::lse for these arguments, and with how many column
 // blocks per row (0 = it would write C as usual).
 int gemm_fuses_lse(const GemmArgs& a);

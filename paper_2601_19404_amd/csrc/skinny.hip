@@ -1,5 +1,5 @@
 // C[M,N] (op)= A[M,K] * W[N,K]^T for a handful of rows (bf16 operands, fp32 accumulation): the
-// contractions of a decode step of a small batch.
+// contractions of a decode step of a small batch, and the narrow ones of a larger batch in groups of 64 rows.
 //
 // What bounds them is how fast a CU can be fed: 64 rows use a weight 64 times, far from what the matrix
 // cores need to be the limit, and every weight byte comes from HBM once per decode step (the layers
@@ -22,6 +22,21 @@
 #include "kernels.hpp"
 
 namespace rpo {
+
+// 65 rows and more (QKV and O of a decode step): the 16-row weight blocks per workgroup (0: not for this kernel).
+// (measured up to 512 rows).  Every group of 64 rows reads the weights again, from L2, and a workgroup that waits for a second round costs more
+// than all that is gained, so the groups are taken only where they fit the CUs in one round.  Weights from HBM,
+// 64x64 / 32x128 tiles -> this kernel, us: N = 2048, K = 1536: 128 rows 8.6 -> 5.6 (one block), 256 rows 8.8 -> 6.5 (two),
+// 512 rows 9.7 -> 8.2 (four); N = 1536: 8.9 -> 5.9, 9.2 -> 6.6, 9.8 -> 8.5; N = K = 3584: 128 rows 20.1 -> 14.7 (two), 256
+// rows 21.5 -> 19.2 (four).  Past one round: 512 rows of N = 2048 with two blocks 11.1, N = 4608, K = 3584 with four 31.5
+// against 31.4.  A deep K (down) and a wide N (gate/up, LM head) lose: 24.1 -> 26 and 34 -> 36 us at 256 rows.
+int gemm_skinny_groups(const GemmArgs& a) {
+    if (a.K > 4096 || a.M > 512 || (a.epilogue != kEpiStore && a.epilogue != kEpiAddF32)) return 0;
+    const int groups = ceil_div(a.M, 64);
+    for (int nb = 1; nb <= 4; nb *= 2)
+        if ((int64_t)ceil_div(a.N, nb * 16) * groups <= 256) return nb;
+    return 0;
+}
 
 namespace {
 
@@ -57,8 +72,8 @@ template <int MA, int NB, int NW, int S, int EPI>
 __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __restrict__ A, int64_t lda,
                                                               const bf16* __restrict__ W, int64_t ldw,
                                                               void* __restrict__ Cv, int64_t ldc, int M, int N,
-                                                              int K, int slabs_per_split, RopeKvArgs rk,
-                                                              LseFuse lf) {
+                                                              int K, int slabs_per_split, int blocks,
+                                                              int row_groups, RopeKvArgs rk, LseFuse lf) {
     static_assert(EPI != kEpiLogitsMax || NB == 4, "row maxima are kept per 64 columns");
     constexpr int MB = (MA + 1) / 2;  // 16-column MFMA blocks of activations (MA = 1: rows 0 .. 7 twice)
     constexpr int ROWS = MB * 16, COLS = NB * 16;
@@ -71,7 +86,15 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, g = lane >> 4;
-    const int b = blockIdx.x;
+    // Row groups of one column block sit next to each other on one XCD (workgroups go to the eight XCDs in turn):
+    // the weights come from HBM once and from that XCD's L2 for the other groups.
+    int b = blockIdx.x, m0 = 0;
+    if (row_groups > 1) {
+        const int t = b >> 3;
+        m0 = t % row_groups * (MA * 8);
+        b = (t / row_groups) * 8 + (b & 7);
+        if (b >= blocks) return;  // the whole workgroup
+    }
     const int F = N / 2;
 
     // Load addressing: an instruction fills 8 rows; lane l stores piece position l % 8 of row l / 8 and fetches
@@ -93,7 +116,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
                 row = min((b * NB + t) * 16 + half * 8 + l8, N - 1);
             off[j] = (uint32_t)(((int64_t)row * ldw + piece * 8) * 2);
         } else {
-            off[j] = (uint32_t)(((int64_t)min((j - 2 * NB) * 8 + l8, M - 1) * lda + piece * 8) * 2);
+            off[j] = (uint32_t)(((int64_t)min(m0 + (j - 2 * NB) * 8 + l8, M - 1) * lda + piece * 8) * 2);
         }
     }
     const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem + wave * (S * STAGE);
@@ -184,10 +207,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
     if constexpr (EPI == kEpiSwiglu) {
         const bool vec = (ldc & 3) == 0 && ((uintptr_t)Cv & 7) == 0;
         for (int it = tid; it < ROWS * NB * 2; it += NW * 64) {
-            const int m = it / (NB * 2), q = it % (NB * 2);
+            const int m = m0 + it / (NB * 2), q = it % (NB * 2);
             const int c = (q >> 1) * 16 + (q & 1) * 4, oc = (b * NB + (q >> 1)) * 8 + (q & 1) * 4;
             if (m >= M) continue;
-            const f32x4_t gate = total(m, c), up = total(m, 8 + c);
+            const f32x4_t gate = total(m - m0, c), up = total(m - m0, 8 + c);
             u16x4_t o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16(silu_f(gate[e]) * up[e]).bits;
@@ -203,11 +226,11 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
     } else if constexpr (EPI == kEpiRope) {
         const int pt = rk.geom.page_tokens;
         for (int it = tid; it < ROWS * NB * 2; it += NW * 64) {
-            const int m = it / (NB * 2), q = it % (NB * 2);
+            const int m = m0 + it / (NB * 2), q = it % (NB * 2);
             const int unit = b * NB + (q >> 1), head = unit >> 3;
             const int c = (q >> 1) * 16 + (q & 1) * 4, ch = (unit & 7) * 8 + (q & 1) * 4;
             if (m >= M) continue;
-            const f32x4_t x1 = total(m, c), x2 = total(m, 8 + c);
+            const f32x4_t x1 = total(m - m0, c), x2 = total(m - m0, 8 + c);
             int pos = -1;
             int64_t page = 0;
             const int seq = rk.row_seq ? rk.row_seq[m] : m;
@@ -258,9 +281,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
         const bool vec = EPI == kEpiStore ? (ldc & 3) == 0 && ((uintptr_t)Cv & 7) == 0
                                           : (ldc & 3) == 0 && ((uintptr_t)Cv & 15) == 0;
         for (int it = tid; it < ROWS * QPR; it += NW * 64) {
-            const int m = it / QPR, c = (it % QPR) * 4, n = b * COLS + c;
+            const int m = m0 + it / QPR, c = (it % QPR) * 4, n = b * COLS + c;
             if (m >= M) continue;  // all lanes of a row's quads together
-            const f32x4_t v = total(m, c);
+            const f32x4_t v = total(m - m0, c);
             if constexpr (EPI == kEpiStore) {
                 bf16* dst = (bf16*)Cv + (int64_t)m * ldc + n;
                 u16x4_t o;
@@ -316,9 +339,11 @@ hipError_t launch_one(const GemmArgs& a, int blocks, hipStream_t s, int splits =
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    kern<<<dim3((unsigned)blocks, (unsigned)splits), dim3(NW * 64), lds, s>>>(
+    const int row_groups = ceil_div(a.M, MA * 8);
+    const int grid = row_groups == 1 ? blocks : ceil_div(blocks, 8) * 8 * row_groups;
+    kern<<<dim3((unsigned)grid, (unsigned)splits), dim3(NW * 64), lds, s>>>(
         (const bf16*)a.A, a.lda, (const bf16*)a.W, a.ldw, out ? out : a.C, a.ldc, a.M, a.N, a.K,
-        ceil_div(a.K / 64, splits),
+        ceil_div(a.K / 64, splits), blocks, row_groups,
         (EPI == kEpiRope && a.rope) ? *a.rope : RopeKvArgs{},
         (EPI == kEpiLogitsMax && a.block_max) ? *a.block_max : LseFuse{});
     return hipGetLastError();
@@ -351,12 +376,24 @@ hipError_t launch_rows(const GemmArgs& a, int splits, hipStream_t s) {
     }
 }
 
+// More than 64 rows: groups of 64, with the blocks that gemm_skinny_groups found to fit one round.
+template <int EPI>
+hipError_t launch_groups(const GemmArgs& a, hipStream_t s) {
+    switch (gemm_skinny_groups(a)) {
+        case 1: return launch_one<8, 1, 4, 2, EPI>(a, ceil_div(a.N, 16), s);
+        case 2: return launch_one<8, 2, 4, 1, EPI>(a, ceil_div(a.N, 32), s);
+        case 4: return launch_one<8, 4, 4, 1, EPI>(a, ceil_div(a.N, 64), s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 template <int EPI>
 hipError_t launch_epi(const GemmArgs& a, hipStream_t s, int splits = 1) {
     if (a.M <= 8) return launch_rows<1, EPI>(a, splits, s);
     if (a.M <= 16) return launch_rows<2, EPI>(a, splits, s);
     if (a.M <= 32) return launch_rows<4, EPI>(a, splits, s);
     if (a.M <= 64) return launch_rows<8, EPI>(a, splits, s);
+    if constexpr (EPI == kEpiStore || EPI == kEpiAddF32 || EPI == kEpiRope) return launch_groups<EPI>(a, s);
     return hipErrorInvalidValue;
 }
 
@@ -368,7 +405,7 @@ hipError_t launch_epi(const GemmArgs& a, hipStream_t s, int splits = 1) {
 // the residual and the RMSNorm (12.0 / 14.3 us with that reduction).  A shallow K stays unsplit: its workgroups
 // would get less than eight slabs.
 int gemm_skinny_splits(const GemmArgs& a) {
-    if (a.epilogue != kEpiAddF32 || !a.ws || a.K < 4096) return 1;
+    if (a.epilogue != kEpiAddF32 || !a.ws || a.K < 4096 || a.M > 64) return 1;
     const int tiles = ceil_div(a.N, 64), slabs = a.K / 64;
     int splits = 256 / tiles;
     splits = splits < slabs / 8 ? splits : slabs / 8;

@@ -76,6 +76,15 @@ def test_gemm_skinny_row_and_column_edges(rpo, M, N, K):
             _gemm_case(rpo, M, N, K, torch.bfloat16, epi, path=0, seed=7, ws_mb=ws_mb, pad=pad)
 
 
+@pytest.mark.parametrize("M", [65, 128, 129, 250, 512])
+@pytest.mark.parametrize("N,K", [(5, 64), (200, 192), (1540, 1536), (2048, 320), (2052, 3584), (4100, 128)])
+def test_gemm_skinny_row_groups(rpo, M, N, K):
+    """The same kernel in groups of 64 rows: a last group of one row, blocks of 16 / 32 / 64 columns and a column count
+    that ends inside one, column blocks that do not divide among the XCDs; past one round of workgroups the tiles."""
+    for epi, pad in ((0, 0), (2, 8)):
+        _gemm_case(rpo, M, N, K, torch.bfloat16, epi, path=0, seed=11, pad=pad)
+
+
 @pytest.mark.parametrize("path", [17, 19, 20, 21, 22, 27])
 @pytest.mark.parametrize("shape", [(300, 520, 1536), (77, 1536, 4480)])
 def test_gemm_mfma_bf16_every_tile_shape(rpo, shape, path):

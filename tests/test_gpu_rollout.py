@@ -291,6 +291,21 @@ def test_bf16_many_rows_wide_rotary_tile(rpo):
     run_case(rpo, BF16_2KV, p, a, m, G=16)
 
 
+@pytest.mark.parametrize("n_groups", [5, 13])
+def test_bf16_rotary_projection_in_row_groups(rpo, n_groups):
+    """80 and 208 decode rows of a 4096-column QKV projection: groups of 64 rows with two and four 16-row blocks."""
+    mcfg = synth.ModelCfg("row-groups", 2, 512, 24, 4, 128, 512, 512, "bf16")
+    p, a, m = bf16_workload(mcfg, lens=tuple(20 + 7 * i for i in range(n_groups)), ms=(3,) * n_groups, seed=4)
+    run_case(rpo, mcfg, p, a, m, G=16)
+
+
+def test_bf16_deep_down_projection_of_a_wide_model(rpo):
+    """The K-split reduction with the RMSNorm of a row of more than 4096 columns: two column groups per thread."""
+    mcfg = synth.ModelCfg("wide", 2, 4160, 4, 2, 128, 4096, 512, "bf16")
+    p, a, m = bf16_workload(mcfg, lens=(20, 41), ms=(3, 4), seed=6)
+    run_case(rpo, mcfg, p, a, m, G=4)
+
+
 @pytest.mark.parametrize("d_model,lens", [(2056, (70, 33)), (1000, (20, 41)), (132, (20, 41)), (768, (1101, 990))])
 def test_rmsnorm_row_widths_and_row_counts(rpo, d_model, lens):
     """Row norms: widths that leave a remainder in the workgroup-per-row kernel (one past 2048), and a prefill
