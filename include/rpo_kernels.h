@@ -79,7 +79,7 @@ int rpo_probe_peaks(const void *src_dev, void *dst_dev, size_t bytes, float *scr
  *     rollouts through them as a cross-check of the MFMA kernels),
  * 2 = MFMA GEMM with register-staged LDS fills instead of direct-to-LDS loads (the fallback
  *     used when K is not a multiple of 64; selectable so that the tests reach it at any K),
- * 16 + k (k = 1, 3..6, 11) = MFMA GEMM with the fixed tile shape of kernel id k, so that the tests
+ * 16 + k (k = 1, 3..6, 11, 13, 14) = MFMA GEMM with the fixed tile shape of kernel id k, so that the tests
  *     can force every tile shape onto one problem (attention as in 0).
  * Unsynchronised: set it from the thread that issues the compute calls, between calls.
  * Errors: RPO_EINVAL. */
@@ -103,6 +103,7 @@ int rpo_set_kernel_path(int path);
  *   6  <64,64,2,2> (decode-sized problems, shallow K, no K split)
  *      (all epilogues of a tile shape together; a K-split launch includes its reduction)
  *   11 <256,192,4,2> (large M with a narrow N: fewer idle CUs in the last round of workgroups)
+ *   13 <256,160,4,1>, 14 <128,160,4,1> (gate/up projection of a decode step, where one round holds their tiles)
  *   7  gemm_generic_kernel      8  attn_decode_mfma_kernel (+ merge)   9  attn_chunk_mfma_kernel
  *   10 sample_kernel
  * The timing state and rpo_set_kernel_path's switch are process-wide and unsynchronised: use them

@@ -898,6 +898,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma2_kernel(const bf16* __re
     constexpr int A_INST = BM / 8 / NW, B_INST = BN / 8 / NW;  // a wave instruction fills 8 rows (1 KiB)
     constexpr int A_STAGE = BM * BK, B_STAGE = BN * BK;        // elements
     constexpr int N_INST = A_INST + B_INST;
+    constexpr int kReads = (MI + NI + MI * NI - 1) / (MI * NI);  // fragment reads after every MFMA
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile/wave mismatch");
     static_assert(EPI != kEpiRope, "no LDS-staged epilogue here");
     constexpr bool kTrans = EPI != kEpiStore;
@@ -999,8 +1000,11 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma2_kernel(const bf16* __re
                     acc[i][j] = kTrans ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[c][j], af[c][i], acc[i][j], 0, 0, 0)
                                        : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[c][i], bfr[c][j], acc[i][j], 0, 0, 0);
                     __builtin_amdgcn_sched_barrier(0);
-                    if (t < NI) bfr[n][t] = *(const bf16x8_t*)(bs + t * 32 * BK + piece);
-                    else if (t < NI + MI) af[n][t - NI] = *(const bf16x8_t*)(as + (t - NI) * 32 * BK + piece);
+#pragma unroll
+                    for (int q = t * kReads; q < t * kReads + kReads; ++q) {
+                        if (q < NI) bfr[n][q] = *(const bf16x8_t*)(bs + q * 32 * BK + piece);
+                        else if (q < NI + MI) af[n][q - NI] = *(const bf16x8_t*)(as + (q - NI) * 32 * BK + piece);
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 }
         }
@@ -1025,8 +1029,11 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma2_kernel(const bf16* __re
                 acc[i][j] = kTrans ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[c][j], af[c][i], acc[i][j], 0, 0, 0)
                                    : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[c][i], bfr[c][j], acc[i][j], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-                if (t < NI) bfr[n][t] = *(const bf16x8_t*)(bs1 + t * 32 * BK + piece0);
-                else if (t < NI + MI) af[n][t - NI] = *(const bf16x8_t*)(as1 + (t - NI) * 32 * BK + piece0);
+#pragma unroll
+                for (int q = t * kReads; q < t * kReads + kReads; ++q) {
+                    if (q < NI) bfr[n][q] = *(const bf16x8_t*)(bs1 + q * 32 * BK + piece0);
+                    else if (q < NI + MI) af[n][q - NI] = *(const bf16x8_t*)(as1 + (q - NI) * 32 * BK + piece0);
+                }
 #pragma unroll
                 for (int d = 0; d < kPer; ++d)
                     if (t * kPer + d < N_INST) dma_one(cur, dma_sl, stage, t * kPer + d, on);
@@ -1279,6 +1286,10 @@ TileCfg pick_tile(const GemmArgs& a) {
                 if (a.epilogue != kEpiSwiglu || (dma2_ok(a, 1) && (a.N / 2) % 16 == 0))
                     return TileCfg{kKidGemm256x192, 256, 192};
                 return TileCfg{kKidGemm256, 256, 256};
+            case kKidGemm128x160:
+                if (a.epilogue == kEpiSwiglu && dma2_ok(a, 1, 4) && (a.N / 2) % 16 == 0)
+                    return TileCfg{kKidGemm128x160, 128, 160};
+                return TileCfg{kKidGemm256, 256, 256};
             default: return TileCfg{kKidGemm64, 64, 128};
         }
     }
@@ -1290,6 +1301,14 @@ TileCfg pick_tile(const GemmArgs& a) {
     const int t256 = ceil_div(a.M, 256) * ceil_div(a.N, 256);
     // The two narrower tiles interleave gate and up rows as only gemm_dma2_kernel does: what it does not take
     // (a single K slab, for one) stays with the tiles whose register-staged form is right.
+    // The gate/up projection of a decode step, and 128x128 tiles that outnumber the CUs (two of them on some, one on
+    // most): 128x160 tiles with four stages, if one round holds them.  They also halve the padding of up to 128 rows.
+    // Weights from HBM, us, 128x128 or 256x160 tiles -> these: K = 1536, N = 17920, 192 rows 30.1 -> 22.8, 256 rows 33.5 ->
+    // 24.3; K = 3584, N = 37888, 72 rows 74.6 -> 55.2, 128 rows 85.2 -> 59.7 (4.5 TB/s of weights).  Where 128x128 tiles
+    // fit one round they stay: more CUs work on them (128 rows of N = 17920: 22.4 against 24.5).
+    if (a.epilogue == kEpiSwiglu && a.M > 64 && ceil_div(a.M, 128) * ceil_div(a.N, 128) > 256 &&
+        ceil_div(a.M, 128) * ceil_div(a.N, 160) <= 256 && dma2_ok(a, 1, 4) && (a.N / 2) % 16 == 0)
+        return TileCfg{kKidGemm128x160, 128, 160};
     // The gate/up projection of a decode step: one round of fewer 256x256 tiles than CUs; 256x192
     // tiles still fit one round and each is a quarter cheaper.
     if (a.epilogue == kEpiSwiglu && a.M > 128 && t256 >= 128 && t256 <= 256 && dma2_ok(a, 1) &&
@@ -1333,7 +1352,7 @@ bool deep_pipeline(const GemmArgs& a, const TileCfg& t) {
 // too few, and only when the workspace can hold the partials.
 int pick_splits(const GemmArgs& a, const TileCfg& t) {
     if (t.id == kKidGemm32 || t.id == kKidGemm64x64) return 1;
-    if ((t.id == kKidGemm256x192 || t.id == kKidGemm256x160) && a.epilogue == kEpiSwiglu) return 1;
+    if ((t.id == kKidGemm256x192 || t.id == kKidGemm256x160 || t.id == kKidGemm128x160) && a.epilogue == kEpiSwiglu) return 1;
     const int tiles = ceil_div(a.M, t.bm) * ceil_div(a.N, t.bn);
     if (tiles >= 128 || a.K < 1024) return 1;  // half a chip of tiles: splitting costs more than it gains
     // one workgroup per CU with the deep pipeline, two otherwise
@@ -1367,13 +1386,14 @@ hipError_t launch_one(const GemmArgs& a, int splits, void* out, hipStream_t s) {
     const dim3 grid((unsigned)(per_xcd * kXcd)), block(WM * WN * 64);
     // direct-to-LDS loads need whole 64-deep slabs; path 2 keeps the register-staged kernel
     const bool dma = a.K % kBK == 0 && a.path != 2;
-    // The wide two-stage tiles run on gemm_dma2_kernel (what it does not take goes to the register-staged kernel).
-    constexpr bool kWide = DST == 2 && DBK == 64 && BM >= 128 && EPI != kEpiRope;
+    // The wide two-stage tiles and the decode gate/up ones run on gemm_dma2_kernel (what it does not take goes to the
+    // register-staged kernel).
+    constexpr bool kWide = (DST == 2 || SWIGLU == 2) && DBK == 64 && BM >= 128 && EPI != kEpiRope;
     if constexpr (kWide) {
         // The decode gate/up tile leaves room for a third stage in the 160 KiB of LDS: two slabs in flight
         // feed a workgroup that streams its weights from HBM (measured at 512 rows, weights not cached:
         // 35.8 -> 34.3 us at K = 1536, 81.1 -> 78.8 us at K = 3584).
-        constexpr int S = (BM == 256 && BN == 160) ? 3 : 2;
+        constexpr int S = (BM == 256 && BN == 160) ? 3 : DST;
         if (dma2_ok(a, splits, S)) {
             const size_t lds = (size_t)S * (BM + BN) * 64 * sizeof(bf16);
             auto kern = gemm_dma2_kernel<BM, BN, WM, WN, EPI, SWIGLU, S>;
@@ -1573,6 +1593,8 @@ static hipError_t launch_gemm_only(const GemmArgs& a, int splits, const TileCfg&
             return launch_tile<64, 64, 2, 2, 4>(a, splits, s);
         case kKidGemm256x160:
             return launch_one<256, 160, 4, 1, kEpiSwiglu, 2>(a, 1, a.C, s);
+        case kKidGemm128x160:
+            return launch_one<128, 160, 4, 1, kEpiSwiglu, 2, 4>(a, 1, a.C, s);
         case kKidGemm256x192:
             if (a.epilogue == kEpiSwiglu) return launch_one<256, 192, 4, 2, kEpiSwiglu, 2>(a, 1, a.C, s);
             return launch_tile<256, 192, 4, 2>(a, splits, s);

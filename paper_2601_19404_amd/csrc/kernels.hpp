@@ -110,7 +110,8 @@ enum KernelId : int {
     kKidSample = 10,        // sample_kernel
     kKidGemm256Swiglu = 12, // <256,256,2,4> with the fused SwiGLU epilogue (gate/up of prefill / log-prob chunks)
     kKidGemm256x160 = 13,   // <256,160,4,1> fused SwiGLU only (decode gate/up: one round of workgroups on more CUs)
-    kKidCount = 14,
+    kKidGemm128x160 = 14,   // <128,160,4,1> the same with four stages, where 256-row tiles would be half padding or too few
+    kKidCount = 15,
 };
 // Which kernel launch_gemm picks for these arguments.
 int gemm_kernel_id(const GemmArgs& a);

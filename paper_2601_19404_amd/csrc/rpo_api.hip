@@ -51,8 +51,8 @@ extern "C" int rpo_probe_peaks(const void* src_dev, void* dst_dev, size_t bytes,
 }
 
 extern "C" int rpo_set_kernel_path(int path) {
-    if (path != 0 && path != 1 && path != 2 && path != 17 && !(path >= 19 && path <= 22) && path != 27 && path != 29)
-        return fail(RPO_EINVAL, "kernel path must be 0, 1, 2, 17, 19..22, 27 or 29");
+    if (path != 0 && path != 1 && path != 2 && path != 17 && !(path >= 19 && path <= 22) && path != 27 && path != 29 && path != 30)
+        return fail(RPO_EINVAL, "kernel path must be 0, 1, 2, 17, 19..22, 27, 29 or 30");
     g_kernel_path = path;
     return RPO_OK;
 }
