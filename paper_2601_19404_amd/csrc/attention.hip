@@ -451,9 +451,10 @@ __global__ __launch_bounds__(256) void attn_decode_mfma_kernel(AttnArgs a, Decod
 // A few MB at most: what counts is one round of loads.  All loads of a thread are issued before any is used (at
 // most kMaxPieces pieces), and a row's heads go to different workgroups (one workgroup walking a row's 28 heads
 // seven rounds deep took 8.7 us and 12 heads three rounds deep 4.9 us; now 4.8 and 2.9 us).
-constexpr int kMaxPieces = 9;  // decode_splits() caps the prefix pieces at 8, plus the private one
+// kMaxPieces: 9 or 17 (decode_splits() caps the prefix pieces at 16, plus the private one).
 // Query row blockIdx.x belongs to rollout row_seq[blockIdx.x] (compacted batch; < 0: padding) or to
 // the rollout of the same index; the pieces are stored by rollout.
+template <int kMaxPieces>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o,
                                                          const float* __restrict__ part_ml, int n_pieces,
                                                          int Hq, const uint8_t* __restrict__ active,
@@ -521,12 +522,18 @@ hipError_t launch_attn_chunk(const AttnArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Prefix pieces per group: about two workgroups per CU.  A piece walks its pages one after the other (a microsecond
+// and more per page when little else runs), so a few groups
+// are cut finer (up to 16 pieces, not 8): rollout passes of the 7B shape, 2 x 8: 385.3 -> 383.0 ms.
+constexpr int kMaxSplit = 16;
 static int decode_splits(int n_groups_live, int Hkv, int n_ct, int max_shared_pages) {
     if (max_shared_pages <= 0) return 1;
     int want = ceil_div(512, n_groups_live * Hkv * n_ct);
-    want = want < 1 ? 1 : (want > 8 ? 8 : want);
+    want = want < 1 ? 1 : (want > kMaxSplit ? kMaxSplit : want);
     const int cap = max_shared_pages / 2 > 0 ? max_shared_pages / 2 : 1;  // at least two pages per piece
-    return want < cap ? want : cap;
+    want = want < cap ? want : cap;
+    // no pieces that the longest prefix leaves empty (16 x 8, 7B shape, 17 - 20 pages: 633.3 -> 628.6 ms)
+    return ceil_div(max_shared_pages, ceil_div(max_shared_pages, want));
 }
 
 size_t attn_decode_partial_floats(int rows, int Hq, int dh, int max_shared_pages) {
@@ -558,8 +565,8 @@ hipError_t launch_attn_decode(const DecodeAttnArgs& d, hipStream_t s) {
     attn_decode_mfma_kernel<<<grid, 256, kAttnLds, s>>>(a, dg, d.shared_pages, part_o, part_ml);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (dg.n_split + 1 > kMaxPieces) return hipErrorInvalidValue;
-    attn_merge_kernel<<<dim3(a.rows, ceil_div(a.Hq * (kDh / 2), 256)), 256, 0, s>>>(part_o, part_ml, dg.n_split + 1, a.Hq, a.active,
+    auto merge = dg.n_split + 1 <= 9 ? attn_merge_kernel<9> : attn_merge_kernel<kMaxSplit + 1>;
+    merge<<<dim3(a.rows, ceil_div(a.Hq * (kDh / 2), 256)), 256, 0, s>>>(part_o, part_ml, dg.n_split + 1, a.Hq, a.active,
                                              d.row_of ? a.row_seq : nullptr, (bf16*)a.out);
     return hipGetLastError();
 }
