@@ -1334,6 +1334,17 @@ TileCfg pick_tile(const GemmArgs& a) {
             const int t192 = ceil_div(a.M, 256) * ceil_div(a.N, 192);
             if (ceil_div(t192, 256) * 0.78 < ceil_div(t256, 256) * 0.97) return TileCfg{kKidGemm256x192, 256, 192};
         }
+        // The same for gate/up: a round of 256x192 tiles costs about 0.86 and one of 256x160 tiles 0.76 of a round of
+        // 256x256 (measured up to four of those; beyond, the last round weighs little).  us, 256x256 -> chosen: N = 17920,
+        // K = 1536: 1000 rows 80.6 -> 65.5 (160), 1280 rows 86 -> 76 (192), 1400 rows 87 stays (95 and 103), 2048 rows 127
+        // -> 115 (192); N = 37888, K = 3584: 300 rows 169 -> 128, 512 rows 180 -> 139 (160), 600 rows 185 stays (196 and 221).
+        const int r256 = ceil_div(t256, 256);
+        if (a.epilogue == kEpiSwiglu && a.M > 256 && r256 <= 4 && dma2_ok(a, 1, 3) && (a.N / 2) % 16 == 0) {
+            const double c192 = ceil_div(ceil_div(a.M, 256) * ceil_div(a.N, 192), 256) * 0.86;
+            const double c160 = ceil_div(ceil_div(a.M, 256) * ceil_div(a.N, 160), 256) * 0.76;
+            if (c160 < r256 * 0.97 && c160 <= c192) return TileCfg{kKidGemm256x160, 256, 160};
+            if (c192 < r256 * 0.97) return TileCfg{kKidGemm256x192, 256, 192};
+        }
         return TileCfg{kKidGemm256, 256, 256};
     }
     if (a.K <= 4096 && a.K % kBK == 0 && a.epilogue != kEpiSwiglu && a.path != 2) {

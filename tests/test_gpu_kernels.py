@@ -98,11 +98,12 @@ def test_gemm_mfma_bf16_every_tile_shape(rpo, shape, path):
 @pytest.mark.parametrize("M,F,K", [(512, 8960, 1536), (40, 1024, 768), (700, 256, 2048), (130, 96, 1024),
                                    (1, 32, 64), (512, 8960, 64), (8, 8960, 192), (17, 416, 128), (64, 18944, 576), (33, 2592, 448),
                                    (300, 18944, 3584), (264, 8032, 512), (100, 18944, 512), (200, 18944, 512),
-                                   (192, 8960, 320), (129, 8992, 256), (72, 18944, 256), (128, 18944, 192)])
+                                   (192, 8960, 320), (129, 8992, 256), (72, 18944, 256), (128, 18944, 192),
+                                   (1000, 8960, 192), (1100, 8960, 192)])
 def test_gemm_swiglu(rpo, M, F, K, path, ws_mb):
     """Fused gate/up projection: C = silu(A Wg^T) * (A Wu^T), W = [gate rows; up rows].  Path 27 forces
     the 256x192 tile and path 30 the 128x160 one (gate / up rows interleaved in blocks of 16), which path 0 picks for
-    decode batches (192 x 8960, 129 x 8992, 72 x 18944 and 128 x 18944: the latter)."""
+    decode batches (192 x 8960, 129 x 8992, 72 x 18944 and 128 x 18944: the latter; two rounds: 1000 x 8960 256x160, 1100 x 8960 256x192)."""
     g = torch.Generator().manual_seed(M + F)
     a = torch.randn(M, K, generator=g).to(torch.bfloat16)
     w = (torch.randn(2 * F, K, generator=g) * 0.05).to(torch.bfloat16)
