@@ -23,13 +23,13 @@
 
 namespace rpo {
 
-// 65 rows and more (QKV and O of a decode step): the 16-row weight blocks per workgroup (0: not for this kernel).
-// (measured up to 512 rows).  Every group of 64 rows reads the weights again, from L2, and a workgroup that waits for a second round costs more
+// 65 to 512 rows (QKV and O of a decode step): the 16-row weight blocks per workgroup, 0: not for this kernel.
+// Every group of 64 rows reads the weights again, from L2, and a workgroup that waits for a second round costs more
 // than all that is gained, so the groups are taken only where they fit the CUs in one round.  Weights from HBM,
-// 64x64 / 32x128 tiles -> this kernel, us: N = 2048, K = 1536: 128 rows 8.6 -> 5.6 (one block), 256 rows 8.8 -> 6.5 (two),
-// 512 rows 9.7 -> 8.2 (four); N = 1536: 8.9 -> 5.9, 9.2 -> 6.6, 9.8 -> 8.5; N = K = 3584: 128 rows 20.1 -> 14.7 (two), 256
-// rows 21.5 -> 19.2 (four).  Past one round: 512 rows of N = 2048 with two blocks 11.1, N = 4608, K = 3584 with four 31.5
-// against 31.4.  A deep K (down) and a wide N (gate/up, LM head) lose: 24.1 -> 26 and 34 -> 36 us at 256 rows.
+// 64x64 tiles -> this kernel, us: N = 2048, K = 1536: 128 rows 8.6 -> 5.6 (one block), 256 rows 8.8 -> 6.5 (two),
+// 512 rows 9.7 -> 8.2 (four); N = 1536: 8.9 -> 5.9, 9.2 -> 6.6, 9.8 -> 8.5; N = K = 3584: 128 rows 20.1 -> 14.7 (two),
+// 256 rows 21.5 -> 19.2 (four).  Past one round: 512 rows of N = 2048 with two blocks 11.1; N = 4608, K = 3584, 256 rows
+// with four 31.5 against 31.4.  A deep K (down) and a wide N (gate/up) lose: 22.9 -> 25.3, 34.1 -> 35.9 us at 256 rows.
 int gemm_skinny_groups(const GemmArgs& a) {
     if (a.K > 4096 || a.M > 512 || (a.epilogue != kEpiStore && a.epilogue != kEpiAddF32)) return 0;
     const int groups = ceil_div(a.M, 64);
