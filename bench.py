@@ -32,6 +32,7 @@ DOMINANT_TRAFFIC = dict(launch="gate/up projection of a full chunk, M=32768 N=17
                         read_bytes=2680.2e6, write_bytes=587.6e6, algorithmic_bytes=155.7e6 + 587.2e6,
                         source="profiles/gemm_hbm_traffic_pmc.txt (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE)")
 KERNEL_BOUND = {"gemm256": "mfma", "gemm256_swiglu": "mfma", "gemm256x192": "mfma", "gemm256x160": "mfma",
+                "gemm128x160": "mfma", "gemm_skinny": "hbm",
                 "gemm128": "mfma", "gemm64": "mfma", "gemm32": "mfma", "gemm64x64": "mfma",
                 "gemm_generic": "alu", "attn_chunk": "mfma", "attn_decode": "hbm", "sample": "hbm"}
 

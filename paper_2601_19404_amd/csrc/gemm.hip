@@ -1589,7 +1589,7 @@ size_t gemm_splitk_scratch_bytes(const GemmArgs& a) {
 
 int gemm_kernel_id(const GemmArgs& a) {
     if (!mfma_ok(a)) return kKidGemmGeneric;
-    if (skinny_ok(a)) return kKidNone;
+    if (skinny_ok(a)) return kKidGemmSkinny;
     const int id = pick_tile(a).id;
     // the heaviest instantiation of a rollout step is reported on its own
     return (id == kKidGemm256 && a.epilogue == kEpiSwiglu) ? (int)kKidGemm256Swiglu : id;

@@ -100,8 +100,8 @@ enum KernelId : int {
     // tile shapes of gemm_dma_kernel / gemm_mfma_kernel <BM, BN, waves along M, waves along N>
     kKidGemm256 = 1,        // <256,256,2,4> (many-tile problems)
     kKidGemm128 = 3,        // <128,128,2,2> (decode-sized problems with a deep K, K split)
-    kKidGemm64 = 4,         // <64,128,1,2>  (the same for M <= 64)
-    kKidGemm32 = 5,         // <32,128,1,4>  (decode QKV projection: one head per tile, no K split)
+    kKidGemm64 = 4,         // <64,128,1,2>  (the same for M <= 64, where the few-row kernel does not take them)
+    kKidGemm32 = 5,         // <32,128,1,4>  (decode QKV projection of more rows than the few-row kernel takes: one head per tile, no K split)
     kKidGemm64x64 = 6,      // <64,64,2,2>   (decode-sized problems with a shallow K, no K split)
     kKidGemmGeneric = 7,
     kKidGemm256x192 = 11,   // <256,192,4,2> (large M, narrow N: fewer idle CUs in the last round)
@@ -111,7 +111,8 @@ enum KernelId : int {
     kKidGemm256Swiglu = 12, // <256,256,2,4> with the fused SwiGLU epilogue (gate/up of prefill / log-prob chunks)
     kKidGemm256x160 = 13,   // <256,160,4,1> fused SwiGLU only (decode gate/up: one round of workgroups on more CUs)
     kKidGemm128x160 = 14,   // <128,160,4,1> the same with four stages, where 256-row tiles would be half padding or too few
-    kKidCount = 15,
+    kKidGemmSkinny = 15,    // gemm_skinny_kernel (few rows, every epilogue; a K split includes its reduction)
+    kKidCount = 16,
 };
 // Which kernel launch_gemm picks for these arguments.
 int gemm_kernel_id(const GemmArgs& a);

@@ -364,6 +364,23 @@ def test_profile_sampling_and_peak_probe(rpo):
     assert 200.0 < mfma_tflops < 2500.0               # below the published bf16 MFMA peak
 
 
+def test_profile_sees_the_kernels_of_a_decode_step(rpo):
+    """The few-row kernel (a K split with its reduction: one launch) and the 128x160 gate/up tile have ids of their own."""
+    rpo.rpo_set_kernel_path(0)
+    ws = torch.empty(32 << 20, dtype=torch.uint8, device="cuda")
+    for name, shapes in (("gemm_skinny", ((8, 2048, 1536, 0), (40, 1536, 8960, 2), (200, 1536, 1536, 2))),
+                         ("gemm128x160", ((192, 17920, 320, 3),))):
+        for M, N, K, epi in shapes:
+            a = torch.randn(M, K, device="cuda").to(torch.bfloat16)
+            w = (torch.randn(N, K, device="cuda") * 0.05).to(torch.bfloat16)
+            c = torch.zeros(M, N // 2 if epi == 3 else N, device="cuda",
+                            dtype=torch.bfloat16 if epi in (0, 3) else torch.float32)
+            rpo.rpo_profile_start(rpo.KERNEL_IDS[name], 1)
+            rpo.rpo_gemm_nt(a, w, c, epi, ws)
+            n, _, flops, _ = rpo.rpo_profile_stop(rpo.KERNEL_IDS[name])
+            assert n == 1 and flops == pytest.approx(2.0 * M * N * K), f"{name} M={M} N={N} K={K}"
+
+
 # ---------------------------------------------------------------------------
 def _attn_decode_case(rpo, mcfg, prefix_lens, G, n_fill, suffix_views, check_groups, seed):
     """rpo_attn_decode (the shared-prefix decode attention of one layer, alone) against the plain
