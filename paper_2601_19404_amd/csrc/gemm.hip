@@ -1268,15 +1268,6 @@ bool dma2_ok(const GemmArgs& a, int splits, int stages = 2) {
            (uint64_t)256 * (uint64_t)a.lda * sizeof(bf16) < (1ull << 32);  // a tile's activation rows as well
 }
 
-// A handful of rows: the weight-streaming kernel of skinny.hip (figures there; at 64 rows it is ahead of the
-// 64-row tiles on every projection, by 1.1x (down) to 1.6x (QKV)), or narrow projections of more rows.
-constexpr int kSkinnyRows = 64;
-bool skinny_ok(const GemmArgs& a) {
-    return a.path == 0 && (a.M <= kSkinnyRows || gemm_skinny_groups(a) > 0) && a.K % kBK == 0 && !a.lse && mfma_ok(a) &&
-           (uint64_t)a.N * (uint64_t)a.ldw * sizeof(bf16) < (1ull << 32) &&  // 32-bit load offsets
-           (uint64_t)a.M * (uint64_t)a.lda * sizeof(bf16) < (1ull << 32);
-}
-
 TileCfg pick_tile(const GemmArgs& a) {
     if (a.path >= 16) {  // tuning aid: a fixed tile shape
         switch (a.path - 16) {
@@ -1379,6 +1370,19 @@ int pick_splits(const GemmArgs& a, const TileCfg& t) {
     if (splits > 16) splits = 16;
     while (splits > 1 && (size_t)splits * a.M * a.N * 4 > a.ws_bytes) --splits;
     return splits < 1 ? 1 : splits;
+}
+
+// A handful of rows: the weight-streaming kernel of skinny.hip, or narrow projections of more rows (the rules and
+// their figures are there).
+constexpr int kSkinnyRows = 64;
+bool skinny_ok(const GemmArgs& a) {
+    if (a.path != 0 || a.K % kBK != 0 || a.lse || !mfma_ok(a) ||
+        (uint64_t)a.N * (uint64_t)a.ldw * sizeof(bf16) >= (1ull << 32) ||  // 32-bit load offsets
+        (uint64_t)a.M * (uint64_t)a.lda * sizeof(bf16) >= (1ull << 32))
+        return false;
+    if (a.M > kSkinnyRows) return gemm_skinny_groups(a) > 0;
+    const bool tiles_split_k = a.ws && a.ws_bytes && pick_splits(a, pick_tile(a)) > 1;
+    return gemm_skinny_takes(a, tiles_split_k);
 }
 
 // The fused reduction + rotary kernel keeps one fp32 row in LDS and addresses C with row stride N.

@@ -80,6 +80,8 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 // splits > 1: fp32 partial sums of that many K ranges to a.ws[splits][M][N] instead.
 hipError_t launch_gemm_skinny(const GemmArgs& a, int epi, int splits, hipStream_t s);
 int gemm_skinny_splits(const GemmArgs& a);
+// Up to 64 rows: whether that kernel is the faster one, given whether the tiles would split K.
+bool gemm_skinny_takes(const GemmArgs& a, bool tiles_split_k);
 // More than 64 rows: whether that kernel takes the problem in groups of 64 rows (> 0) or not at all (0).
 int gemm_skinny_groups(const GemmArgs& a);
 // Whether launch_gemm would honour GemmArgs::lse for these arguments, and with how many column

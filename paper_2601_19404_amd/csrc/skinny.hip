@@ -351,12 +351,23 @@ hipError_t launch_one(const GemmArgs& a, int blocks, hipStream_t s, int splits =
 
 template <int MA, int EPI>
 hipError_t launch_rows(const GemmArgs& a, int splits, hipStream_t s) {
+    // A workgroup reads all activations whatever its weight blocks are, and one that waits for a second round costs
+    // a whole round: the fewest weight blocks per workgroup that put all of them on the CUs in one round.  Beyond
+    // what six (gate/up) or three blocks hold: two smaller workgroups per CU, so that one's loads cover the other's
+    // reduction.  us, five blocks always (gate/up) or one (store) -> this, weights from HBM: gate/up, F = 2048, K =
+    // 3584, 8 / 64 rows 15.7 / 23.1 -> 7.9 / 13.3; F = 11008, K = 3584 39.9 / 51.2 -> 29.6 / 33.8; store, N = 12288, K =
+    // 3584 17.0 / 33.3 -> 17.7 / 21.8; N = 8192, K = 1536 6.7 / 11.0 -> 6.8 / 9.1.
     if constexpr (EPI == kEpiSwiglu) {
-        // 40 outputs per workgroup put F = 8960 on 224 CUs in one round.  More blocks than CUs: two smaller
-        // workgroups per CU, so that one's loads cover the other's reduction.
-        const int blocks = ceil_div(a.N / 2, 8 * 5);
-        if (blocks <= 256) return launch_one<MA, 5, 4, 1, EPI>(a, blocks, s);
-        return launch_one<MA, 5, 2, 2, EPI>(a, blocks, s);
+        const int units = ceil_div(a.N / 2, 8);
+        if (units <= 256) return launch_one<MA, 1, 8, 1, EPI>(a, units, s);
+        if (units <= 256 * 2) return launch_one<MA, 2, 4, 1, EPI>(a, ceil_div(units, 2), s);
+        if (units <= 256 * 3) return launch_one<MA, 3, 4, 1, EPI>(a, ceil_div(units, 3), s);
+        if (units <= 256 * 4) return launch_one<MA, 4, 4, 1, EPI>(a, ceil_div(units, 4), s);
+        if (units <= 256 * 5) return launch_one<MA, 5, 4, 1, EPI>(a, ceil_div(units, 5), s);
+        if (units <= 256 * 6) return launch_one<MA, 6, 4, 1, EPI>(a, ceil_div(units, 6), s);
+        if (units <= 512 * 4) return launch_one<MA, 4, 2, 2, EPI>(a, ceil_div(units, 4), s);
+        if (units <= 512 * 5) return launch_one<MA, 5, 2, 2, EPI>(a, ceil_div(units, 5), s);
+        return launch_one<MA, 6, 2, 2, EPI>(a, ceil_div(units, 6), s);
     } else if constexpr (EPI == kEpiRope) {
         // from 16 rows on the activations weigh as much as a block's weights: two blocks share them where that
         // still leaves half the CUs a workgroup
@@ -367,12 +378,16 @@ hipError_t launch_rows(const GemmArgs& a, int splits, hipStream_t s) {
     } else if constexpr (EPI == kEpiLogitsMax) {
         return launch_one<MA, 4, 2, 2, EPI>(a, ceil_div(a.N, 64), s);
     } else {
-        if constexpr (EPI == kEpiStoreF32) {
-            if (a.N >= 16384) return launch_one<MA, 4, 2, 2, EPI>(a, ceil_div(a.N, 64), s);
+        const int units = ceil_div(a.N, 16);
+        if (units <= 256) return launch_one<MA, 1, 8, 1, EPI>(a, units, s);
+        if constexpr (MA <= 4) {  // 64 rows leave no LDS for a second workgroup of two blocks
+            if (units <= 256 * 2 || (units > 256 * 4 && units <= 512 * 3))
+                return launch_one<MA, 2, 4, 2, EPI>(a, ceil_div(units, 2), s);
+        } else {
+            if (units <= 256 * 2) return launch_one<MA, 2, 4, 1, EPI>(a, ceil_div(units, 2), s);
         }
-        const int blocks = ceil_div(a.N, 16);
-        if (blocks <= 256) return launch_one<MA, 1, 8, 1, EPI>(a, blocks, s);
-        return launch_one<MA, 1, MA <= 2 ? 8 : 4, 2, EPI>(a, blocks, s);
+        if (units <= 256 * 3) return launch_one<MA, 3, 4, 1, EPI>(a, ceil_div(units, 3), s);
+        return launch_one<MA, 4, 2, 2, EPI>(a, ceil_div(units, 4), s);
     }
 }
 
@@ -413,6 +428,32 @@ int gemm_skinny_splits(const GemmArgs& a) {
     while (splits > 1 && (size_t)splits * a.M * a.N * sizeof(float) > a.ws_bytes) --splits;
     if (splits < 2) return 1;
     return ceil_div(slabs, ceil_div(slabs, splits));  // every split has slabs of its own
+}
+
+// Where the tiles of gemm.hip are the faster ones, up to 64 rows.  All figures us with the weights from HBM, tiles
+// against this kernel.
+bool gemm_skinny_takes(const GemmArgs& a, bool tiles_split_k) {
+    if (a.block_max) return true;  // the tile that knows the row maxima is 256 rows tall (64 x 151936 x 3584: 294, 244)
+    const bool few = a.M <= 16, some = a.M <= 32;
+    // A K split that goes through memory: from 33 rows on the tiles feed a deep K better (N = 3584, K = 18944, 32 / 64
+    // rows: 30.6, 29.8 / 31.7, 34.6; N = 4096, K = 12288, 64 rows: 27.2, 26.5; N = 8192, K = 28672, 32 rows: 86, 91;
+    // N = K = 6144, 64 rows: 22.6, 24.2).
+    if (gemm_skinny_splits(a) > 1) return few || a.K <= (some ? 20480 : a.N <= 4096 ? 12288 : 4096);
+    // Tiles that split K over the CUs against workgroups that walk all of it (store, N = 1536: 64 rows, K = 4096 13.2,
+    // 12.6, K = 8192 17.3, 21.4; 24 rows, K = 8192 14.8, 14.1, K = 16384 18.1, 24.9; 8 rows, K = 16384 18.0, 17.2).
+    if (tiles_split_k && a.K > (few ? 16384 : some ? 6144 : 4096)) return false;
+    if (a.epilogue == kEpiSwiglu) {
+        // F = 14336, K = 3584: 8 rows 37.6, 37.1; 32 rows 37.9, 41.2; F = 22016: 64 rows 71.5, 66.4; F = 28672: 8 rows
+        // 72.8, 73.6; 64 rows 80.9, 91.4.
+        const int F = a.N / 2;
+        return F <= 12288 || (F <= 16384 ? few : F <= 24576);
+    }
+    if (a.N <= 8192) return true;
+    // N = 16384: 32 rows, K = 512 6.3, 7.3 (accumulating); 64 rows, K = 1536 13.2, 14.1; K = 3584 34.7, 26.1
+    if (a.N <= 16384) return (a.N <= 12288 ? some : few) || a.K >= 2048;
+    // N = 32768, K = 3584: 32 rows 38.3, 35.7; 64 rows 38.3, 39.1; K = 6144, 64 rows 76, 85.  A vocabulary (N = 151936, 64
+    // rows): K = 1536 117, 114; K = 3584 227, 244.  N = 24000, 20 rows: K = 128 4.6, 5.1; K = 256 the same.
+    return few || (some && a.K >= 256) || (a.epilogue == kEpiStoreF32 && a.N > 24576 && a.K < 3072);
 }
 
 hipError_t launch_gemm_skinny(const GemmArgs& a, int epi, int splits, hipStream_t s) {

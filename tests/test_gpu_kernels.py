@@ -76,6 +76,40 @@ def test_gemm_skinny_row_and_column_edges(rpo, M, N, K):
             _gemm_case(rpo, M, N, K, torch.bfloat16, epi, path=0, seed=7, ws_mb=ws_mb, pad=pad)
 
 
+@pytest.mark.parametrize("M", [5, 16, 30, 50])
+@pytest.mark.parametrize("N", [4096, 4104, 8192, 8204, 12288, 12300, 16400, 24580])
+def test_gemm_skinny_blocks_per_workgroup(rpo, M, N):
+    """One to four 16-column weight blocks per workgroup: the widest of each choice, and one that ends inside a block."""
+    for epi in (0, 1, 2):
+        _gemm_case(rpo, M, N, 320, torch.bfloat16, epi, path=0, seed=13, pad=8 if N % 8 else 0)
+
+
+@pytest.mark.parametrize("M,N,K,epi,few", [
+    (64, 768, 8192, 0, False), (64, 768, 8192, 3, False), (1, 1536, 8192, 3, True), (24, 2048, 8192, 3, False),
+    (33, 512, 4160, 1, False), (17, 512, 6208, 0, False), (64, 3584, 18944, 2, False), (48, 16384, 1024, 0, False),
+    (64, 512, 4096, 0, True), (32, 512, 6144, 0, True), (16, 512, 8192, 1, True), (64, 1536, 8960, 2, True),
+    (64, 10240, 2048, 0, True), (20, 32768, 256, 1, True), (40, 32768, 4096, 1, False)])
+def test_gemm_few_rows_takes_the_faster_kernel(rpo, M, N, K, epi, few):
+    """Up to 64 rows: a deep K that the tiles split over the CUs, and the widths where their rows fill better, stay
+    with the tiles (64 x 768 x 8192 gate/up: 15 us against 42 when all of it went to the few-row kernel)."""
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    a = torch.randn(M, K, device="cuda", generator=g).to(torch.bfloat16)
+    w = (torch.randn(N, K, device="cuda", generator=g) * 0.05).to(torch.bfloat16)
+    n_out = N // 2 if epi == 3 else N
+    c = torch.zeros(M, n_out, device="cuda", dtype=torch.bfloat16 if epi in (0, 3) else torch.float32)
+    ws = torch.empty(32 << 20, dtype=torch.uint8, device="cuda")
+    rpo.rpo_set_kernel_path(0)
+    rpo.rpo_profile_start(rpo.KERNEL_IDS["gemm_skinny"], 1)
+    rpo.rpo_gemm_nt(a, w, c, epi, ws)
+    assert rpo.rpo_profile_stop(rpo.KERNEL_IDS["gemm_skinny"])[0] == (1 if few else 0)
+    exact = a.float() @ w.float().t()
+    if epi == 3:
+        exact = torch.nn.functional.silu(exact[:, :n_out]) * exact[:, n_out:]
+    # bf16 results: half a last place; the fp32 sums of both sides: a few 2^-24 sqrt(K) of the terms' size
+    err = (c.float() - exact).norm() / exact.norm()
+    assert err < (4e-3 if epi in (0, 3) else 1e-4)
+
+
 @pytest.mark.parametrize("M", [65, 128, 129, 250, 512])
 @pytest.mark.parametrize("N,K", [(5, 64), (200, 192), (1540, 1536), (2048, 320), (2052, 3584), (4100, 128)])
 def test_gemm_skinny_row_groups(rpo, M, N, K):
@@ -99,7 +133,9 @@ def test_gemm_mfma_bf16_every_tile_shape(rpo, shape, path):
                                    (1, 32, 64), (512, 8960, 64), (8, 8960, 192), (17, 416, 128), (64, 18944, 576), (33, 2592, 448),
                                    (300, 18944, 3584), (264, 8032, 512), (100, 18944, 512), (200, 18944, 512),
                                    (192, 8960, 320), (129, 8992, 256), (72, 18944, 256), (128, 18944, 192),
-                                   (1000, 8960, 192), (1100, 8960, 192)])
+                                   (1000, 8960, 192), (1100, 8960, 192),
+                                   (9, 2048, 192), (30, 2080, 192), (64, 4128, 192), (8, 6176, 192), (50, 8224, 192),
+                                   (16, 10272, 192), (33, 12288, 192), (7, 12320, 192), (40, 16416, 192), (64, 20512, 192)])
 def test_gemm_swiglu(rpo, M, F, K, path, ws_mb):
     """Fused gate/up projection: C = silu(A Wg^T) * (A Wu^T), W = [gate rows; up rows].  Path 27 forces
     the 256x192 tile and path 30 the 128x160 one (gate / up rows interleaved in blocks of 16), which path 0 picks for
