@@ -30,11 +30,17 @@ namespace rpo {
 // 512 rows 9.7 -> 8.2 (four); N = 1536: 8.9 -> 5.9, 9.2 -> 6.6, 9.8 -> 8.5; N = K = 3584: 128 rows 20.1 -> 14.7 (two),
 // 256 rows 21.5 -> 19.2 (four).  Past one round: 512 rows of N = 2048 with two blocks 11.1; N = 4608, K = 3584, 256 rows
 // with four 31.5 against 31.4.  A deep K (down) and a wide N (gate/up) lose: 22.9 -> 25.3, 34.1 -> 35.9 us at 256 rows.
+// A round is counted per XCD: all groups of a column block go to one of them, so 35 blocks of 7 groups put 35
+// workgroups on the 32 CUs of three XCDs and 28 on the others (N = 1100, 400 rows, K = 512 to 3584, accumulating: 6.1 ->
+// 7.8, 9.5 -> 11.4, 16.5 -> 17.6 us with two blocks).  Less than four slabs leave waves without one (N = 5120,
+// K = 64, 96 rows 3.4 -> 3.9), and over a shallow K four blocks have too little to do for the residual's read at their
+// end (accumulating: 96 rows, N = 8192, K = 1536 10.7 -> 12.4; 512 rows, N = 1100, K = 512 6.2 -> 7.2).
 int gemm_skinny_groups(const GemmArgs& a) {
-    if (a.K > 4096 || a.M > 512 || (a.epilogue != kEpiStore && a.epilogue != kEpiAddF32)) return 0;
+    if (a.K > 4096 || a.K < 256 || a.M > 512 || (a.epilogue != kEpiStore && a.epilogue != kEpiAddF32)) return 0;
     const int groups = ceil_div(a.M, 64);
     for (int nb = 1; nb <= 4; nb *= 2)
-        if ((int64_t)ceil_div(a.N, nb * 16) * groups <= 256) return nb;
+        if ((int64_t)ceil_div(ceil_div(a.N, nb * 16), 8) * groups <= 32)
+            return nb == 4 && a.epilogue == kEpiAddF32 && a.K < (groups == 2 ? 2048 : 1024) ? 0 : nb;
     return 0;
 }
 

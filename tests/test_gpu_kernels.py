@@ -119,6 +119,17 @@ def test_gemm_skinny_row_groups(rpo, M, N, K):
         _gemm_case(rpo, M, N, K, torch.bfloat16, epi, path=0, seed=11, pad=pad)
 
 
+@pytest.mark.parametrize("M,N,K,epi,groups", [
+    (400, 1100, 512, 2, False), (400, 1100, 1024, 2, True), (512, 2048, 1536, 0, True), (448, 2048, 512, 0, True), (448, 2064, 512, 0, False),
+    (96, 8192, 1536, 2, False), (96, 8192, 2048, 2, True), (96, 8192, 1536, 0, True), (96, 4608, 192, 0, False)])
+def test_gemm_row_groups_fit_one_round_of_every_xcd(rpo, M, N, K, epi, groups):
+    """The eight XCDs take the column blocks in turn, with all their row groups: 32 workgroups each, not 256 in all."""
+    rpo.rpo_set_kernel_path(0)
+    rpo.rpo_profile_start(rpo.KERNEL_IDS["gemm_skinny"], 1)
+    _gemm_case(rpo, M, N, K, torch.bfloat16, epi, path=0, seed=17)
+    assert rpo.rpo_profile_stop(rpo.KERNEL_IDS["gemm_skinny"])[0] == (1 if groups else 0)
+
+
 @pytest.mark.parametrize("path", [17, 19, 20, 21, 22, 27])
 @pytest.mark.parametrize("shape", [(300, 520, 1536), (77, 1536, 4480)])
 def test_gemm_mfma_bf16_every_tile_shape(rpo, shape, path):
