@@ -1268,6 +1268,8 @@ bool dma2_ok(const GemmArgs& a, int splits, int stages = 2) {
            (uint64_t)256 * (uint64_t)a.lda * sizeof(bf16) < (1ull << 32);  // a tile's activation rows as well
 }
 
+int pick_splits(const GemmArgs& a, const TileCfg& t);
+
 TileCfg pick_tile(const GemmArgs& a) {
     if (a.path >= 16) {  // tuning aid: a fixed tile shape
         switch (a.path - 16) {
@@ -1296,10 +1298,11 @@ TileCfg pick_tile(const GemmArgs& a) {
     // four-deep load pipeline beat wider tiles whose K-split partial sums need a second kernel;
     // with a deep K, 128x128 tiles split along K.
     const int t256 = ceil_div(a.M, 256) * ceil_div(a.N, 256);
-    // The two narrower tiles interleave gate and up rows as only gemm_dma2_kernel does: what it does not take
-    // (a single K slab, for one) stays with the tiles whose register-staged form is right.
-    // The gate/up projection of a decode step, and 128x128 tiles that outnumber the CUs (two of them on some, one on
-    // most): 128x160 tiles with four stages, if one round holds them.  They also halve the padding of up to 128 rows.
+    // The narrower gate/up tiles (128x160, 256x160, 256x192) interleave gate and up rows as only gemm_dma2_kernel
+    // does: what it does not take (a single K slab, for one) stays with the tiles whose register-staged form is right.
+    //
+    // The gate/up projection of a decode step whose 128x128 tiles outnumber the CUs (two of them on some CUs, one on
+    // most) takes 128x160 tiles with four stages, if one round holds those.  They also halve the padding of up to 128 rows.
     // Weights from HBM, us, 128x128 or 256x160 tiles -> these: K = 1536, N = 17920, 192 rows 30.1 -> 22.8, 256 rows 33.5 ->
     // 24.3; K = 3584, N = 37888, 72 rows 74.6 -> 55.2, 128 rows 85.2 -> 59.7 (4.5 TB/s of weights).  Where 128x128 tiles
     // fit one round they stay: more CUs work on them (128 rows of N = 17920: 22.4 against 24.5).
@@ -1331,10 +1334,18 @@ TileCfg pick_tile(const GemmArgs& a) {
         // -> 115 (192); N = 37888, K = 3584: 300 rows 169 -> 128, 512 rows 180 -> 139 (160), 600 rows 185 stays (196 and 221).
         const int r256 = ceil_div(t256, 256);
         if (a.epilogue == kEpiSwiglu && a.M > 256 && r256 <= 4 && dma2_ok(a, 1, 3) && (a.N / 2) % 16 == 0) {
+            // A few 256x256 tiles split K over the CUs, which the other two cannot: a share of a round, about 17 ns per
+            // value of K, and the reduction, about 10 us and its partial sums at 4 TB/s each way.  us, K = 8192: 520 x
+            // 1024 32 split, 117 with 256x160 tiles; K = 3584: 700 x 2048 34, 58; 2048 x 2048 50, 60; 2500 x 2048 76, 60; K =
+            // 1536: 2048 x 2048 35, 30.
+            const int s256 = pick_splits(a, TileCfg{kKidGemm256, 256, 256});
+            const double c256 = s256 == 1 ? r256
+                                          : (double)ceil_div(t256 * s256, 256) / s256 +
+                                                (10. + 1e-6 * s256 * a.M * a.N) / (0.017 * a.K);
             const double c192 = ceil_div(ceil_div(a.M, 256) * ceil_div(a.N, 192), 256) * 0.86;
             const double c160 = ceil_div(ceil_div(a.M, 256) * ceil_div(a.N, 160), 256) * 0.76;
-            if (c160 < r256 * 0.97 && c160 <= c192) return TileCfg{kKidGemm256x160, 256, 160};
-            if (c192 < r256 * 0.97) return TileCfg{kKidGemm256x192, 256, 192};
+            if (c160 < c256 * 0.97 && c160 <= c192) return TileCfg{kKidGemm256x160, 256, 160};
+            if (c192 < c256 * 0.97) return TileCfg{kKidGemm256x192, 256, 192};
         }
         return TileCfg{kKidGemm256, 256, 256};
     }

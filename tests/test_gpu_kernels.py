@@ -411,6 +411,26 @@ def test_profile_sampling_and_peak_probe(rpo):
     assert 200.0 < mfma_tflops < 2500.0               # below the published bf16 MFMA peak
 
 
+@pytest.mark.parametrize("M,N,K,split", [(520, 1024, 8192, True), (700, 2048, 3584, True), (2048, 2048, 3584, True),
+                                         (2500, 2048, 3584, False), (2048, 2048, 1536, False), (1000, 17920, 1536, False)])
+def test_gate_up_of_few_tiles_splits_k(rpo, M, N, K, split):
+    """Gate/up of 513 rows up: 256x256 tiles that split K over the CUs where those are too few, 256x160 ones (which
+    cannot) where they fill their rounds better."""
+    a = torch.randn(M, K, device="cuda").to(torch.bfloat16)
+    w = (torch.randn(N, K, device="cuda") * 0.02).to(torch.bfloat16)
+    c = torch.zeros(M, N // 2, device="cuda", dtype=torch.bfloat16)
+    ws = torch.empty(96 << 20, dtype=torch.uint8, device="cuda")
+    rpo.rpo_set_kernel_path(0)
+    for name in ("gemm256_swiglu", "gemm256x160"):
+        rpo.rpo_profile_start(rpo.KERNEL_IDS[name], 1)
+    rpo.rpo_gemm_nt(a, w, c, 3, ws)
+    assert rpo.rpo_profile_stop(rpo.KERNEL_IDS["gemm256_swiglu"])[0] == (1 if split else 0)
+    assert rpo.rpo_profile_stop(rpo.KERNEL_IDS["gemm256x160"])[0] == (0 if split else 1)
+    exact = a.float() @ w.float().t()
+    exact = torch.nn.functional.silu(exact[:, :N // 2]) * exact[:, N // 2:]
+    assert (c.float() - exact).norm() / exact.norm() < 4e-3     # half a last place of bf16
+
+
 def test_profile_sees_the_kernels_of_a_decode_step(rpo):
     """The few-row kernel (a K split with its reduction: one launch) and the 128x160 gate/up tile have ids of their own."""
     rpo.rpo_set_kernel_path(0)
