@@ -523,22 +523,28 @@ hipError_t launch_attn_chunk(const AttnArgs& a, hipStream_t s) {
 }
 
 // Prefix pieces per group: about two workgroups per CU.  A piece walks its pages one after the other (a microsecond
-// and more per page when little else runs), so a few groups
-// are cut finer (up to 16 pieces, not 8): rollout passes of the 7B shape, 2 x 8: 385.3 -> 383.0 ms.
+// and more per page when little else runs), so a few groups are cut into up to 16 pieces, but beyond eight only while
+// these and the private pieces are resident together (two workgroups per CU).  us a launch, eight pieces / up to 16: 12
+// query heads on 2 KV heads, 1 x 8 rollouts, 4000 tokens 17.8 / 13.3, 5 x 6, 2100 tokens 12.7 / 12.2; 16 x 8, 2100 tokens
+// would be 19.1 / 23.5; 28 heads on 4, 2 x 8, 4000 tokens 18.8 / 15.6, 8 x 8, 2100 tokens would be 19.6 / 24.3.
 constexpr int kMaxSplit = 16;
-static int decode_splits(int n_groups_live, int Hkv, int n_ct, int max_shared_pages) {
+static int decode_splits(int n_groups_live, int Hkv, int n_ct, int G, int max_shared_pages) {
     if (max_shared_pages <= 0) return 1;
     int want = ceil_div(512, n_groups_live * Hkv * n_ct);
-    want = want < 1 ? 1 : (want > kMaxSplit ? kMaxSplit : want);
+    if (want > 8) {
+        const int room = (512 / (n_groups_live * Hkv) - G) / n_ct;
+        want = want < room ? want : room;
+        want = want < 8 ? 8 : (want > kMaxSplit ? kMaxSplit : want);
+    }
     const int cap = max_shared_pages / 2 > 0 ? max_shared_pages / 2 : 1;  // at least two pages per piece
     want = want < cap ? want : cap;
-    // no pieces that the longest prefix leaves empty (16 x 8, 7B shape, 17 - 20 pages: 633.3 -> 628.6 ms)
+    // no pieces that the longest prefix leaves empty (28 heads on 4, 16 x 8, 1100 tokens 28.1 -> 25.6 us)
     return ceil_div(max_shared_pages, ceil_div(max_shared_pages, want));
 }
 
 size_t attn_decode_partial_floats(int rows, int Hq, int dh, int max_shared_pages) {
     (void)max_shared_pages;
-    return (size_t)rows * Hq * 17 * (dh + 2);
+    return (size_t)rows * Hq * (kMaxSplit + 1) * (dh + 2);
 }
 
 hipError_t launch_attn_decode(const DecodeAttnArgs& d, hipStream_t s) {
@@ -553,7 +559,7 @@ hipError_t launch_attn_decode(const DecodeAttnArgs& d, hipStream_t s) {
     dg.n_rows = d.n_rollouts;
     dg.row_of = d.row_of;
     const int n_groups_live = ceil_div(d.n_rollouts, d.G);
-    dg.n_split = decode_splits(n_groups_live, a.Hkv, dg.n_ct, d.max_shared_pages);
+    dg.n_split = decode_splits(n_groups_live, a.Hkv, dg.n_ct, d.G, d.max_shared_pages);
     const size_t n_slots = (size_t)d.n_rollouts * a.Hq * (dg.n_split + 1);
     if (n_slots * (kDh + 2) > d.partial_floats) return hipErrorInvalidValue;
     float* part_o = d.partial;

@@ -505,6 +505,14 @@ def test_attn_decode_alone_small(rpo):
                       suffix_views=(0, 1, 37, 70), check_groups=(0, 2, 3, 5), seed=61)
 
 
+@pytest.mark.parametrize("prefix_lens", [(2100, 1200, 70), (1310, 700), (1180,)])
+def test_attn_decode_alone_more_than_eight_prefix_pieces(rpo, prefix_lens):
+    """A few groups with long prefixes: 16, 10 and 9 prefix pieces; the shorter groups leave some of theirs empty."""
+    mcfg = synth.ModelCfg("attn-1layer-fine", 1, 256, 6, 1, 128, 256, 512, "bf16")
+    _attn_decode_case(rpo, mcfg, prefix_lens=prefix_lens, G=8, n_fill=3, suffix_views=(3,),
+                      check_groups=range(len(prefix_lens)), seed=63)
+
+
 def test_attn_decode_alone_benchmark_shape(rpo):
     """The 1.5B benchmark's attention launch: 64 groups x 8 rollouts, 12 q / 2 kv heads, ~2000-token
     shared prefixes (31-32 shared pages per group, four prefix pieces per group and KV head), 150
