@@ -53,7 +53,8 @@ int rpo_attn_decode(struct rpo_batch *b, int32_t layer, const void *q_dev, int32
  * tight serving loops, harnesses that forbid hipMalloc): the same contraction, kernels and
  * results, with the K-split partial sums in a fixed 16 MiB device array that belongs to the
  * library (one copy per GPU, held until the process ends).  Allocates nothing, on the host or the
- * device.  Arguments as rpo_gemm_nt.  A problem whose K split needs more than 16 MiB of partial
+ * device; the first call on a GPU has the runtime load the kernels' code there, if no other call has
+ * (a few MB), so that no later one does.  Arguments as rpo_gemm_nt.  A problem whose K split needs more than 16 MiB of partial
  * sums (splits * M * N * 4 bytes; only skinny problems with a deep K are split) is rejected with
  * RPO_ENOMEM and nothing is enqueued.  All calls on one GPU share the array: calls that may run
  * concurrently on one GPU (different streams, different threads) race on it; calls on one

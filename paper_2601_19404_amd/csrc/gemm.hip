@@ -1598,8 +1598,14 @@ size_t gemm_splitk_scratch_bytes(const GemmArgs& a) {
     GemmArgs u = a;
     u.ws = (void*)(uintptr_t)256;  // never dereferenced: only "a workspace exists"
     u.ws_bytes = ~(size_t)0;
-    const int splits = pick_splits(u, pick_tile(u));
+    const int splits = skinny_ok(u) ? gemm_skinny_splits(u) : pick_splits(u, pick_tile(u));
     return splits > 1 ? (size_t)splits * a.M * a.N * sizeof(float) : 0;
+}
+
+hipError_t gemm_load_kernels() {
+    hipFuncAttributes attr;
+    const hipError_t e = hipFuncGetAttributes(&attr, (const void*)gemm_splitk_reduce_kernel<kEpiStore>);
+    return e == hipSuccess ? gemm_skinny_load_kernels() : e;
 }
 
 int gemm_kernel_id(const GemmArgs& a) {

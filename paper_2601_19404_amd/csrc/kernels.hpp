@@ -116,6 +116,10 @@ enum KernelId : int {
     kKidGemmSkinny = 15,    // gemm_skinny_kernel (few rows, every epilogue; a K split includes its reduction)
     kKidCount = 16,
 };
+// Has the runtime load the code objects of the GEMM kernels onto the current device now (it does so, a few MB each, at
+// the first launch out of each of them otherwise).
+hipError_t gemm_load_kernels();
+hipError_t gemm_skinny_load_kernels();
 // Which kernel launch_gemm picks for these arguments.
 int gemm_kernel_id(const GemmArgs& a);
 // Bytes of fp32 K-split partial sums launch_gemm would write for these arguments if the

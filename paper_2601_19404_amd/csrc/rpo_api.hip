@@ -1178,6 +1178,7 @@ extern "C" int rpo_gemm_nt_noalloc(const void* a_dev, int64_t lda, const void* w
         void* p = nullptr;
         HIP_TRY(hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)));
         if (!p) return fail(RPO_EHIP, "rpo_gemm_nt_noalloc: the scratch array has no device address");
+        HIP_TRY(gemm_load_kernels());  // no later call is the first to launch out of a code object
         g_scratch_ptr[dev] = p;
     }
     GemmArgs g;

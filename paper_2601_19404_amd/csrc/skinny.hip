@@ -462,6 +462,11 @@ bool gemm_skinny_takes(const GemmArgs& a, bool tiles_split_k) {
     return few || (some && a.K >= 256) || (a.epilogue == kEpiStoreF32 && a.N > 24576 && a.K < 3072);
 }
 
+hipError_t gemm_skinny_load_kernels() {
+    hipFuncAttributes attr;
+    return hipFuncGetAttributes(&attr, (const void*)gemm_skinny_kernel<1, 1, 8, 4, kEpiStore>);
+}
+
 hipError_t launch_gemm_skinny(const GemmArgs& a, int epi, int splits, hipStream_t s) {
     if (splits > 1) return launch_epi<kEpiPartial>(a, s, splits);
     switch (epi) {

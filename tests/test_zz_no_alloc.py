@@ -26,8 +26,10 @@ def test_noalloc_gemm_matches_workspace_gemm_twice_second_call_smaller():
     # the code object that holds it (its 16 MiB are taken then, once, until the process ends)
     a0, w0 = _operands(64, 256, 1024, seed=1)
     rpo.rpo_gemm_nt_noalloc(a0, w0, torch.zeros(64, 256, device="cuda"), 1)
-    # skinny problems with a deep K: split along K, partial sums in the scratch
-    for (M, N, K, epi) in ((512, 1536, 8960, 2), (200, 1536, 8960, 2), (96, 768, 4096, 1), (40, 2048, 2048, 3)):
+    # skinny problems with a deep K: split along K, partial sums in the scratch (the last three on tiles of 64 rows and
+    # in the few-row kernel; 40 x 2048 x 2048 is not split any more)
+    for (M, N, K, epi) in ((512, 1536, 8960, 2), (200, 1536, 8960, 2), (96, 768, 4096, 1), (40, 2048, 2048, 3),
+                           (40, 2048, 8192, 3), (40, 1536, 8960, 2), (8, 512, 4096, 2)):
         a, w = _operands(M, N, K, seed=M + N)
         n_out = N // 2 if epi == 3 else N
         dt = torch.bfloat16 if epi in (0, 3) else torch.float32
