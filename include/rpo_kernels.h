@@ -105,7 +105,9 @@ int rpo_set_kernel_path(int path);
  *   6  <64,64,2,2> (decode-sized problems, shallow K, no K split)
  *      (all epilogues of a tile shape together; a K-split launch includes its reduction)
  *   11 <256,192,4,2> (large M with a narrow N: fewer idle CUs in the last round of workgroups)
- *   13 <256,160,4,1>, 14 <128,160,4,1> (gate/up projection of a decode step, where one round holds their tiles)
+ *   13 <256,160,4,1> (gate/up projection of a decode step, where one round holds its tiles, and of a small
+ *      chunk, where it fills its rounds better)
+ *   14 <128,160,4,1> (gate/up projection of a decode step, where one round holds its tiles)
  *   15 gemm_skinny_kernel (up to 64 rows, and narrow projections of up to 512 in groups of 64; every
  *      epilogue; a K-split launch includes its reduction)
  *   7  gemm_generic_kernel      8  attn_decode_mfma_kernel (+ merge)   9  attn_chunk_mfma_kernel

@@ -144,13 +144,14 @@ def test_gemm_mfma_bf16_every_tile_shape(rpo, shape, path):
                                    (1, 32, 64), (512, 8960, 64), (8, 8960, 192), (17, 416, 128), (64, 18944, 576), (33, 2592, 448),
                                    (300, 18944, 3584), (264, 8032, 512), (100, 18944, 512), (200, 18944, 512),
                                    (192, 8960, 320), (129, 8992, 256), (72, 18944, 256), (128, 18944, 192),
-                                   (1000, 8960, 192), (1100, 8960, 192),
+                                   (1000, 8960, 192), (1100, 8960, 192), (2600, 8960, 192), (2600, 8960, 256),
                                    (9, 2048, 192), (30, 2080, 192), (64, 4128, 192), (8, 6176, 192), (50, 8224, 192),
                                    (16, 10272, 192), (33, 12288, 192), (7, 12320, 192), (40, 16416, 192), (64, 20512, 192)])
 def test_gemm_swiglu(rpo, M, F, K, path, ws_mb):
     """Fused gate/up projection: C = silu(A Wg^T) * (A Wu^T), W = [gate rows; up rows].  Path 27 forces
     the 256x192 tile and path 30 the 128x160 one (gate / up rows interleaved in blocks of 16), which path 0 picks for
-    decode batches (192 x 8960, 129 x 8992, 72 x 18944 and 128 x 18944: the latter; two rounds: 1000 x 8960 256x160, 1100 x 8960 256x192)."""
+    decode batches (192 x 8960, 129 x 8992, 72 x 18944 and 128 x 18944: the latter; two rounds: 1000 x 8960 256x160, 1100 x 8960 256x192;
+    2600 x 8960: 1232 tiles of 256x160, which resident workgroups walk)."""
     g = torch.Generator().manual_seed(M + F)
     a = torch.randn(M, K, generator=g).to(torch.bfloat16)
     w = (torch.randn(2 * F, K, generator=g) * 0.05).to(torch.bfloat16)
@@ -412,7 +413,8 @@ def test_profile_sampling_and_peak_probe(rpo):
 
 
 @pytest.mark.parametrize("M,N,K,split", [(520, 1024, 8192, True), (700, 2048, 3584, True), (2048, 2048, 3584, True),
-                                         (2500, 2048, 3584, False), (2048, 2048, 1536, False), (1000, 17920, 1536, False)])
+                                         (2500, 2048, 3584, False), (2048, 2048, 1536, False), (1000, 17920, 1536, False),
+                                         (2600, 17920, 256, False)])
 def test_gate_up_of_few_tiles_splits_k(rpo, M, N, K, split):
     """Gate/up of 513 rows up: 256x256 tiles that split K over the CUs where those are too few, 256x160 ones (which
     cannot) where they fill their rounds better."""
