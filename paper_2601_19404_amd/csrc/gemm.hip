@@ -23,7 +23,8 @@
 //    the MFMA operands swapped, which leaves a lane with one row and runs of four columns.
 //  * gemm_mfma_kernel: the same tiling with register-staged LDS fills, for K that is not a
 //    multiple of 64 (and selectable for comparison).
-//  * skinny.hip: up to 64 rows, K a multiple of 64.
+//  * skinny.hip: up to 64 rows, and narrow projections of up to 512 in groups of 64, K a multiple of 64 (the rules
+//    are there).
 //  * gemm_generic_kernel: any dtype on the vector ALUs (fp32 tiny model, shapes the
 //    MFMA kernels do not take).
 #include "kernels.hpp"
@@ -796,16 +797,6 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const bf16* __res
 // (none after the workgroup's last tile), and inside a slab every MFMA is followed by one fragment read
 // / one load so that the matrix pipe never waits behind a burst of memory instructions.
 // ---------------------------------------------------------------------------
-__device__ inline void dma_load16_s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr) {
-    asm volatile(
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %0, %1\n\t"
-        :
-        : "v"(voff), "s"(sbase), "s"(lds_byte_addr)
-        : "memory");
-}
-
 template <int MI, int NI, int TM, int TN, int BN, int WN, int EPI, int SWIGLU>
 __device__ inline void dma2_epilogue(f32x16_t (&acc)[MI][NI], void* __restrict__ Cv, int64_t ldc, int M, int N, int m0,
                                      int n0, int wm, int wn, int lane, int split, const LseFuse& lf) {
@@ -1331,7 +1322,7 @@ TileCfg pick_tile(const GemmArgs& a) {
         // The same for gate/up: a round of 256x192 tiles costs about 0.86 and one of 256x160 tiles 0.76 of a round of
         // 256x256 (measured up to four of those; beyond, the last round weighs little).  us, 256x256 -> chosen: N = 17920,
         // K = 1536: 1000 rows 80.6 -> 65.5 (160), 1280 rows 86 -> 76 (192), 1400 rows 87 stays (95 and 103), 2048 rows 127
-        // -> 115 (192); N = 37888, K = 3584: 300 rows 169 -> 128, 512 rows 180 -> 139 (160), 600 rows 185 stays (196 and 221).
+        // -> 115 (192), 2561 to 2816 rows 158 - 166 -> 152 - 157 (160); N = 37888, K = 3584: 300 rows 169 -> 128, 512 rows 180 -> 139 (160), 600 rows 185 stays (196 and 221).
         const int r256 = ceil_div(t256, 256);
         if (a.epilogue == kEpiSwiglu && a.M > 256 && r256 <= 4 && dma2_ok(a, 1, 3) && (a.N / 2) % 16 == 0) {
             // A few 256x256 tiles split K over the CUs, which the other two cannot: a share of a round, about 17 ns per
@@ -1465,8 +1456,8 @@ hipError_t launch_one(const GemmArgs& a, int splits, void* out, hipStream_t s) {
                                       (EPI == kEpiRope && a.rope) ? *a.rope : RopeKvArgs{}, LseFuse{});
         return hipGetLastError();
     }
-    if constexpr (EPI == kEpiRope || EPI == kEpiLse || EPI == kEpiLogitsMax) {
-        return hipErrorInvalidValue;  // only the direct-to-LDS kernel has this epilogue
+    if constexpr (EPI == kEpiRope || EPI == kEpiLse || EPI == kEpiLogitsMax || SWIGLU == 2) {
+        return hipErrorInvalidValue;  // only the direct-to-LDS kernels have this epilogue or this order of gate / up rows
     } else {
         const size_t lds = (size_t)2 * (BM + BN) * kLdsRow * sizeof(bf16);
         auto kern = gemm_mfma_kernel<BM, BN, WM, WN, EPI, SWIGLU>;

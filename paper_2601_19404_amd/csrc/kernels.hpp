@@ -9,6 +9,18 @@ namespace rpo {
 // g * sigmoid(g); the hardware reciprocal (1 ulp) replaces the IEEE division sequence
 __device__ inline float silu_f(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
+// 16 bytes per lane from global memory (uniform base + 32-bit lane offset) straight into LDS at
+// lds_byte_addr + 16 * lane.  The compiler does not see the load: every wait for it is written out.
+__device__ inline void dma_load16_s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr) {
+    asm volatile(
+        "s_mov_b32 m0, %2\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %0, %1\n\t"
+        :
+        : "v"(voff), "s"(sbase), "s"(lds_byte_addr)
+        : "memory");
+}
+
 enum DType : int { kF32 = 0, kBF16 = 1 };
 
 inline size_t dtype_size(int dt) { return dt == kF32 ? 4 : 2; }
@@ -111,7 +123,7 @@ enum KernelId : int {
     kKidAttnChunk = 9,      // attn_chunk_mfma_kernel
     kKidSample = 10,        // sample_kernel
     kKidGemm256Swiglu = 12, // <256,256,2,4> with the fused SwiGLU epilogue (gate/up of prefill / log-prob chunks)
-    kKidGemm256x160 = 13,   // <256,160,4,1> fused SwiGLU only (decode gate/up: one round of workgroups on more CUs)
+    kKidGemm256x160 = 13,   // <256,160,4,1> fused SwiGLU only (gate/up of a decode step in one round of workgroups on more CUs, and of up to 2816 rows where it fills its rounds better)
     kKidGemm128x160 = 14,   // <128,160,4,1> the same with four stages, where 256-row tiles would be half padding or too few
     kKidGemmSkinny = 15,    // gemm_skinny_kernel (few rows, every epilogue; a K split includes its reduction)
     kKidCount = 16,

@@ -806,8 +806,8 @@ int decode_step_body(rpo_batch* b, const int32_t* tokens_dev, int rows, int n_ro
         LseFuse bm;
         bm.part = b->at<float>(L.blkmax);
         g.block_max = &bm;
-        // A handful of rows streams the LM-head weights either way: keep the 256-wide tile whose
-        // epilogue knows the maxima rather than sweep the logits again.
+        // 65 to 512 rows over a small vocabulary would take narrower tiles: keep the 256-wide one, whose
+        // epilogue knows the maxima, rather than sweep the logits again.
         if (g.path == 0 && gemm_fuses_max(g) == 0) {
             g.path = 16 + kKidGemm256;
             if (gemm_fuses_max(g) == 0) g.path = 0;

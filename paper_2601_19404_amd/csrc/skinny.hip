@@ -50,17 +50,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x4_t __attribute__((ext_vector_type(4)));
 
-// 16 bytes per lane from global memory (uniform base + 32-bit lane offset) straight into LDS at
-// lds_byte_addr + 16 * lane.  The compiler does not see the load: every wait for it is written out.
-__device__ inline void dma_load16_s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr) {
-    asm volatile(
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %0, %1\n\t"
-        :
-        : "v"(voff), "s"(sbase), "s"(lds_byte_addr)
-        : "memory");
-}
 template <int N>
 __device__ inline void wait_loads() {  // all but the newest N loads of this wave have landed
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
