@@ -436,6 +436,10 @@ bool gemm_skinny_takes(const GemmArgs& a, bool tiles_split_k) {
     if (gemm_skinny_splits(a) > 1) return few || a.K <= (some ? 20480 : a.N <= 4096 ? 12288 : 4096);
     // Tiles that split K over the CUs against workgroups that walk all of it (store, N = 1536: 64 rows, K = 4096 13.2,
     // 12.6, K = 8192 17.3, 21.4; 24 rows, K = 8192 14.8, 14.1, K = 16384 18.1, 24.9; 8 rows, K = 16384 18.0, 17.2).
+    // A QKV projection whose tiles split K rotates in the reduction, one workgroup per row, which costs more
+    // (a decode step of four layers, K = 5120, N = 7168, 48 rows 922, 808; K = 8192, N = 10240, 24 rows 1585, 1480, 64 rows
+    // 1695, 1764).
+    if (a.rope && tiles_split_k) return some || a.K <= 6144;
     if (tiles_split_k && a.K > (few ? 16384 : some ? 6144 : 4096)) return false;
     if (a.epilogue == kEpiSwiglu) {
         // F = 14336, K = 3584: 8 rows 37.6, 37.1; 32 rows 37.9, 41.2; F = 22016: 64 rows 71.5, 66.4; F = 28672: 8 rows
