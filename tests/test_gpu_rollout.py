@@ -283,8 +283,8 @@ def test_bf16_two_kv_heads_many_rollouts_mfma(rpo):
 
 
 def test_bf16_many_rows_wide_rotary_tile(rpo):
-    """528 rollouts x 16 heads: more 32-row tiles than CUs, so the QKV projection of a decode step
-    takes its 64-row tiles (rotation and KV page write in the epilogue), with a ragged last tile."""
+    """528 rollouts x 16 heads: above 512 rows the QKV projection of a decode step takes the wide tiles
+    and the rotation and KV page write a kernel of their own, with a ragged last tile."""
     ng = 33
     lens = tuple(20 + (5 * k) % 23 for k in range(ng))
     p, a, m = bf16_workload(BF16_2KV, lens=lens, ms=(2,) * ng, seed=5)
@@ -297,6 +297,26 @@ def test_bf16_rotary_projection_in_row_groups(rpo, n_groups):
     mcfg = synth.ModelCfg("row-groups", 2, 512, 24, 4, 128, 512, 512, "bf16")
     p, a, m = bf16_workload(mcfg, lens=tuple(20 + 7 * i for i in range(n_groups)), ms=(3,) * n_groups, seed=4)
     run_case(rpo, mcfg, p, a, m, G=16)
+
+
+@pytest.mark.parametrize("n_groups", [13, 16])
+def test_bf16_rotary_tiles_of_a_decode_step(rpo, n_groups):
+    """28 q / 4 kv heads: 4608 columns do not fit one round of row groups at 208 and 256 rows, so the QKV projection runs
+    on the rotary tiles, 32 rows tall at 208 (252 tiles) and 64 at 256; the groups end one after the other."""
+    mcfg = synth.ModelCfg("rotary-tiles", 2, 256, 28, 4, 128, 512, 512, "bf16")
+    p, a, m = bf16_workload(mcfg, lens=tuple(20 + 7 * i for i in range(n_groups)), ms=(4,) + (3,) * (n_groups - 1), seed=8)
+    rpo.rpo_profile_start(rpo.KERNEL_IDS["gemm32"], 1)
+    run_case(rpo, mcfg, p, a, m, G=16)
+    assert rpo.rpo_profile_stop(rpo.KERNEL_IDS["gemm32"])[0] >= 2 * 2      # two layers of two steps at least
+
+
+@pytest.mark.parametrize("d_model,G", [(4160, 4), (4160, 24), (6528, 24)])
+def test_bf16_rotary_projection_of_few_rows_deep_in_k(rpo, d_model, G):
+    """Up to 64 rows the rotary projection where its tiles would split K: few-row kernel with one and two weight blocks;
+    6528 values deep and 48 rows: tiles split along K, rotated in the reduction."""
+    mcfg = synth.ModelCfg("deep-rotary", 1, d_model, 28, 4, 128, 256, 512, "bf16")
+    p, a, m = bf16_workload(mcfg, lens=(20, 41), ms=(3, 3), seed=12)
+    run_case(rpo, mcfg, p, a, m, G=G, oracle_rollouts=[0, G - 1])
 
 
 def test_bf16_deep_down_projection_of_a_wide_model(rpo):
