@@ -1,5 +1,8 @@
 """Pins for oracle/philox.py and oracle/sampler.py."""
+import math
 import os
+import struct
+from fractions import Fraction
 
 import numpy as np
 import pytest
@@ -127,13 +130,9 @@ def test_logprob_output_and_row_map():
     np.testing.assert_array_equal(toks, t2)
 
 
-def test_weights_as_a_truncating_double_sum():
-    """The sweep of the kernel in numpy: x + 1.5 * 2^23 rounds x and holds n in its low bits, p 2^n is an integer
-    addition to p's bits, and the floor is the truncation of a double in [2^12, 2^13) to its last place, 2^-40."""
-    rng = np.random.default_rng(0)
-    edges = np.array([0.0, -0.0, -0.5, -1.5, -2.5, -39.5, -40.0, -40.5, -41.0, -59.9, -60.0, -1e30, -np.inf], np.float32)
-    edges = np.concatenate([edges, np.nextafter(edges[:11], np.float32(-1e3)), np.nextafter(edges[2:11], np.float32(0))])
-    x = np.concatenate([edges, (-62.0 * rng.random(200000)).astype(np.float32)])
+def _sweep_weights(x):
+    """p 2^n of the kernel's sweep as doubles: x + 1.5 * 2^23 rounds x and holds n in its low bits, and p 2^n is an
+    integer addition to p's bits."""
     c = np.fmax(x, np.float32(-60.0))
     t = c + np.float32(1.5 * 2 ** 23)
     f = c - (t - np.float32(1.5 * 2 ** 23))
@@ -141,5 +140,59 @@ def test_weights_as_a_truncating_double_sum():
     for k in sampler.COEF[6::-1]:
         p = p * f
         p = p + k
-    w = (p.view(np.uint32) + (t.view(np.uint32) << np.uint32(23))).view(np.float32).astype(np.float64)
+    return (p.view(np.uint32) + (t.view(np.uint32) << np.uint32(23))).view(np.float32).astype(np.float64)
+
+
+def _edge_exponents():
+    edges = np.array([0.0, -0.0, -0.5, -1.5, -2.5, -39.5, -40.0, -40.5, -41.0, -59.9, -60.0, -1e30, -np.inf], np.float32)
+    return np.concatenate([edges, np.nextafter(edges[:11], np.float32(-1e3)), np.nextafter(edges[2:11], np.float32(0))])
+
+
+def test_weights_of_the_sweep():
+    rng = np.random.default_rng(0)
+    x = np.concatenate([_edge_exponents(), (-62.0 * rng.random(200000)).astype(np.float32)])
+    w = _sweep_weights(x)
     np.testing.assert_array_equal(np.floor(w * 2.0 ** 40).astype(np.uint64), sampler.exp2_fixed(x))
+
+
+def _add_f64(acc, w, toward_zero=True):
+    """acc + w in double precision, rounded toward zero (or to nearest, ties to even), from the exact sum."""
+    exact = Fraction(acc) + Fraction(w)
+    last = Fraction(2) ** (math.frexp(float(exact))[1] - 53)
+    if exact < last * 2 ** 52:                       # float() has rounded up to the next power of two
+        last /= 2
+    n = exact / last
+    return float((math.floor(n) if toward_zero else round(n)) * last)
+
+
+def _bits(v):
+    return struct.unpack("<q", struct.pack("<d", v))[0]
+
+
+def test_weights_as_a_truncating_double_sum():
+    """The kernel's sum of 16 weights: doubles added to 2^12 with rounding toward zero, the integer sum read off the
+    mantissa (a double in [2^12, 2^13) has a last place of 2^-40)."""
+    rng = np.random.default_rng(1)
+    below = np.float32(-41.0) + rng.uniform(-1e-3, 1.0, size=(20, 16)).astype(np.float32)   # around 2^-40 and below
+    spread = (-62.0 * rng.random((100, 16))).astype(np.float32)
+    peaked = (-3.0 * rng.random((60, 16))).astype(np.float32)
+    e = _edge_exponents()
+    edges = rng.choice(e, size=(40, 16))
+    x = np.concatenate([np.zeros((1, 16), np.float32), np.full((1, 16), -41.0, np.float32),
+                        np.full((1, 16), -np.inf, np.float32), below, spread, peaked, edges])
+    differ = 0
+    for row in x:
+        want = int(np.sum(sampler.exp2_fixed(row), dtype=np.uint64))
+        acc = nearest = 4096.0
+        for w in _sweep_weights(row):
+            acc, nearest = _add_f64(acc, float(w)), _add_f64(nearest, float(w), toward_zero=False)
+        assert 4096.0 <= acc < 8192.0 and _bits(acc) - _bits(4096.0) == want
+        differ += _bits(nearest) - _bits(4096.0) != want
+    assert differ > 50                               # the rounding mode is what makes the sums exact
+
+
+def test_double_addition_of_this_test():
+    rng = np.random.default_rng(2)
+    for a, b in zip(4096.0 + 3000.0 * rng.random(500), np.ldexp(rng.random(500), rng.integers(-60, 3, size=500))):
+        assert _add_f64(a, b, toward_zero=False) == a + b
+        assert _add_f64(a, b) in (a + b, math.nextafter(a + b, 0.0)) and Fraction(_add_f64(a, b)) <= Fraction(a) + Fraction(b)
