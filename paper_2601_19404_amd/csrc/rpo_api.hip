@@ -1197,6 +1197,16 @@ extern "C" int rpo_gemm_nt_noalloc(const void* a_dev, int64_t lda, const void* w
     g.ws = g_scratch_ptr[dev];
     g.ws_bytes = kScratchBytes;
     const size_t need = gemm_splitk_scratch_bytes(g);
+    if (need > kScratchBytes) {  // gate/up tiles that never split K hold some of these in few rounds
+        GemmArgs unsplit = g;
+        unsplit.ws = nullptr;
+        unsplit.ws_bytes = 0;
+        const int id = gemm_kernel_id(unsplit);
+        if (epilogue == kEpiSwiglu && (id == kKidGemm256x160 || id == kKidGemm256x192)) {
+            HIP_TRY(launch_gemm(unsplit, (hipStream_t)stream));
+            return RPO_OK;
+        }
+    }
     if (need > kScratchBytes)
         return fail(RPO_ENOMEM,
                     "rpo_gemm_nt_noalloc: this problem splits K and needs %zu bytes of partial sums; the static "

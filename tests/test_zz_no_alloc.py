@@ -52,6 +52,22 @@ def test_noalloc_gemm_matches_workspace_gemm_twice_second_call_smaller():
         np.testing.assert_allclose(got.float().cpu().numpy(), exact.cpu().numpy(), atol=0.15, rtol=2e-2)
 
 
+def test_noalloc_gate_up_beyond_the_scratch_on_unsplit_tiles():
+    from paper_2601_19404_amd import binding as rpo
+    rpo.lib()
+    rpo.rpo_set_kernel_path(0)
+    # 24 tiles of 256 x 256 in seven K splits would need 40 MB: 256 x 160 tiles without a split, as without a workspace
+    a, w = _operands(700, 2048, 3584, seed=6)
+    got, ref = (torch.zeros(700, 1024, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    rpo.rpo_gemm_nt_noalloc(a, w, got, 3)
+    rpo.rpo_gemm_nt(a, w, ref, 3, None)
+    torch.cuda.synchronize()
+    assert torch.equal(ref, got)
+    exact = a.float() @ w.float().t()
+    exact = torch.nn.functional.silu(exact[:, :1024]) * exact[:, 1024:]
+    assert (got.float() - exact).norm() / exact.norm() < 4e-3     # half a last place of bf16
+
+
 def test_noalloc_gemm_rejects_what_the_scratch_cannot_hold():
     from paper_2601_19404_amd import binding as rpo
     rpo.lib()
