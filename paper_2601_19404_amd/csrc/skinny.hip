@@ -3,10 +3,12 @@
 //
 // What bounds them is how fast a CU can be fed: 64 rows use a weight 64 times, far from what the matrix
 // cores need to be the limit, and every weight byte comes from HBM once per decode step (the layers
-// together are larger than every cache).  Measured on this chip, all CUs reading: loads of whole
-// 128-byte lines into LDS reach 120 GB/s per CU from L2 and 7.5 TB/s from HBM; the fragment layout
-// loaded straight into registers (16 rows x 64 bytes per instruction) reaches 38 GB/s per CU from L2
-// whatever is in flight, and a kernel built on it lost to the 64-row tiles from 16 rows on.  Hence:
+// together are larger than every cache).  Measured on this chip: loads of whole 128-byte lines, into LDS or
+// into registers, reach 133 GB/s per CU from L2 (all CUs reading 2 MB) and 107 from HBM (16 CUs reading); the
+// fragment layout (16 rows x 64 bytes per instruction) reaches 37 and 38 whatever is in flight.  All CUs together get
+// 6.0 to 6.2 TB/s from HBM either way (6 GiB read once; 7.4 to 9.1 TB/s from 128 MB, which the 256 MB memory-side
+// cache holds), so it is the activations, read again by every workgroup, that the layout decides over: a kernel built on
+// fragments lost to the 64-row tiles from 16 rows on.  Hence:
 //   * weights and activations go to LDS in pieces of 8 rows x 128 bytes, and every wave has a ring of
 //     its own that only it reads: the main loop has no barrier, a wave waits for its own loads only;
 //   * K is split over the NW waves of a workgroup (wave w takes slabs w, w + NW, ...), so a narrow
