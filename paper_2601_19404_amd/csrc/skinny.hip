@@ -362,7 +362,9 @@ hipError_t launch_rows(const GemmArgs& a, int splits, hipStream_t s) {
         if (units <= 256 * 4) return launch_one<MA, 4, 4, 1, EPI>(a, ceil_div(units, 4), s);
         if (units <= 256 * 5) return launch_one<MA, 5, 4, 1, EPI>(a, ceil_div(units, 5), s);
         if (units <= 256 * 6) return launch_one<MA, 6, 4, 1, EPI>(a, ceil_div(units, 6), s);
-        if (units <= 512 * 4) return launch_one<MA, 4, 2, 2, EPI>(a, ceil_div(units, 4), s);
+        if constexpr (MA <= 2) {  // more rows of these widths are not taken
+            if (units <= 512 * 4) return launch_one<MA, 4, 2, 2, EPI>(a, ceil_div(units, 4), s);
+        }
         if (units <= 512 * 5) return launch_one<MA, 5, 2, 2, EPI>(a, ceil_div(units, 5), s);
         return launch_one<MA, 6, 2, 2, EPI>(a, ceil_div(units, 6), s);
     } else if constexpr (EPI == kEpiRope) {
