@@ -2,7 +2,7 @@
 // the decoder (QKV, O, gate/up, down, LM head).  Both operands are K-contiguous.
 //
 //  * gemm_dma_kernel / gemm_dma2_kernel: bf16 operands on the CDNA4 matrix cores
-//    (v_mfma_f32_32x32x16_bf16).  64-deep K slabs go from global memory straight into LDS
+//    (v_mfma_f32_32x32x16_bf16; in gemm_dma2_kernel v_mfma_f32_16x16x32_bf16).  64-deep K slabs go from global memory straight into LDS
 //    (global_load_lds_dwordx4), two to four stages deep; fragments are double-buffered in registers.
 //    Tile shapes and what they are for (pick_tile): 256x256 (many-tile problems: prefill / log-prob
 //    chunks, wide decode projections), 256x192 / 256x160 (large M with a narrow N, decode gate/up),
@@ -10,9 +10,9 @@
 //    workspace and a reduction kernel applies the epilogue -- deterministic, no floating-point
 //    atomics), 64x64 and 32x128 (shallow-K decode projections, one tile per CU, no K split).
 //    (tile, K-split) work items are dealt evenly to the 8 XCDs, neighbouring tiles to the same XCD
-//    (each has its own L2).  The wide two-stage tiles run on gemm_dma2_kernel: every MFMA is followed
-//    by one fragment read or one load (the matrix pipe never waits behind a burst of memory
-//    instructions), the barrier of a slab sits before its last k-step (the next slab's first
+//    (each has its own L2).  The wide two-stage tiles run on gemm_dma2_kernel: fragment reads and loads are
+//    spread between the MFMAs of a k-step (the matrix pipe never waits behind a burst of memory
+//    instructions), the barrier of a slab sits before its second k-step (the next slab's first
 //    fragments and the loads of the slab after it go out under that k-step's MFMAs), and when a
 //    launch has many rounds of tiles one resident workgroup per CU walks its share of them, the
 //    next tile's first loads in flight during the epilogue.
@@ -27,6 +27,8 @@
 //    are there).
 //  * gemm_generic_kernel: any dtype on the vector ALUs (fp32 tiny model, shapes the
 //    MFMA kernels do not take).
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace rpo {
@@ -791,31 +793,121 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const bf16* __res
 }
 
 // ---------------------------------------------------------------------------
-// Direct-to-LDS kernel of the wide tiles, S stages (2, or 3 where the tile leaves room in the 160 KiB
+// Direct-to-LDS kernel of the wide tiles, S stages (2, or 3 and 4 where the tile leaves room in the 160 KiB
 // of LDS).  A workgroup walks over several tiles (virtual block ids blockIdx.x, blockIdx.x + gridDim.x,
 // ...): the loads of the next tile's first S slabs go out during the last S slabs of the current one
-// (none after the workgroup's last tile), and inside a slab every MFMA is followed by one fragment read
-// / one load so that the matrix pipe never waits behind a burst of memory instructions.
+// (none after the workgroup's last tile), and inside a slab every MFMA is followed by at most one fragment read
+// and one load so that the matrix pipe never waits behind a burst of memory instructions.
+//
+// The large launches are bound by power: the chip lowers its clock until the kernel fits (a variant with 7 % fewer
+// cycles a tile ran at a 4 % lower clock), so what counts is energy per product and not only filled issue slots.  Hence
+// v_mfma_f32_16x16x32_bf16: it reads and writes an accumulator every 32 values of K instead of every 16.  A loop of
+// nothing but MFMAs on changing operands sustains 2.04 PFLOP/s with it and 1.80 with the 32x32x16 form, 1.83 and 1.66
+// with this kernel's fragment reads beside them.  With it and the order of reads and loads below, before -> now, us:
+// 32768 x 17920 x 1536 gate/up 1500 -> 1340 (1.35 PFLOP/s), 15360 x 37888 x 3584 3290 -> 2966, 32768 x 2048 x 1536 (bf16)
+// 185 -> 158, 32535 x 1536 x 8960 (accumulating) 800 -> 744, 512 x 17920 x 1536 gate/up 34.7 -> 33.0, 256 x 17920 24.6 ->
+// 25.2.  Tried and no faster: three stages of A beside two of B (deep K -2 %, K = 1536 +3 %), four waves of 128x128, bands
+// of five and six tile columns.
+//
+// Operands swapped (weights first): lane l holds activation row l % 16 of a 16x16 block and its four consecutive
+// columns 4 (l / 16) .. + 3.
 // ---------------------------------------------------------------------------
-template <int MI, int NI, int TM, int TN, int BN, int WN, int EPI, int SWIGLU>
-__device__ inline void dma2_epilogue(f32x16_t (&acc)[MI][NI], void* __restrict__ Cv, int64_t ldc, int M, int N, int m0,
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+
+__device__ inline u32x2_t pack_bf16x4(float a, float b, float c, float d) {
+    return u32x2_t{(uint32_t)f32_to_bf16(a).bits | (uint32_t)f32_to_bf16(b).bits << 16,
+                   (uint32_t)f32_to_bf16(c).bits | (uint32_t)f32_to_bf16(d).bits << 16};
+}
+
+// NB neighbouring 16-column blocks of bf16 results of one row: v[j] are columns col + 16 j + 4 (lane / 16) .. + 3, col a
+// multiple of 16.  Two blocks at a time trade halves between the lane groups (v_permlane16_swap: odd rows of 16 lanes
+// of the one register with even rows of the other), after which a lane holds eight neighbouring columns: 16-byte stores,
+// 64 bytes of a row together.  `row` is the row's first element, nullptr: this row does not exist.
+template <int NB>
+__device__ inline void store_bf16_blocks(u32x2_t (&v)[NB], bf16* row, int col, int n_cols, int64_t ldc, int lane) {
+    const int g = lane >> 4;
+    const bool vec16 = (ldc & 7) == 0 && ((uintptr_t)row & 15) == 0, vec8 = (ldc & 3) == 0 && ((uintptr_t)row & 7) == 0;
+#pragma unroll
+    for (int j = 0; j < NB; j += 2) {
+        if (j + 1 < NB && col + 16 * j + 32 <= n_cols) {  // wave-uniform
+            const u32x2_t lo = __builtin_amdgcn_permlane16_swap(v[j].x, v[j + 1 < NB ? j + 1 : j].x, false, false);
+            const u32x2_t hi = __builtin_amdgcn_permlane16_swap(v[j].y, v[j + 1 < NB ? j + 1 : j].y, false, false);
+            const int c = col + 16 * (j + (g & 1)) + 8 * (g >> 1);
+            if (!row) continue;
+            if (vec16) {
+                *(u32x4_t*)(row + c) = u32x4_t{lo.x, hi.x, lo.y, hi.y};
+            } else if (vec8) {
+                *(u32x2_t*)(row + c) = u32x2_t{lo.x, hi.x};
+                *(u32x2_t*)(row + c + 4) = u32x2_t{lo.y, hi.y};
+            } else {
+                const uint32_t w[4] = {lo.x, hi.x, lo.y, hi.y};
+#pragma unroll
+                for (int e = 0; e < 8; ++e) row[c + e].bits = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+            }
+        } else {
+#pragma unroll
+            for (int b = j; b < (j + 2 < NB ? j + 2 : NB); ++b) {
+                const int c = col + 16 * b + 4 * g;
+                if (!row) continue;
+                if (vec8 && c + 3 < n_cols) {
+                    *(u32x2_t*)(row + c) = v[b];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (c + e < n_cols) row[c + e].bits = (uint16_t)(v[b][e >> 1] >> (16 * (e & 1)));
+                }
+            }
+        }
+    }
+}
+
+// max and sum over the four lanes that share a row
+__device__ inline float max_over_row(float v) {
+    v = fmaxf(v, __shfl_xor(v, 16, 64));
+    return fmaxf(v, __shfl_xor(v, 32, 64));
+}
+
+template <int MI, int NI, int TM, int TN, int BN, int WN, int EPI, int SW>
+__device__ inline void dma2_epilogue(f32x4_t (&acc)[MI][NI], void* __restrict__ Cv, int64_t ldc, int M, int N, int m0,
                                      int n0, int wm, int wn, int lane, int split, const LseFuse& lf) {
-    constexpr bool kTrans = EPI != kEpiStore;
-    if constexpr (EPI == kEpiLse) {
-        const int half = lane >> 5;
-        const int blk = (n0 / BN) * WN + wn;
-        const int cbase = n0 + wn * TN;
+    const int r_in = lane & 15, g = lane >> 4;
+    const int cbase = n0 + wn * TN;
+    if constexpr (EPI == kEpiSwiglu || EPI == kEpiStore) {
+        // Gate and up of an output column sit in the same register of two blocks: neighbours where the weight rows are
+        // interleaved by 16 (SW 2), two apart where by 32 (SW 1).
+        constexpr int NB = EPI == kEpiSwiglu ? NI / 2 : NI;
+        const int n_cols = EPI == kEpiSwiglu ? N / 2 : N, col = EPI == kEpiSwiglu ? cbase >> 1 : cbase;
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
-            const int r = m0 + wm * TM + i * 32 + (lane & 31);
+            const int gm = m0 + wm * TM + i * 16 + r_in;
+            u32x2_t v[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                if constexpr (EPI == kEpiSwiglu) {
+                    const f32x4_t gt = acc[i][SW == 2 ? 2 * b : 4 * (b / 2) + (b & 1)];
+                    const f32x4_t up = acc[i][SW == 2 ? 2 * b + 1 : 4 * (b / 2) + 2 + (b & 1)];
+                    v[b] = pack_bf16x4(silu_f(gt[0]) * up[0], silu_f(gt[1]) * up[1], silu_f(gt[2]) * up[2],
+                                       silu_f(gt[3]) * up[3]);
+                } else {
+                    v[b] = pack_bf16x4(acc[i][b][0], acc[i][b][1], acc[i][b][2], acc[i][b][3]);
+                }
+            }
+            store_bf16_blocks<NB>(v, gm < M ? (bf16*)Cv + (int64_t)gm * ldc : nullptr, col, n_cols, ldc, lane);
+        }
+    } else if constexpr (EPI == kEpiLse) {
+        const int blk = (n0 / BN) * WN + wn;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const int r = m0 + wm * TM + i * 16 + r_in;
             const int tgt = r < M ? lf.target[r] : -1;
             float mx = -INFINITY, zt = 0.f;
             bool have = false;
 #pragma unroll
             for (int j = 0; j < NI; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int col = cbase + j * 32 + 8 * (e >> 2) + 4 * half + (e & 3);
+                for (int e = 0; e < 4; ++e) {
+                    const int col = cbase + j * 16 + 4 * g + e;
                     const float v = col < N ? acc[i][j][e] : -INFINITY;
                     acc[i][j][e] = v;
                     mx = fmaxf(mx, v);
@@ -824,17 +916,18 @@ __device__ inline void dma2_epilogue(f32x16_t (&acc)[MI][NI], void* __restrict__
                         have = true;
                     }
                 }
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            mx = max_over_row(mx);
             const float muse = mx == -INFINITY ? 0.f : mx;
             const float nb = -muse * lf.k2;
             float sum = 0.f;
 #pragma unroll
             for (int j = 0; j < NI; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][e], lf.k2, nb));
+                for (int e = 0; e < 4; ++e) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][e], lf.k2, nb));
+            sum += __shfl_xor(sum, 16, 64);
             sum += __shfl_xor(sum, 32, 64);
             if (r < M) {
-                if (half == 0) {
+                if (g == 0) {
                     float* p = lf.part + ((int64_t)r * lf.blocks + blk) * 2;
                     p[0] = mx;
                     p[1] = sum;
@@ -843,56 +936,111 @@ __device__ inline void dma2_epilogue(f32x16_t (&acc)[MI][NI], void* __restrict__
             }
         }
     } else if constexpr (EPI == kEpiLogitsMax) {
-        // transposed accumulators: a lane owns a row and, per register quad, four consecutive columns
-        const int half = lane >> 5;
         const int blk = (n0 / BN) * WN + wn;
-        const int cbase = n0 + wn * TN;
         float* C = (float*)Cv;
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
-            const int r = m0 + wm * TM + i * 32 + (lane & 31);
+            const int r = m0 + wm * TM + i * 16 + r_in;
             float mx = -INFINITY;
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int col = cbase + j * 32 + 8 * q + 4 * half;
-                    if (r < M && col < N) {  // N is a multiple of 4 (checked by the launcher): whole quads
-                        const float4 v = float4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2],
-                                                acc[i][j][4 * q + 3]};
-                        *(float4*)(C + (int64_t)r * ldc + col) = v;
-                        mx = fmaxf(fmaxf(mx, fmaxf(v.x, v.y)), fmaxf(v.z, v.w));
-                    }
+            for (int j = 0; j < NI; ++j) {
+                const int col = cbase + j * 16 + 4 * g;
+                if (r < M && col < N) {  // N is a multiple of 4 (checked by the launcher): whole quads
+                    const f32x4_t v = acc[i][j];
+                    *(f32x4_t*)(C + (int64_t)r * ldc + col) = v;
+                    mx = fmaxf(fmaxf(mx, fmaxf(v[0], v[1])), fmaxf(v[2], v[3]));
                 }
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-            if (r < M && half == 0) lf.part[(int64_t)r * lf.blocks + blk] = mx;
+            }
+            mx = max_over_row(mx);
+            if (r < M && g == 0) lf.part[(int64_t)r * lf.blocks + blk] = mx;
         }
     } else {
-        if constexpr (kTrans)
-            gemm_epilogue_t<MI, NI, TM, TN, EPI, SWIGLU>(acc, Cv, ldc, M, N, m0, n0, wm, wn, lane, split);
-        else
-            gemm_epilogue<MI, NI, TM, TN, EPI>(acc, Cv, ldc, M, N, m0, n0, wm, wn, lane, split);
+        // fp32 results: store, accumulate, or K-split partial sums
+        const int64_t ld = EPI == kEpiPartial ? (int64_t)N : ldc;
+        float* C = (float*)Cv + (EPI == kEpiPartial ? (int64_t)split * M * (int64_t)N : 0);
+        const bool vec = (ld & 3) == 0 && ((uintptr_t)C & 15) == 0;
+        if (vec && cbase + TN <= N) {
+            // Every column of the wave's blocks exists (the same answer in every lane): straight-line code, no
+            // wait between the writes.  Accumulating: all reads of 32 rows go out before their first write
+            // (the compiler may not move a read of C across a write to C; read and written quad by quad, every
+            // quad would wait a full memory round trip: o-projection of an 8192-row chunk 69 -> 51 us).  The reads are
+            // waited for on every path (rows beyond M read the last row): a read left pending in some lanes would
+            // make the compiler wait for it, and with it for all slabs in flight, at the head of the slab loop.
+            constexpr int RB = MI % 2 == 0 ? 2 : 1;
+#pragma unroll
+            for (int i = 0; i < MI; i += RB) {
+                f32x4_t c[RB][NI];
+#pragma unroll
+                for (int k = 0; k < RB; ++k)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) {
+                        if (EPI == kEpiAddF32) {
+                            const int gm = min(m0 + wm * TM + (i + k) * 16 + r_in, M - 1);
+                            c[k][j] = *(const f32x4_t*)(C + (int64_t)gm * ld + cbase + j * 16 + 4 * g);
+                        } else {
+                            c[k][j] = acc[i + k][j];
+                        }
+                    }
+                if (EPI == kEpiAddF32) {
+#pragma unroll
+                    for (int k = 0; k < RB; ++k)
+#pragma unroll
+                        for (int j = 0; j < NI; ++j) {
+                            c[k][j] += acc[i + k][j];
+                            asm volatile("" : "+v"(c[k][j]));  // the sum is formed here, not under the branch below
+                        }
+                }
+#pragma unroll
+                for (int k = 0; k < RB; ++k) {
+                    const int gm = m0 + wm * TM + (i + k) * 16 + r_in;
+                    if (gm >= M) continue;
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) *(f32x4_t*)(C + (int64_t)gm * ld + cbase + j * 16 + 4 * g) = c[k][j];
+                }
+            }
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const int gm = m0 + wm * TM + i * 16 + r_in;
+            if (gm >= M) continue;
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                const int gn = cbase + j * 16 + 4 * g;
+                float* dst = C + (int64_t)gm * ld + gn;
+                if (vec && gn + 3 < N) {
+                    *(f32x4_t*)dst = EPI == kEpiAddF32 ? *(const f32x4_t*)dst + acc[i][j] : acc[i][j];
+                } else {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        if (gn + t < N) dst[t] = EPI == kEpiAddF32 ? dst[t] + acc[i][j][t] : acc[i][j][t];
+                }
+            }
+        }
     }
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, int SWIGLU, int S = 2>
+template <int BM, int BN, int WM, int WN, int EPI, int SWIGLU, int S = 2, bool ONCE = false>
 __global__ __launch_bounds__(WM* WN * 64) void gemm_dma2_kernel(const bf16* __restrict__ A, int64_t lda,
                                                                 const bf16* __restrict__ W, int64_t ldw,
                                                                 void* __restrict__ Cv, int64_t ldc, int M,
                                                                 int N, int K, int grid_m, int grid_n,
                                                                 int n_tiles, int splits, int k_per_split, int F,
                                                                 int n_vblocks, LseFuse lf) {
-    constexpr int BK = 64, KS = 4;
+    constexpr int BK = 64;
     constexpr int NW = WM * WN;
     constexpr int TM = BM / WM, TN = BN / WN;
-    constexpr int MI = TM / 32, NI = TN / 32;
+    constexpr int MI = TM / 16, NI = TN / 16;
     constexpr int A_INST = BM / 8 / NW, B_INST = BN / 8 / NW;  // a wave instruction fills 8 rows (1 KiB)
     constexpr int A_STAGE = BM * BK, B_STAGE = BN * BK;        // elements
     constexpr int N_INST = A_INST + B_INST;
-    constexpr int kReads = (MI + NI + MI * NI - 1) / (MI * NI);  // fragment reads after every MFMA
+    constexpr int kRead = (MI * NI - 2) / (MI + NI);  // MFMAs from one fragment read to the next
+    constexpr int kLoad = MI * NI / N_INST;           // and from one load to the next, in the k-step that issues them
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile/wave mismatch");
+    static_assert(kRead >= 1 && kLoad >= 1, "a fragment read and a load find an MFMA to follow");
     static_assert(EPI != kEpiRope, "no LDS-staged epilogue here");
-    constexpr bool kTrans = EPI != kEpiStore;
+    static_assert(SWIGLU != 1 || EPI != kEpiSwiglu || NI % 4 == 0, "gate/up blocks of 32 inside a wave");
+    static_assert(EPI != kEpiSwiglu || NI % 2 == 0, "gate/up block pairs inside a wave");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     bf16* As = (bf16*)smem_raw;        // [S][BM][BK]
@@ -926,110 +1074,103 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma2_kernel(const bf16* __re
 #pragma unroll
         for (int j = 0; j < A_INST; ++j) {
             const int row = (j * NW + wave) * 8 + (lane >> 3);
-            const int piece = (lane & 7) ^ lds_swizzle<BK>(row);
+            const int piece = (lane & 7) ^ (row & 7);
             o.a_off[j] = (uint32_t)(((int64_t)min(row, M - 1 - m0) * lda + piece * 8) * 2);
         }
 #pragma unroll
         for (int j = 0; j < B_INST; ++j) {
             const int row = (j * NW + wave) * 8 + (lane >> 3);
-            const int piece = (lane & 7) ^ lds_swizzle<BK>(row);
+            const int piece = (lane & 7) ^ (row & 7);
             o.b_off[j] = (uint32_t)(((int64_t)weight_row<SWIGLU>(min(n0 + row, N - 1), F) * ldw + piece * 8) * 2);
         }
     };
-    // instruction t (A first, then B) of slab sl of tile source o into stage st
-    auto dma_one = [&](const Src& o, int sl, int st, int t, int on) __attribute__((always_inline)) {
-        if (!on) return;  // uniform
+    // The loads of slab sl of tile source o into stage st: bases in scalar registers, kept as they are, so that a load is
+    // three instructions (a wave that has its SIMD to itself shows every one of them).
+    struct Slab {
+        const bf16 *a, *b;
+        uint32_t lds_a, lds_b;
+    };
+    auto slab_src = [&](const Src& o, int sl, int st) __attribute__((always_inline)) {
+        Slab r{o.a_base + sl * BK, o.b_base + sl * BK, lds_a + (st * A_STAGE + wave * 512) * 2, lds_b + (st * B_STAGE + wave * 512) * 2};
+        asm volatile("" : "+s"(r.a), "+s"(r.b), "+s"(r.lds_a), "+s"(r.lds_b));
+        return r;
+    };
+    // instruction t (A first, then B)
+    auto dma_one = [&](const Src& o, const Slab& r, int t) __attribute__((always_inline)) {
         if (t < A_INST)
-            dma_load16_s(o.a_base + sl * BK, o.a_off[t], lds_a + (st * A_STAGE + (t * NW + wave) * 512) * 2);
+            dma_load16_at<false>(r.a, o.a_off[t], r.lds_a, t * NW * 1024);
         else
-            dma_load16_s(o.b_base + sl * BK, o.b_off[t - A_INST], lds_b + (st * B_STAGE + ((t - A_INST) * NW + wave) * 512) * 2);
+            dma_load16_at<ONCE>(r.b, o.b_off[t - A_INST], r.lds_b, (t - A_INST) * NW * 1024);
     };
 
     Src cur;
     setup(tc, cur);
-    f32x16_t acc[MI][NI];
+    f32x4_t acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+        for (int j = 0; j < NI; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-    const int frag_row = lane & 31;
-    const int frag_g = lds_swizzle<BK>(frag_row);
-    const int frag_half = lane >> 5;
+    // A slab is two k-steps of 32: lane l reads the 16-byte piece 4 ks + l / 16 of row l % 16 of a block, at position
+    // piece ^ (row % 8) of the row.  The LDS serves a 16-byte read in four turns of 16 lanes, lanes 0-3, 12-15, 20-23
+    // and 24-27 together: with the permutation of the 32-row blocks above (also ^ row / 8) two of them met in every
+    // bank and each read took twice as long.
+    const int frag_row = lane & 15;
+    const int frag_g = frag_row & 7;
     const int a_frag = (wm * TM + frag_row) * BK, b_frag = (wn * TN + frag_row) * BK;
-    const int piece0 = (frag_half ^ frag_g) * 8;
+    const int piece0 = ((lane >> 4) ^ frag_g) * 8, piece1 = ((4 + (lane >> 4)) ^ frag_g) * 8;
     bf16x8_t af[2][MI], bfr[2][NI];
 
 #pragma unroll
-    for (int sl = 0; sl < S; ++sl)
+    for (int sl = 0; sl < S; ++sl) {
+        const Slab r = slab_src(cur, sl, sl);
 #pragma unroll
-        for (int t = 0; t < N_INST; ++t) dma_one(cur, sl, sl, t, 1);
+        for (int t = 0; t < N_INST; ++t) dma_one(cur, r, t);
+    }
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 1) * N_INST) : "memory");
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < NI; ++j) bfr[0][j] = *(const bf16x8_t*)(Bs + b_frag + j * 32 * BK + piece0);
+    for (int j = 0; j < NI; ++j) bfr[0][j] = *(const bf16x8_t*)(Bs + b_frag + j * 16 * BK + piece0);
 #pragma unroll
-    for (int i = 0; i < MI; ++i) af[0][i] = *(const bf16x8_t*)(As + a_frag + i * 32 * BK + piece0);
+    for (int i = 0; i < MI; ++i) af[0][i] = *(const bf16x8_t*)(As + a_frag + i * 16 * BK + piece0);
 
-    // One slab (g = running slab count of this workgroup: stage g & 1).  The loads that go out in its
-    // last k-step fetch slab dma_sl of the tile `cur` describes, into this slab's stage.
+    // Multiply with fragment set c and read set c ^ 1 at `as_n`, `bs_n`; the MFMA order turns round in every row of
+    // blocks, so that one operand stays where it is from each MFMA to the next.  Reads and loads are spread over the
+    // k-step: eight waves that read their fragments in one go ask the LDS for twice what it delivers, and a wave
+    // behind a read that the LDS cannot take yet issues no MFMA either (2680 -> 2540 cycles a slab of 256x256).
+    auto k_step = [&](auto cc, const bf16* as_n, const bf16* bs_n, auto load) __attribute__((always_inline)) {
+        constexpr int c = decltype(cc)::value, n = c ^ 1;
+#pragma unroll
+        for (int t = 0; t < MI * NI; ++t) {
+            const int i = t / NI, j = i % 2 ? NI - 1 - t % NI : t % NI;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[c][j], af[c][i], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            const int q = t / kRead;
+            if (t % kRead == 0 && q < NI) bfr[n][q] = *(const bf16x8_t*)(bs_n + q * 16 * BK);
+            if (t % kRead == 0 && q >= NI && q < NI + MI) af[n][q - NI] = *(const bf16x8_t*)(as_n + (q - NI) * 16 * BK);
+            if (t % kLoad == kLoad / 2 && t / kLoad < N_INST) load(t / kLoad);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // One slab.  The loads that go out in its second k-step fetch slab dma_sl of the tile `cur` describes into this
+    // slab's stage.
     auto slab_body = [&](const int stage, const int dma_sl, const int on) __attribute__((always_inline)) {
         const int stage1 = stage + 1 == S ? 0 : stage + 1;
-        const bf16* as = As + stage * A_STAGE + a_frag;
-        const bf16* bs = Bs + stage * B_STAGE + b_frag;
-#pragma unroll
-        for (int ks = 0; ks < KS - 1; ++ks) {
-            const int c = ks & 1, n = c ^ 1;
-            const int piece = (((ks + 1) * 2 + frag_half) ^ frag_g) * 8;
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NI; ++j) {
-                    const int t = i * NI + j;
-                    acc[i][j] = kTrans ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[c][j], af[c][i], acc[i][j], 0, 0, 0)
-                                       : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[c][i], bfr[c][j], acc[i][j], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int q = t * kReads; q < t * kReads + kReads; ++q) {
-                        if (q < NI) bfr[n][q] = *(const bf16x8_t*)(bs + q * 32 * BK + piece);
-                        else if (q < NI + MI) af[n][q - NI] = *(const bf16x8_t*)(as + (q - NI) * 32 * BK + piece);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-        }
-        // Last k-step: its fragments are in registers.  Once every wave's are, this stage is free, and the
-        // following slab has landed in the other stage.
-        constexpr int c = (KS - 1) & 1, n = c ^ 1;
-        // the S - 2 slabs after the next one may still be in flight -- unless the loads have stopped (tail of the
-        // workgroup's last tile): then everything outstanding is waited for
+        k_step(std::integral_constant<int, 0>{}, As + stage * A_STAGE + a_frag + piece1, Bs + stage * B_STAGE + b_frag + piece1,
+               [](int) {});
+        // The second k-step's fragments are in registers.  Once every wave's are, this stage is free, and the
+        // following slab has landed in the next one.  The S - 2 slabs after that may still be in flight -- unless the
+        // loads have stopped (tail of the workgroup's last tile): then everything outstanding is waited for.
         if (S > 2 && on)
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * N_INST) : "memory");
         else
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __syncthreads();
-        const bf16* as1 = As + stage1 * A_STAGE + a_frag;
-        const bf16* bs1 = Bs + stage1 * B_STAGE + b_frag;
-        constexpr int kPer = (N_INST + MI * NI - 1) / (MI * NI);
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                const int t = i * NI + j;
-                acc[i][j] = kTrans ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[c][j], af[c][i], acc[i][j], 0, 0, 0)
-                                   : __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[c][i], bfr[c][j], acc[i][j], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int q = t * kReads; q < t * kReads + kReads; ++q) {
-                    if (q < NI) bfr[n][q] = *(const bf16x8_t*)(bs1 + q * 32 * BK + piece0);
-                    else if (q < NI + MI) af[n][q - NI] = *(const bf16x8_t*)(as1 + (q - NI) * 32 * BK + piece0);
-                }
-#pragma unroll
-                for (int d = 0; d < kPer; ++d)
-                    if (t * kPer + d < N_INST) dma_one(cur, dma_sl, stage, t * kPer + d, on);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+        const bf16 *as1 = As + stage1 * A_STAGE + a_frag + piece0, *bs1 = Bs + stage1 * B_STAGE + b_frag + piece0;
+        const Slab r = slab_src(cur, dma_sl, stage);
+        k_step(std::integral_constant<int, 1>{}, as1, bs1, [&](int t) __attribute__((always_inline)) {
+            if (on) dma_one(cur, r, t);  // uniform; a second copy of the k-step without loads would spill the accumulators
+        });
     };
 
     // this workgroup's tiles: virtual blocks blockIdx.x + i * gridDim.x while they map to a work item
@@ -1061,9 +1202,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma2_kernel(const bf16* __re
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+            for (int j = 0; j < NI; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
@@ -1399,7 +1538,7 @@ bool norm_fusable(const GemmArgs& a) {
            ((uintptr_t)a.norm_out % 8 == 0) && ((uintptr_t)a.norm_gain % 8 == 0);
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, int SWIGLU, int DST = kDmaStages, int DBK = kDmaBK>
+template <int BM, int BN, int WM, int WN, int EPI, int SWIGLU, int DST = kDmaStages, int DBK = kDmaBK, bool ONCE = false>
 hipError_t launch_one(const GemmArgs& a, int splits, void* out, hipStream_t s) {
     // direct-to-LDS pipeline shape: DBK-deep slabs in DST stages
     const int gm = ceil_div(a.M, BM), gn = ceil_div(a.N, BN);
@@ -1419,7 +1558,7 @@ hipError_t launch_one(const GemmArgs& a, int splits, void* out, hipStream_t s) {
         constexpr int S = (BM == 256 && BN == 160) ? 3 : DST;
         if (dma2_ok(a, splits, S)) {
             const size_t lds = (size_t)S * (BM + BN) * 64 * sizeof(bf16);
-            auto kern = gemm_dma2_kernel<BM, BN, WM, WN, EPI, SWIGLU, S>;
+            auto kern = gemm_dma2_kernel<BM, BN, WM, WN, EPI, SWIGLU, S, ONCE>;
             static bool attr_set2 = false;  // one flag per template instance
             if (!attr_set2) {
                 hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1626,6 +1765,8 @@ static hipError_t launch_gemm_only(const GemmArgs& a, int splits, const TileCfg&
         case kKidGemm256x160:
             return launch_one<256, 160, 4, 1, kEpiSwiglu, 2>(a, 1, a.C, s);
         case kKidGemm128x160:
+            // one row of tiles: every weight row is read by one workgroup (K = 3584, N = 37888, 128 rows 57.0 -> 52.3 us)
+            if (a.M <= 128) return launch_one<128, 160, 4, 1, kEpiSwiglu, 2, 4, 64, true>(a, 1, a.C, s);
             return launch_one<128, 160, 4, 1, kEpiSwiglu, 2, 4>(a, 1, a.C, s);
         case kKidGemm256x192:
             if (a.epilogue == kEpiSwiglu) return launch_one<256, 192, 4, 2, kEpiSwiglu, 2>(a, 1, a.C, s);

@@ -10,15 +10,32 @@ namespace rpo {
 __device__ inline float silu_f(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
 // 16 bytes per lane from global memory (uniform base + 32-bit lane offset) straight into LDS at
-// lds_byte_addr + 16 * lane.  The compiler does not see the load: every wait for it is written out.
+// lds_byte_addr + off + 16 * lane.  The compiler does not see the load: every wait for it is written out.
+// ONCE is for data that is read once (weights that no other workgroup reads): the non-temporal hint keeps it from
+// taking the place of other lines on its way.  256 CUs streaming rows of 128 bytes from HBM: 6.15 -> 7.05 TB/s; for
+// lines that others read as well it is a loss (activations, each read by every CU: 113 -> 59 GB/s per CU).
+template <bool ONCE>
+__device__ inline void dma_load16_at(const void* sbase, uint32_t voff, uint32_t lds_byte_addr, int off) {
+    if constexpr (ONCE)
+        asm volatile(
+            "s_add_u32 m0, %2, %3\n\t"
+            "s_nop 0\n\t"
+            "global_load_lds_dwordx4 %0, %1 nt\n\t"
+            :
+            : "v"(voff), "s"(sbase), "s"(lds_byte_addr), "i"(off)
+            : "memory", "scc");
+    else
+        asm volatile(
+            "s_add_u32 m0, %2, %3\n\t"
+            "s_nop 0\n\t"
+            "global_load_lds_dwordx4 %0, %1\n\t"
+            :
+            : "v"(voff), "s"(sbase), "s"(lds_byte_addr), "i"(off)
+            : "memory", "scc");
+}
+
 __device__ inline void dma_load16_s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr) {
-    asm volatile(
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %0, %1\n\t"
-        :
-        : "v"(voff), "s"(sbase), "s"(lds_byte_addr)
-        : "memory");
+    dma_load16_at<false>(sbase, voff, lds_byte_addr, 0);
 }
 
 enum DType : int { kF32 = 0, kBF16 = 1 };

@@ -196,6 +196,38 @@ def test_gemm_swiglu_resident_and_three_stage_tiles(rpo, M, F, K):
     assert np.all(err <= tol), f"max err {err.max()}"
 
 
+@pytest.mark.parametrize("cpad", [8, 4, 1])
+@pytest.mark.parametrize("M,N,K,epi,path", [
+    (257, 528, 192, 0, 17), (300, 1003, 128, 0, 17), (140, 400, 256, 0, 27), (700, 1056, 192, 2, 17), (129, 520, 192, 1, 27),
+    (600, 2112, 192, 3, 17), (600, 2112, 192, 3, 27), (600, 2112, 192, 3, 29), (200, 2112, 256, 3, 30), (90, 37888, 256, 3, 0)])
+def test_gemm_wide_tiles_column_ends_and_row_strides(rpo, M, N, K, epi, path, cpad):
+    """The 16-byte stores of two neighbouring 16-column blocks and what stands in for them: columns that end inside
+    a block, inside a pair of blocks or between them, row strides that are no multiple of 16 or of 8 bytes."""
+    g = torch.Generator().manual_seed(K + N)
+    a = torch.randn(M, K, generator=g).bfloat16()
+    w = (torch.randn(N, K, generator=g) * 0.1).bfloat16()
+    n_out = N // 2 if epi == 3 else N
+    c0 = torch.randn(M, n_out + cpad, generator=g).to(torch.float32 if epi in (1, 2) else torch.bfloat16)
+    c = c0.cuda()
+    rpo.rpo_set_kernel_path(path)
+    rpo.rpo_gemm_nt(a.cuda(), w.cuda(), c[:, :n_out], epi, None)
+    torch.cuda.synchronize()
+    ref = a.double() @ w.double().t()
+    scale = K ** 0.5 * 0.1
+    tol = 1e-6 * ref.abs() + 2e-5 * scale                       # fp32 accumulation
+    if epi == 2:
+        ref = ref + c0[:, :n_out].double()
+    if epi == 3:                                                # |silu'| <= 1.1: the error of either factor times the other
+        gate, up = ref[:, :n_out], ref[:, n_out:]
+        ref = torch.nn.functional.silu(gate) * up
+        tol = 4e-5 * scale * (1 + gate.abs() + up.abs())
+    if epi in (0, 3):
+        tol = tol + 2.0 ** -8 * ref.abs()                       # one bf16 rounding of the result
+    got = c.cpu()
+    assert bool(((got[:, :n_out].double() - ref).abs() <= tol).all())
+    assert torch.equal(got[:, n_out:], c0[:, n_out:])           # nothing beyond the last column
+
+
 def test_gemm_mfma_bf16_padded_strides(rpo):
     _gemm_case(rpo, 70, 90, 128, torch.bfloat16, 1, path=0, pad=8)
     _gemm_case(rpo, 70, 90, 128, torch.bfloat16, 2, path=0, pad=8)
