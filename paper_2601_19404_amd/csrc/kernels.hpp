@@ -34,10 +34,6 @@ __device__ inline void dma_load16_at(const void* sbase, uint32_t voff, uint32_t 
             : "memory", "scc");
 }
 
-__device__ inline void dma_load16_s(const void* sbase, uint32_t voff, uint32_t lds_byte_addr) {
-    dma_load16_at<false>(sbase, voff, lds_byte_addr, 0);
-}
-
 enum DType : int { kF32 = 0, kBF16 = 1 };
 
 inline size_t dtype_size(int dt) { return dt == kF32 ? 4 : 2; }

@@ -21,6 +21,10 @@
 //   11.7 / 13.1 / 15.1; K = 8960, N = 1536 (down, with its reduction) 15.3 / 16.0 / 17.2 -> 12.0 / 13.3 / 14.3;
 //   K = 3584: N = 3584 (O) 12.7 / 13.5 / 14.9 -> 7.6 / 11.0 / 12.8; N = 37888 (gate/up) 61.9 / 63.5 / 68.7 ->
 //   49.8 / 51.3 / 57.4 (5.5 TB/s of weights at 8 rows).
+// Weights asked for with the non-temporal hint, and no bank conflicts left in the fragment reads (42 % of the LDS cycles
+// before), the same shapes, 8 / 30 / 64 rows: QKV 4.4 / 5.6 / 7.0 -> 3.8 / 4.9 / 6.4, gate/up 12.4 / 13.8 / 15.9 -> 11.0 / 12.7 /
+// 14.9, down 11.9 / 12.9 / 14.5 -> 10.9 / 12.1 / 14.4; O (K = 3584) 7.7 / 9.9 / 13.2 -> 6.9 / 9.2 / 12.4; gate/up (N = 37888) 48.2 /
+// 51.6 / 57.7 -> 42.7 / 46.9 / 54.6 (6.4 TB/s); LM head (N = 151936, K = 1536) 85.4 / 97.5 / 114 -> 73.0 / 89.8 / 111.
 #include "kernels.hpp"
 
 namespace rpo {
@@ -65,7 +69,7 @@ __device__ inline void wait_loads() {  // all but the newest N loads of this wav
 //   otherwise:  16 (NB blockIdx.x + t) ..
 // kEpiPartial: workgroup (b, z) multiplies K slabs [z slabs_per_split, ...) only and stores fp32 partial sums to
 // Cv[z][M][N] (ldc is not used).
-template <int MA, int NB, int NW, int S, int EPI>
+template <int MA, int NB, int NW, int S, int EPI, bool GROUPS>
 __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __restrict__ A, int64_t lda,
                                                               const bf16* __restrict__ W, int64_t ldw,
                                                               void* __restrict__ Cv, int64_t ldc, int M, int N,
@@ -77,6 +81,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
     constexpr int LD = COLS + 4;      // fp32 row of the partial sums, 16-byte pieces
     constexpr int INST = 2 * NB + MA;  // loads per slab; each fills 1 KiB of LDS (8 rows x 128 bytes)
     constexpr int STAGE = INST * 1024;
+    // One workgroup reads a weight row: 8 / 30 rows of K = 3584, N = 37888 48.1 -> 42.7 / 51.5 -> 46.9 us = 6.4 / 5.8 TB/s.
+    // Not where 64 rows of activations, read by every workgroup, outweigh them (down, K = 8960: 14.5 -> 14.9 us).
+    constexpr bool kOnce = !GROUPS && !(EPI == kEpiPartial && MA == 8);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // rings [NW][S][STAGE], then partial sums
     float* part = (float*)smem;                                          // [NW][ROWS][LD]
 
@@ -86,7 +93,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
     // Row groups of one column block sit next to each other on one XCD (workgroups go to the eight XCDs in turn):
     // the weights come from HBM once and from that XCD's L2 for the other groups.
     int b = blockIdx.x, m0 = 0;
-    if (row_groups > 1) {
+    if constexpr (GROUPS) {
         const int t = b >> 3;
         m0 = t % row_groups * (MA * 8);
         b = (t / row_groups) * 8 + (b & 7);
@@ -95,13 +102,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
     const int F = N / 2;
 
     // Load addressing: an instruction fills 8 rows; lane l stores piece position l % 8 of row l / 8 and fetches
-    // piece (l % 8) ^ swizzle(row), which spreads the fragment reads over the LDS banks.
+    // piece (l % 8) ^ (row % 8), which spreads the fragment reads over the LDS banks (a 16-byte read is served 16 lanes
+    // at a time: 0-3, 12-15, 20-23 and 24-27 together, so two pieces of eight rows each).
     uint32_t off[INST];
 #pragma unroll
     for (int j = 0; j < INST; ++j) {
         const int l8 = lane >> 3;                   // row in the 8-row group
         const int half = j < 2 * NB ? (j & 1) : ((j - 2 * NB) & 1);  // which half of a 16-row block
-        const int piece = (lane & 7) ^ l8 ^ half;
+        const int piece = (lane & 7) ^ l8;
         if (j < 2 * NB) {
             const int t = j >> 1;
             int row;
@@ -138,10 +146,15 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
         const bf16* wb = W + sl * 64;
         const bf16* ab = A + sl * 64;
 #pragma unroll
-        for (int j = 0; j < INST; ++j) dma_load16_s(j < 2 * NB ? wb : ab, off[j], ring + st * STAGE + j * 1024);
+        for (int j = 0; j < INST; ++j) {
+            if (j < 2 * NB)
+                dma_load16_at<kOnce>(wb, off[j], ring + st * STAGE, j * 1024);
+            else
+                dma_load16_at<false>(ab, off[j], ring + st * STAGE, j * 1024);
+        }
     };
-    const int sw = (r & 7) ^ (r >> 3);
-    const int ar = MA == 1 ? (r & 7) : r, asw = MA == 1 ? (r & 7) : sw;
+    const int sw = r & 7;
+    const int ar = MA == 1 ? (r & 7) : r;
     auto multiply = [&](int st) __attribute__((always_inline)) {
         const unsigned char* base = ring_p + st * STAGE;
 #pragma unroll
@@ -152,7 +165,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
                 wf[t] = *(const bf16x8_t*)(base + t * 2048 + r * 128 + (((4 * h + g) ^ sw) << 4));
 #pragma unroll
             for (int m = 0; m < MB; ++m)
-                af[m] = *(const bf16x8_t*)(base + NB * 2048 + m * 2048 + ar * 128 + (((4 * h + g) ^ asw) << 4));
+                af[m] = *(const bf16x8_t*)(base + NB * 2048 + m * 2048 + ar * 128 + (((4 * h + g) ^ sw) << 4));
 #pragma unroll
             for (int m = 0; m < MB; ++m)
 #pragma unroll
@@ -322,22 +335,22 @@ constexpr size_t skinny_lds() {
 }
 
 // PER_CU workgroups share a CU's 160 KiB of LDS; the ring is as deep as that allows, at most four slabs.
-template <int MA, int NB, int NW, int PER_CU, int EPI>
+template <int MA, int NB, int NW, int PER_CU, int EPI, bool GROUPS = false>
 hipError_t launch_one(const GemmArgs& a, int blocks, hipStream_t s, int splits = 1, void* out = nullptr) {
     constexpr int kFit = 160 / PER_CU / (NW * (2 * NB + MA));
     constexpr int S = kFit < 4 ? kFit : 4;
     static_assert(S >= 2, "the ring needs two slabs");
     constexpr size_t lds = skinny_lds<MA, NB, NW, S>();
     static_assert(lds * PER_CU <= 160 * 1024, "LDS");
-    auto kern = gemm_skinny_kernel<MA, NB, NW, S, EPI>;
+    auto kern = gemm_skinny_kernel<MA, NB, NW, S, EPI, GROUPS>;
     static bool attr_set = false;  // one flag per template instance
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const int row_groups = ceil_div(a.M, MA * 8);
-    const int grid = row_groups == 1 ? blocks : ceil_div(blocks, 8) * 8 * row_groups;
+    const int row_groups = GROUPS ? ceil_div(a.M, MA * 8) : 1;
+    const int grid = GROUPS ? ceil_div(blocks, 8) * 8 * row_groups : blocks;
     kern<<<dim3((unsigned)grid, (unsigned)splits), dim3(NW * 64), lds, s>>>(
         (const bf16*)a.A, a.lda, (const bf16*)a.W, a.ldw, out ? out : a.C, a.ldc, a.M, a.N, a.K,
         ceil_div(a.K / 64, splits), blocks, row_groups,
@@ -394,9 +407,9 @@ hipError_t launch_rows(const GemmArgs& a, int splits, hipStream_t s) {
 template <int EPI>
 hipError_t launch_groups(const GemmArgs& a, hipStream_t s) {
     switch (gemm_skinny_groups(a)) {
-        case 1: return launch_one<8, 1, 4, 2, EPI>(a, ceil_div(a.N, 16), s);
-        case 2: return launch_one<8, 2, 4, 1, EPI>(a, ceil_div(a.N, 32), s);
-        case 4: return launch_one<8, 4, 4, 1, EPI>(a, ceil_div(a.N, 64), s);
+        case 1: return launch_one<8, 1, 4, 2, EPI, true>(a, ceil_div(a.N, 16), s);
+        case 2: return launch_one<8, 2, 4, 1, EPI, true>(a, ceil_div(a.N, 32), s);
+        case 4: return launch_one<8, 4, 4, 1, EPI, true>(a, ceil_div(a.N, 64), s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -461,7 +474,7 @@ bool gemm_skinny_takes(const GemmArgs& a, bool tiles_split_k) {
 
 hipError_t gemm_skinny_load_kernels() {
     hipFuncAttributes attr;
-    return hipFuncGetAttributes(&attr, (const void*)gemm_skinny_kernel<1, 1, 8, 4, kEpiStore>);
+    return hipFuncGetAttributes(&attr, (const void*)gemm_skinny_kernel<1, 1, 8, 4, kEpiStore, false>);
 }
 
 hipError_t launch_gemm_skinny(const GemmArgs& a, int epi, int splits, hipStream_t s) {
