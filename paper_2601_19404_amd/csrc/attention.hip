@@ -26,12 +26,28 @@ typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
-// generic kernel
+// generic kernel: one wave per (row, query head), 64 tokens at a time.  Latency-bound, so everything a step needs is
+// asked for at once: a lane reads its token's key in 16-byte pieces (dh a multiple of 8), and the values in the octets of
+// tokens in which a page keeps a channel, the octets dealt to 64 / dh lane groups where a head is narrower than the wave.
+// fp32, dh = 32, ~75 tokens, 8 rows: 25 -> 9 us (element by element before, one token after the other).
 // ---------------------------------------------------------------------------
 template <typename T>
+__device__ inline void load8(const T* p, float (&v)[8]) {  // p a multiple of 16 bytes
+    T t[8];
+    if constexpr (sizeof(T) == 2) {
+        *(u32x4_t*)t = *(const u32x4_t*)p;
+    } else {
+        *(u32x4_t*)t = *(const u32x4_t*)p;
+        *(u32x4_t*)(t + 4) = *(const u32x4_t*)(p + 4);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = to_f32<T>(t[e]);
+}
+
+template <typename T>
 __global__ __launch_bounds__(64) void attn_generic_kernel(AttnArgs a) {
-    __shared__ float qs[256];
-    __shared__ float ps[64];
+    __shared__ __attribute__((aligned(16))) float qs[256];
+    __shared__ __attribute__((aligned(16))) float ps[64];
     const int r = blockIdx.x, hq = blockIdx.y, lane = threadIdx.x;
     if (a.active && !a.active[r]) return;
     const int seq = a.row_seq ? a.row_seq[r] : r;
@@ -39,12 +55,15 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(AttnArgs a) {
     const SeqDesc sd = a.seqs[seq];
     const int ctx = sd.pos0 + (a.single_row ? 0 : r - sd.row_start) + a.pos_add + 1;
     const int kh = hq / (a.Hq / a.Hkv);
-    const int dh = a.dh, pt = a.geom.page_tokens;
+    const int dh = a.dh, pt = a.geom.page_tokens;  // page_tokens: a power of two >= 16
     const T* q = (const T*)a.q + (int64_t)r * a.q_stride + (int64_t)hq * dh;
     for (int d = lane; d < dh; d += 64) qs[d] = to_f32<T>(q[d]);
     __syncthreads();
     const T* pool = (const T*)a.kv_pool;
     const int32_t* table = a.tables + sd.table_off;
+    const int groups = dh <= 16 ? 4 : dh <= 32 ? 2 : 1, span = 64 / groups;
+    const int grp = lane / span, d0 = lane % span;
+    const bool vec = dh % 8 == 0;
     float o[4] = {0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;
     for (int c0 = 0; c0 < ctx; c0 += 64) {
@@ -55,7 +74,16 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(AttnArgs a) {
             page = table[tok / pt];
             const T* kp = pool + a.geom.k_block(a.layer, page, kh) + (int64_t)(tok % pt) * dh;
             float dot = 0.f;
-            for (int d = 0; d < dh; ++d) dot = fmaf(qs[d], to_f32<T>(kp[d]), dot);
+            if (vec) {
+                for (int d = 0; d < dh; d += 8) {
+                    float k8[8];
+                    load8<T>(kp + d, k8);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) dot = fmaf(qs[d + e], k8[e], dot);
+                }
+            } else {
+                for (int d = 0; d < dh; ++d) dot = fmaf(qs[d], to_f32<T>(kp[d]), dot);
+            }
             s = dot * a.scale;
         }
         const float mnew = fmaxf(m, wave_max(s));  // finite: token c0 is always visible
@@ -69,25 +97,37 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(AttnArgs a) {
         const int nt = min(64, ctx - c0);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int d = lane + 64 * i;
+            if (i > 0 && 64 * i >= dh) continue;  // uniform
+            const int d = d0 + 64 * i;
             float acc = o[i] * alpha;
-            for (int t = 0; t < nt; ++t) {
-                const int pg = __shfl(page, t, 64);
-                if (d < dh) {
-                    const int slot = (c0 + t) % pt;
-                    acc = fmaf(ps[t], to_f32<T>(pool[a.geom.v_block(a.layer, pg, kh) + a.geom.v_elem(slot, d)]),
-                               acc);
+            for (int t0 = 0; t0 < nt; t0 += 32 * groups) {  // four octets per lane group at once
+                float v8[4][8];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int t = t0 + 8 * (u * groups + grp);  // an octet lies in one page
+                    const int pg = __shfl(page, t & 63, 64);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v8[u][e] = 0.f;
+                    if (d < dh && t < nt) load8<T>(pool + a.geom.v_block(a.layer, pg, kh) + a.geom.v_elem((c0 + t) % pt, d), v8[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int t = t0 + 8 * (u * groups + grp);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)  // beyond the context a page holds anything
+                        if (t + e < nt) acc = fmaf(ps[(t + e) & 63], v8[u][e], acc);
                 }
             }
             o[i] = acc;
         }
     }
+    for (int x = span; x < 64; x <<= 1) o[0] += __shfl_xor(o[0], x, 64);
     T* out = (T*)a.out + (int64_t)r * a.Hq * dh + (int64_t)hq * dh;
     const float inv = 1.0f / l;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int d = lane + 64 * i;
-        if (d < dh) out[d] = from_f32<T>(o[i] * inv);
+        const int d = d0 + 64 * i;
+        if (d < dh && grp == 0) out[d] = from_f32<T>(o[i] * inv);
     }
 }
 

@@ -93,24 +93,84 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const T* __restrict__
     }
 }
 
-// generic SwiGLU projection: act[m, j] = silu(A W_gate^T)[m, j] * (A W_up^T)[m, j]
-template <typename T>
-__global__ __launch_bounds__(256) void gemm_generic_swiglu_kernel(const T* __restrict__ A, int64_t lda,
-                                                                  const T* __restrict__ W, int64_t ldw,
-                                                                  T* __restrict__ C, int64_t ldc, int M,
-                                                                  int F, int K) {
-    const int j = blockIdx.x * 256 + threadIdx.x, m = blockIdx.y;
-    if (j >= F) return;
-    const T* a = A + (int64_t)m * lda;
-    const T* wg = W + (int64_t)j * ldw;
-    const T* wu = W + (int64_t)(F + j) * ldw;
-    float g = 0.f, u = 0.f;
-    for (int k = 0; k < K; ++k) {
-        const float av = to_f32<T>(a[k]);
-        g = fmaf(av, to_f32<T>(wg[k]), g);
-        u = fmaf(av, to_f32<T>(wu[k]), u);
+// The same for problems too small to fill the chip with 64x64 tiles, and every generic SwiGLU projection: a wave owns
+// eight rows and four weight rows, its lanes share K (lane l takes k = l, l + 64, ...: whole lines whatever the alignment),
+// and the 32 sums meet by exchanges that halve what a lane holds (32 in all), after which lane l has sum l / 2.  Latency is
+// all that a few rows cost: the tile kernel waits for a load and two barriers every 16 values of K, this one asks for 4
+// x 64 values of K at a time.  us, fp32, before -> now: 8 x 256 x 128 12.8 -> 3.2, 8 x 128 x 256 (accumulating) 25.3 -> 4.0,
+// 64 x 1024 x 1024 103 -> 8.6; SwiGLU (before: a thread walking both weight rows, 64 lines a load) F = 256, K = 128, 8 rows
+// 29.2 -> 3.5, 500 rows 106 -> 8.0.
+// EPI kEpiSwiglu: N = 2F, the four weight rows are two gate rows and the two up rows that belong to them.
+constexpr int kWaveM = 8, kWaveN = 4;
+template <typename T, int EPI>
+__global__ __launch_bounds__(256) void gemm_generic_wave_kernel(const T* __restrict__ A, int64_t lda,
+                                                                const T* __restrict__ W, int64_t ldw,
+                                                                void* __restrict__ Cv, int64_t ldc, int M, int N,
+                                                                int K) {
+    constexpr bool kPairs = EPI == kEpiSwiglu;
+    const int F = kPairs ? N / 2 : N;                  // columns of C
+    constexpr int kCols = kPairs ? kWaveN / 2 : kWaveN;
+    const int lane = threadIdx.x & 63;
+    const int n0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kCols;
+    if (n0 >= F) return;
+    for (int m0 = blockIdx.y * kWaveM; m0 < M; m0 += gridDim.y * kWaveM) {
+        const T* ap[kWaveM];
+        const T* wp[kWaveN];
+#pragma unroll
+        for (int r = 0; r < kWaveM; ++r) ap[r] = A + (int64_t)min(m0 + r, M - 1) * lda;
+#pragma unroll
+        for (int c = 0; c < kWaveN; ++c)
+            wp[c] = W + (int64_t)(min(n0 + c % kCols, F - 1) + (c / kCols) * F) * ldw;
+        float v[kWaveM * kWaveN] = {};
+        constexpr int U = 4;
+        for (int k0 = 0; k0 < K; k0 += 64 * U) {
+            float a[U][kWaveM], w[U][kWaveN];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + u * 64 + lane;
+                if (k0 + u * 64 >= K) continue;  // uniform
+                const bool on = k < K;
+                const int kk = on ? k : K - 1;
+#pragma unroll
+                for (int r = 0; r < kWaveM; ++r) a[u][r] = on ? to_f32<T>(ap[r][kk]) : 0.f;
+#pragma unroll
+                for (int c = 0; c < kWaveN; ++c) w[u][c] = on ? to_f32<T>(wp[c][kk]) : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (k0 + u * 64 >= K) continue;
+#pragma unroll
+                for (int r = 0; r < kWaveM; ++r)
+#pragma unroll
+                    for (int c = 0; c < kWaveN; ++c) v[r * kWaveN + c] = fmaf(a[u][r], w[u][c], v[r * kWaveN + c]);
+            }
+        }
+        auto halve = [&](auto hh) __attribute__((always_inline)) {
+            constexpr int half = decltype(hh)::value;
+            const bool up = (lane & 2 * half) != 0;
+#pragma unroll
+            for (int i = 0; i < half; ++i) {
+                const float keep = up ? v[i + half] : v[i], send = up ? v[i] : v[i + half];
+                v[i] = keep + __shfl_xor(send, 2 * half, 64);
+            }
+        };
+        halve(std::integral_constant<int, 16>{});
+        halve(std::integral_constant<int, 8>{});
+        halve(std::integral_constant<int, 4>{});
+        halve(std::integral_constant<int, 2>{});
+        halve(std::integral_constant<int, 1>{});
+        float sum = v[0] + __shfl_xor(v[0], 1, 64);  // of row l / 8, weight row (l / 2) % 4
+        const int m = m0 + (lane >> 3), c = (lane >> 1) & 3;
+        if constexpr (kPairs) sum = sum / (1.0f + expf(-sum)) * __shfl_xor(sum, 2 * kCols, 64);  // of the gate lanes
+        if ((lane & 1) || c >= kCols || m >= M || n0 + c >= F) continue;
+        const int64_t o = (int64_t)m * ldc + n0 + c;
+        if (EPI == kEpiStore || kPairs)
+            ((T*)Cv)[o] = from_f32<T>(sum);
+        else if (EPI == kEpiStoreF32)
+            ((float*)Cv)[o] = sum;
+        else
+            ((float*)Cv)[o] += sum;
     }
-    C[(int64_t)m * ldc + j] = from_f32<T>(g / (1.0f + expf(-g)) * u);
 }
 
 // Epilogue shared by the MFMA kernels: lane l holds column (l % 32) and rows
@@ -1679,30 +1739,34 @@ hipError_t launch_tile(const GemmArgs& a, int splits, hipStream_t s) {
     }
 }
 
+constexpr int kGenericTiles = 256;
+template <typename T, int EPI>
+void launch_generic_epi(const GemmArgs& a, hipStream_t s) {
+    const T* A = (const T*)a.A;
+    const T* W = (const T*)a.W;
+    // A wave reads 12 values for 32 products, a 64x64 tile 2 for 64: far beyond a chip of tiles those are the faster ones
+    // (us, tiles / waves: 500 x 2048 x 1024 107 / 69, 1000 x 1024 x 1024, both 256 tiles, 127 / 69; 2000 x 2048 x 512, 1024
+    // tiles: 94 with tiles, twice those 69 by the rate of the waves).
+    if (EPI == kEpiSwiglu || ceil_div(a.N, 64) * ceil_div(a.M, 64) <= kGenericTiles) {
+        const int cols = EPI == kEpiSwiglu ? a.N / 2 : a.N, per_wg = 4 * (EPI == kEpiSwiglu ? kWaveN / 2 : kWaveN);
+        const int row_blocks = ceil_div(a.M, kWaveM);
+        gemm_generic_wave_kernel<T, EPI><<<dim3(ceil_div(cols, per_wg), row_blocks < 65535 ? row_blocks : 65535), 256, 0, s>>>(
+            A, a.lda, W, a.ldw, a.C, a.ldc, a.M, a.N, a.K);
+        return;
+    }
+    if constexpr (EPI != kEpiSwiglu)
+        gemm_generic_kernel<T, EPI><<<dim3(ceil_div(a.N, 64), ceil_div(a.M, 64)), 256, 0, s>>>(A, a.lda, W, a.ldw, a.C, a.ldc,
+                                                                                              a.M, a.N, a.K);
+}
+
 template <typename T>
 hipError_t launch_generic(const GemmArgs& a, hipStream_t s) {
-    if (a.epilogue == kEpiSwiglu) {
-        const int F = a.N / 2;
-        gemm_generic_swiglu_kernel<T><<<dim3(ceil_div(F, 256), a.M), 256, 0, s>>>(
-            (const T*)a.A, a.lda, (const T*)a.W, a.ldw, (T*)a.C, a.ldc, a.M, F, a.K);
-        return hipGetLastError();
-    }
-    const dim3 grid(ceil_div(a.N, 64), ceil_div(a.M, 64));
     switch (a.epilogue) {
-        case kEpiStore:
-            gemm_generic_kernel<T, kEpiStore><<<grid, 256, 0, s>>>((const T*)a.A, a.lda, (const T*)a.W,
-                                                                   a.ldw, a.C, a.ldc, a.M, a.N, a.K);
-            break;
-        case kEpiStoreF32:
-            gemm_generic_kernel<T, kEpiStoreF32><<<grid, 256, 0, s>>>(
-                (const T*)a.A, a.lda, (const T*)a.W, a.ldw, a.C, a.ldc, a.M, a.N, a.K);
-            break;
-        case kEpiAddF32:
-            gemm_generic_kernel<T, kEpiAddF32><<<grid, 256, 0, s>>>((const T*)a.A, a.lda, (const T*)a.W,
-                                                                    a.ldw, a.C, a.ldc, a.M, a.N, a.K);
-            break;
-        default:
-            return hipErrorInvalidValue;
+        case kEpiStore: launch_generic_epi<T, kEpiStore>(a, s); break;
+        case kEpiStoreF32: launch_generic_epi<T, kEpiStoreF32>(a, s); break;
+        case kEpiAddF32: launch_generic_epi<T, kEpiAddF32>(a, s); break;
+        case kEpiSwiglu: launch_generic_epi<T, kEpiSwiglu>(a, s); break;
+        default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

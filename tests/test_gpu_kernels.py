@@ -242,6 +242,25 @@ def test_gemm_generic(rpo, shape, dtype, epi):
         _gemm_case(rpo, *shape, dtype, epi, path=0)       # fp32 always takes the generic kernel
 
 
+@pytest.mark.parametrize("epi", [0, 1, 2, 3])
+@pytest.mark.parametrize("M,N,K", [(1, 2, 1), (8, 20, 600), (9, 14, 64), (70, 66, 65), (33, 258, 257), (1030, 1040, 70)])
+def test_gemm_generic_waves_and_tiles(rpo, M, N, K, epi):
+    """fp32: eight rows and four weight rows per wave (their edges, K around the 64 lanes and the 256 values asked for
+    at once), 64x64 tiles where there are more than 256 of them (the last shape; SwiGLU stays with the waves)."""
+    if epi < 3:
+        return _gemm_case(rpo, M, N, K, torch.float32, epi, path=0)
+    g = torch.Generator().manual_seed(M + N)
+    a, w = torch.randn(M, K, generator=g), torch.randn(N, K, generator=g) * 0.1
+    c = torch.zeros(M, N // 2, device="cuda")
+    rpo.rpo_set_kernel_path(0)
+    rpo.rpo_gemm_nt(a.cuda(), w.cuda(), c, 3, None)
+    gu = a.double() @ w.double().t()
+    gate, up = gu[:, :N // 2], gu[:, N // 2:]
+    err = (c.cpu().double() - torch.nn.functional.silu(gate) * up).abs()
+    # 2e-5 sqrt(K) 0.1 on either factor (|silu'| <= 1.1), a few fp32 roundings of the product
+    assert bool((err <= 4e-6 * K ** 0.5 * (1 + gate.abs() + up.abs()) + 1e-6 * (gate * up).abs()).all())
+
+
 def test_gemm_rejects_bad_arguments(rpo):
     a = torch.zeros(4, 8, device="cuda")
     with pytest.raises(ValueError):
@@ -537,6 +556,15 @@ def test_attn_decode_alone_small(rpo):
     mcfg = synth.ModelCfg("attn-1layer", 1, 768, 6, 1, 128, 256, 512, "bf16")
     _attn_decode_case(rpo, mcfg, prefix_lens=(300, 257, 640, 64, 130, 20), G=8, n_fill=70,
                       suffix_views=(0, 1, 37, 70), check_groups=(0, 2, 3, 5), seed=61)
+
+
+@pytest.mark.parametrize("head_dim", [2, 10, 16, 24, 32, 48, 64, 80, 200, 256])
+def test_attn_generic_head_dims(rpo, head_dim):
+    """The vector-ALU attention: four, two and one group of lanes, up to four channels a lane, heads that are and are
+    not read in 16-byte pieces; contexts that end inside and at the end of an octet and of 64 tokens."""
+    mcfg = synth.ModelCfg("attn-generic", 1, 64, 4, 2, head_dim, 64, 256, "bf16")
+    _attn_decode_case(rpo, mcfg, prefix_lens=(130, 64, 5), G=2, n_fill=3, suffix_views=(1, 3), check_groups=(0, 1, 2),
+                      seed=70 + head_dim)
 
 
 @pytest.mark.parametrize("prefix_lens", [(2100, 1200, 70), (1310, 700), (1180,)])
