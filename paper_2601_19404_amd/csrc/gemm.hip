@@ -776,61 +776,75 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const bf16* __res
         // accumulators go to LDS as fp32 [BM][BN + 1]; the rotation pairs (i, i + 64) of a row
         // then sit in one place whatever wave produced them.  q is rotated and stored to C, k is
         // rotated and stored to its page slot, v is stored transposed into its page.
-        static_assert(EPI != kEpiRope || (BN == 128 && WM == 1 && (BM == 32 || BM == 64) && NW == 4), "one head per tile");
+        static_assert(EPI != kEpiRope || (BN == 128 && BM <= 128 && BM % 4 == 0 && NW == 4), "one head per tile");
         constexpr int LD = BN + 1;
         float* tile = (float*)smem_raw;
         int* row_pos = (int*)(tile + BM * LD);   // position, or -1: row beyond M / not active
-        int64_t* row_page = (int64_t*)(row_pos + BM + (BM & 1));
+        // where the row's key and value start in the pool (head 0): the divisions by the page size are done once a row
+        int64_t* row_k = (int64_t*)(row_pos + BM + (BM & 1));
+        int64_t* row_v = row_k + BM;
         __syncthreads();  // every wave's tail loads have landed; the stages can be overwritten
         {
-            const int col = wn * TN + (lane & 31), row_in = (lane >> 5) * 4;
+            const int col = wn * TN + (lane & 31), row_in = wm * TM + (lane >> 5) * 4;
 #pragma unroll
             for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    tile[(i * 32 + 8 * (e >> 2) + row_in + (e & 3)) * LD + col] = acc[i][0][e];
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        tile[(i * 32 + 8 * (e >> 2) + row_in + (e & 3)) * LD + col + j * 32] = acc[i][j][e];
         }
         if (tid < BM) {
             const int r = m0 + tid;
             int pos = -1;
-            int64_t page = 0;
             const int seq = r < M ? (rk.row_seq ? rk.row_seq[r] : r) : -1;
             if (seq >= 0 && !(rk.active && !rk.active[r])) {
                 const SeqDesc sd = rk.seqs[seq];
                 pos = sd.pos0 + (rk.single_row ? 0 : r - sd.row_start) + rk.pos_add;
-                page = rk.tables[sd.table_off + pos / rk.geom.page_tokens];
+                const int pt = rk.geom.page_tokens;
+                const int64_t page = rk.tables[sd.table_off + pos / pt];
+                row_k[tid] = rk.geom.k_block(rk.layer, page, 0) + (int64_t)(pos % pt) * BN;
+                row_v[tid] = rk.geom.v_block(rk.layer, page, 0) + rk.geom.v_elem(pos % pt, 0);
             }
             row_pos[tid] = pos;
-            row_page[tid] = page;
         }
         __syncthreads();
         const int head = n0 / BN;
-        const int pt = rk.geom.page_tokens;
+        const int64_t head_block = rk.geom.head_block();
         bf16* pool = (bf16*)rk.kv_pool;
         if (head < rk.Hq + rk.Hkv) {
+            // The factors of up to eight rows are asked for before the first is used (one row after the other, every
+            // row waits for its own: QKV of 1350 rows, N = 2048, K = 1536 on 128-row tiles 35 us, now 26).
             const int i = tid & 63;
+            constexpr int U = BM / 4 < 8 ? BM / 4 : 8;
+#pragma unroll 1
+            for (int it = 0; it < BM / 4; it += U) {
+                float2 cs[U];
 #pragma unroll
-            for (int it = 0; it < BM / 4; ++it) {
-                const int row = it * 4 + (tid >> 6);
-                const int gm = m0 + row;
-                if (gm >= M) continue;
-                const int pos = row_pos[row];
-                const float x1 = tile[row * LD + i], x2 = tile[row * LD + i + 64];
-                bf16* dst;
-                float y1 = x1, y2 = x2;
-                if (pos >= 0) {
-                    const float2 cs = *(const float2*)(rk.rope + ((int64_t)pos * 64 + i) * 2);
-                    y1 = x1 * cs.x - x2 * cs.y;
-                    y2 = x2 * cs.x + x1 * cs.y;
+                for (int u = 0; u < U; ++u)
+                    cs[u] = *(const float2*)(rk.rope + ((int64_t)max(row_pos[(it + u) * 4 + (tid >> 6)], 0) * 64 + i) * 2);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int row = (it + u) * 4 + (tid >> 6);
+                    const int gm = m0 + row;
+                    if (gm >= M) continue;
+                    const int pos = row_pos[row];
+                    const float x1 = tile[row * LD + i], x2 = tile[row * LD + i + 64];
+                    bf16* dst;
+                    float y1 = x1, y2 = x2;
+                    if (pos >= 0) {
+                        y1 = x1 * cs[u].x - x2 * cs[u].y;
+                        y2 = x2 * cs[u].x + x1 * cs[u].y;
+                    }
+                    if (head < rk.Hq) {
+                        dst = (bf16*)Cv + (int64_t)gm * ldc + n0;  // a finished rollout keeps an unrotated q
+                    } else {
+                        if (pos < 0) continue;
+                        dst = pool + row_k[row] + (head - rk.Hq) * head_block;
+                    }
+                    dst[i] = f32_to_bf16(y1);
+                    dst[i + 64] = f32_to_bf16(y2);
                 }
-                if (head < rk.Hq) {
-                    dst = (bf16*)Cv + (int64_t)gm * ldc + n0;  // a finished rollout keeps an unrotated q
-                } else {
-                    if (pos < 0) continue;
-                    dst = pool + rk.geom.k_block(rk.layer, row_page[row], head - rk.Hq) + (int64_t)(pos % pt) * BN;
-                }
-                dst[i] = f32_to_bf16(y1);
-                dst[i + 64] = f32_to_bf16(y2);
             }
         } else {
             // a wave writes 64 consecutive channels of one row: 2-byte pieces 16 bytes apart (8 lines)
@@ -838,10 +852,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const bf16* __res
 #pragma unroll
             for (int it = 0; it < BM / 2; ++it) {
                 const int row = it * 2 + (tid >> 7);
-                const int pos = row_pos[row];
-                if (pos < 0) continue;
-                pool[rk.geom.v_block(rk.layer, row_page[row], head - rk.Hq - rk.Hkv) + rk.geom.v_elem(pos % pt, d)] =
-                    f32_to_bf16(tile[row * LD + d]);
+                if (row_pos[row] < 0) continue;
+                pool[row_v[row] + (head - rk.Hq - rk.Hkv) * head_block + 8 * d] = f32_to_bf16(tile[row * LD + d]);
             }
         }
     } else {
@@ -1460,6 +1472,14 @@ bool dma2_ok(const GemmArgs& a, int splits, int stages = 2) {
 
 int pick_splits(const GemmArgs& a, const TileCfg& t);
 
+// Workgroups run in rounds of one per CU.  A 256x192 tile costs about 0.78 of a 256x256 one; it wins when the wider tile
+// would leave much of its last round idle (narrow N).
+TileCfg wide_tile(const GemmArgs& a) {
+    const int t256 = ceil_div(a.M, 256) * ceil_div(a.N, 256), t192 = ceil_div(a.M, 256) * ceil_div(a.N, 192);
+    if (ceil_div(t192, 256) * 0.78 < ceil_div(t256, 256) * 0.97) return TileCfg{kKidGemm256x192, 256, 192};
+    return TileCfg{kKidGemm256, 256, 256};
+}
+
 TileCfg pick_tile(const GemmArgs& a) {
     if (a.path >= 16) {  // tuning aid: a fixed tile shape
         switch (a.path - 16) {
@@ -1511,13 +1531,27 @@ TileCfg pick_tile(const GemmArgs& a) {
     }
     // up to 128 rows a 256-row tile multiplies mostly padding
     if (a.epilogue == kEpiSwiglu && a.M > 64 && a.M <= 128 && t256 >= 128) return TileCfg{kKidGemm128, 128, 128};
-    if (a.M > 512 || (a.M > 64 && t256 >= 128)) {
-        // Workgroups run in rounds of one per CU.  A 256x192 tile costs about 0.78 of a 256x256
-        // one; it wins when the wider tile would leave much of its last round idle (narrow N).
-        if (a.epilogue != kEpiSwiglu && a.M > 512) {
-            const int t192 = ceil_div(a.M, 256) * ceil_div(a.N, 192);
-            if (ceil_div(t192, 256) * 0.78 < ceil_div(t256, 256) * 0.97) return TileCfg{kKidGemm256x192, 256, 192};
+    // QKV, O and down of chunks of up to a few thousand rows: 256-row tiles leave most CUs idle there, and a K split of few
+    // tiles pays for its partial sums and a reduction.  64x64 tiles while two workgroups per CU hold them all, else
+    // 128x128 tiles while those do; a deep K stays with 256x192 tiles where their K splits come out at one workgroup per
+    // CU.  us, 256x192 tiles (split) -> now: N = 2048, K = 1536: 700 rows 29.3 -> 12.5, 1300 rows 30.1 -> 18.4, 2500 rows 53 -> 27;
+    // N = K = 1536 (accumulating): 1060 rows 30.9 -> 15.5, 2500 rows 39.5 -> 24.5; N = 1536, K = 8960: 700 rows 55.9 -> 39.5, 2500
+    // rows 105 -> 84 (900 rows 45.0 stays: 47.3; 1536 rows 82.7 -> 86.1); N = 4608, K = 3584: 700 rows 64.6 -> 37.2, 1536 rows 69.8
+    // -> 59 (1800 rows 69 stays: 540 tiles, 90); N = 3584, K = 18944: 700 rows 165 -> 154, 2100 rows 331 -> 281.
+    if (a.M > 512 && (a.epilogue == kEpiStore || a.epilogue == kEpiAddF32) && a.K % kBK == 0 && a.path != 2) {
+        const TileCfg wide = wide_tile(a);
+        const int64_t t64 = (int64_t)ceil_div(a.M, 64) * ceil_div(a.N, 64), t128 = (int64_t)ceil_div(a.M, 128) * ceil_div(a.N, 128);
+        const int splits = pick_splits(a, wide), fit = ceil_div(a.M, wide.bm) * ceil_div(a.N, wide.bn) * splits;
+        // A QKV projection rotates the fp32 sums where it fits a round of one-head tiles, and where the split's reduction
+        // did (the separate rotary kernel rounds them to bf16 first).
+        if (a.rope && rope_direct(a) && (t128 <= 256 || splits > 1)) return TileCfg{kKidGemm32, 32, 128};
+        if (!a.rope || splits == 1) {
+            if (a.K <= 4096 && t64 <= 512) return TileCfg{kKidGemm64x64, 64, 64};
+            if (t128 <= 512 && !(a.K > 4096 && fit >= 250 && fit <= 256)) return TileCfg{kKidGemm128, 128, 128};
         }
+    }
+    if (a.M > 512 || (a.M > 64 && t256 >= 128)) {
+        if (a.epilogue != kEpiSwiglu && a.M > 512 && wide_tile(a).id == kKidGemm256x192) return wide_tile(a);
         // The same for gate/up: a round of 256x192 tiles costs about 0.86 and one of 256x160 tiles 0.76 of a round of
         // 256x256 (measured up to four of those; beyond, the last round weighs little).  us, 256x256 -> chosen: N = 17920,
         // K = 1536: 1000 rows 80.6 -> 65.5 (160), 1280 rows 86 -> 76 (192), 1400 rows 87 stays (95 and 103), 2048 rows 127
@@ -1639,8 +1673,8 @@ hipError_t launch_one(const GemmArgs& a, int splits, void* out, hipStream_t s) {
         }
     } else if (dma) {
         size_t lds = (size_t)DST * (BM + BN) * DBK * sizeof(bf16);
-        if (EPI == kEpiRope) {  // fp32 tile [BM][BN + 1] + per-row position and page
-            const size_t need = (size_t)BM * (BN + 1) * 4 + (size_t)(BM + (BM & 1)) * 4 + (size_t)BM * 8;
+        if (EPI == kEpiRope) {  // fp32 tile [BM][BN + 1] + per-row position and places of its key and value
+            const size_t need = (size_t)BM * (BN + 1) * 4 + (size_t)(BM + (BM & 1)) * 4 + (size_t)BM * 16;
             lds = lds > need ? lds : need;
         }
         auto kern = gemm_dma_kernel<BM, BN, WM, WN, EPI, SWIGLU, DBK, DST>;
@@ -1819,7 +1853,8 @@ static hipError_t launch_gemm_only(const GemmArgs& a, int splits, const TileCfg&
             return launch_tile<128, 128, 2, 2>(a, splits, s);
         case kKidGemm32:
             if (rope_direct(a)) {
-                // one round of workgroups: 64-row tiles once the 32-row ones outnumber the CUs
+                // one round of workgroups: 64-row tiles once the 32-row ones outnumber the CUs, then 128-row ones
+                if (ceil_div(a.M, 64) * (a.N / 128) > 256) return launch_one<128, 128, 2, 2, kEpiRope, 0, 4>(a, 1, a.C, s);
                 if (ceil_div(a.M, 32) * (a.N / 128) > 256) return launch_one<64, 128, 1, 4, kEpiRope, 0, 4>(a, 1, a.C, s);
                 return launch_one<32, 128, 1, 4, kEpiRope, 0, 4>(a, 1, a.C, s);
             }

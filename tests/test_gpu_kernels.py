@@ -558,6 +558,28 @@ def test_attn_decode_alone_small(rpo):
                       suffix_views=(0, 1, 37, 70), check_groups=(0, 2, 3, 5), seed=61)
 
 
+@pytest.mark.parametrize("prefix_lens", [(300, 230), (600, 430), (1100, 950)])
+def test_prefill_rotary_tiles(rpo, prefix_lens):
+    """QKV projection of a prefill chunk on one-head tiles of 64 and 128 rows (the last rows of a tile missing, tiles
+    across two sequences): keys and values through the attention over them, queries through the prefix logits."""
+    mcfg = synth.ModelCfg("rotary-prefill", 1, 256, 12, 2, 128, 256, 512, "bf16")
+    _attn_decode_case(rpo, mcfg, prefix_lens=prefix_lens, G=2, n_fill=1, suffix_views=(0,), check_groups=(0, 1), seed=81)
+    rng = np.random.default_rng(82)
+    w = synth.perturb_gains(synth.make_weights(mcfg, seed=82))
+    model = rpo.rpo_model_create(mcfg, util.to_device(w))
+    batch = rpo.rpo_batch_create(model, 2, 1, max(prefix_lens), 1, 64, sum(prefix_lens))
+    prefixes = [rng.integers(0, mcfg.vocab, size=n).astype(np.int32) for n in prefix_lens]
+    last = torch.empty(2, mcfg.vocab, device="cuda")
+    rpo.rpo_prefill_prefix(batch, torch.from_numpy(np.concatenate(prefixes)).cuda(),
+                           np.concatenate([[0], np.cumsum(prefix_lens)]).astype(np.int32), last)
+    got = last.cpu().numpy()
+    for g in range(2):
+        _, ref = T.prefill(util.oracle_shape(mcfg, storage="bf16"), synth.weights_to_numpy(w), prefixes[g])
+        ref = np.asarray(ref).reshape(-1, mcfg.vocab)[-1]
+        # a single layer with the same bf16 roundings: six ulps of the logit scale at most
+        assert np.abs(got[g] - ref).max() <= 6 * 2.0 ** -8 * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("head_dim", [2, 10, 16, 24, 32, 48, 64, 80, 200, 256])
 def test_attn_generic_head_dims(rpo, head_dim):
     """The vector-ALU attention: four, two and one group of lanes, up to four channels a lane, heads that are and are
