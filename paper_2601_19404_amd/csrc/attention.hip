@@ -153,8 +153,9 @@ constexpr int kPt = 64;       // tokens per page
 // V^T tile [128 channels][64 tokens]: inside a row the tokens are reordered so that the eight tokens a
 // lane group multiplies in one k-step of the second product (32 kk + 4 g + i and 32 kk + 16 + 4 g + i,
 // i < 4: the token order its probabilities leave the first product in) are one 16-byte piece, piece
-// 4 kk + g; piece p of row r sits at p ^ (r & 7) ^ ((r >> 3) & 1), which spreads the 16-byte reads of
-// sixteen consecutive rows (same piece) over the banks.
+// 4 kk + g; piece p of row r sits at p ^ (r & 7), which spreads the 16-byte reads over the banks: the LDS serves them
+// 16 lanes at a time, lanes 0-3, 12-15, 20-23 and 24-27 together, i.e. one piece of eight rows and its neighbour of the other
+// eight.
 constexpr int kKRow = kDh;  // LDS row of the K tile  [64][128]
 constexpr int kVRow = kPt;  // LDS row of the V^T tile [128][64]
 constexpr int kKTile = kPt * kKRow;
@@ -247,7 +248,7 @@ __device__ inline void attn_stream_pages(const bf16* const (&qptr)[NC], const in
             // channel; tokens 8 m .. + 3 are half (m / 2) % 2 of piece 4 (m / 4) + (2 m) % 4, tokens 8 m + 4 .. + 7
             // the same half of the piece after it
             const int vr = c & (kDh - 1), m = c >> 7;
-            const int sw = (vr & 7) ^ ((vr >> 3) & 1);
+            const int sw = vr & 7;
             const int pl = 4 * (m >> 2) + ((2 * m) & 3);
             bf16* vrow = Vs + buf * kVTile + vr * kVRow + 4 * ((m >> 1) & 1);
             *(u32x2_t*)(vrow + ((pl ^ sw) << 3)) = u32x2_t{rv[i].x, rv[i].y};
@@ -333,7 +334,7 @@ __device__ inline void attn_stream_pages(const bf16* const (&qptr)[NC], const in
 #pragma unroll
                 for (int mb2 = 0; mb2 < 8; ++mb2) {
                     const bf16x8_t av = *(const bf16x8_t*)(vs + (mb2 * 16 + c16) * kVRow +
-                                                           (((4 * kk2 + g) ^ (c16 & 7) ^ (c16 >> 3)) << 3));
+                                                           (((4 * kk2 + g) ^ (c16 & 7)) << 3));
 #pragma unroll
                     for (int c = 0; c < NC; ++c)
                         st.ot[c][mb2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bp[c][kk2], st.ot[c][mb2], 0, 0, 0);

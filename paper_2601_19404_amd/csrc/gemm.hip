@@ -1879,8 +1879,43 @@ static hipError_t launch_gemm_only(const GemmArgs& a, int splits, const TileCfg&
     }
 }
 
+// Rows of an accumulating projection that whole rounds of 256x256 tiles take, 0: all of them in one launch.  What is
+// left of the last round would cost a whole one; the remaining rows go to a launch of their own, on 128x128 tiles,
+// which take about 0.42 of a round where one per CU holds them and 0.68 where two do, and some 10 us of launch.  A round
+// is about 1.45 us a slab.  us, one launch -> two: 15360 x 3584 x 18944 (840 tiles, 3.3 rounds) 1925 -> 1732, K = 3584
+// 410 -> 405.
+static int whole_round_rows(const GemmArgs& a) {
+    if (a.epilogue != kEpiAddF32 || a.path != 0 || a.M <= 2048 || a.K % kBK != 0 || !dma2_ok(a, 1) || pick_splits(a, wide_tile(a)) != 1)
+        return 0;
+    const int gn = ceil_div(a.N, 256), t256 = ceil_div(a.M, 256) * gn, rounds = t256 / 256;
+    const int rows = rounds * 256 / gn * 256;
+    if (rounds < 1 || rows <= 0 || rows >= a.M) return 0;
+    const int64_t t128 = (int64_t)ceil_div(a.M - rows, 128) * ceil_div(a.N, 128);
+    if (t128 > 512) return 0;
+    const double split = rounds + (t128 <= 256 ? 0.42 : 0.68) + 10. / (1.45 * (a.K / kBK));
+    const double c256 = ceil_div(t256, 256), c192 = ceil_div(ceil_div(a.M, 256) * ceil_div(a.N, 192), 256) * 0.78;
+    return split < 0.97 * (c256 < c192 ? c256 : c192) ? rows : 0;
+}
+
+static hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s);
+
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
+    const int rows = mfma_ok(a) ? whole_round_rows(a) : 0;
+    if (rows == 0) return launch_gemm_rows(a, s);
+    GemmArgs head = a, tail = a;
+    head.M = rows;
+    head.norm_out = tail.norm_out = nullptr;
+    tail.M = a.M - rows;
+    tail.A = (const bf16*)a.A + (int64_t)rows * a.lda;
+    tail.C = (float*)a.C + (int64_t)rows * a.ldc;
+    hipError_t e = launch_gemm_rows(head, s);
+    if (e == hipSuccess) e = launch_gemm_rows(tail, s);
+    if (e != hipSuccess || !a.norm_out) return e;
+    return launch_rmsnorm((const float*)a.C, nullptr, a.norm_gain, a.dtype, a.N, a.norm_eps, a.norm_out, a.M, s);
+}
+
+static hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
     const bool want_norm = a.norm_out != nullptr && a.epilogue == kEpiAddF32;
     hipError_t e;
     bool norm_done = false, rope_done = false;

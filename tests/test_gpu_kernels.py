@@ -580,6 +580,42 @@ def test_prefill_rotary_tiles(rpo, prefix_lens):
         assert np.abs(got[g] - ref).max() <= 6 * 2.0 ** -8 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("M,N,K", [(4609, 3584, 5120), (5000, 3584, 6144), (11000, 1536, 8960), (11264, 1540, 8960)])
+def test_gemm_whole_rounds_and_the_rest(rpo, M, N, K):
+    """Accumulating projections whose last round of 256x256 tiles is mostly empty: the remaining rows (one, a few, more
+    than a tile) in a launch of their own, at the right place of A and C."""
+    g = torch.Generator(device="cuda").manual_seed(M)
+    a = torch.randn(M, K + 8, generator=g, device="cuda").bfloat16()[:, :K]
+    w = (torch.randn(N, K, generator=g, device="cuda") * 0.1).bfloat16()
+    c0 = torch.randn(M, N + 4, generator=g, device="cuda")
+    c = c0.clone()
+    rpo.rpo_set_kernel_path(0)
+    rpo.rpo_gemm_nt(a, w, c[:, :N], 2, torch.empty(96 << 20, dtype=torch.uint8, device="cuda"))
+    ref = a.double() @ w.double().t()
+    assert bool(((c[:, :N].double() - c0[:, :N].double() - ref).abs() <= 2e-6 * ref.abs() + 2e-5 * K ** 0.5 * 0.1).all())
+    assert torch.equal(c[:, N:], c0[:, N:])
+
+
+def test_prefill_chunk_of_whole_rounds_and_the_rest(rpo):
+    """The same inside a model, where the norm of all rows follows: a prefill in one chunk (4750 rows: the down
+    projection in two launches) against chunks of one sequence, which are too small for it."""
+    mcfg = synth.ModelCfg("whole-rounds", 2, 3584, 28, 4, 128, 5120, 512, "bf16")
+    lens = [1190, 1187, 1180, 1193]
+    rng = np.random.default_rng(5)
+    w = synth.perturb_gains(synth.make_weights(mcfg, seed=5, device="cuda"))
+    model = rpo.rpo_model_create(mcfg, w)
+    toks = torch.from_numpy(rng.integers(0, mcfg.vocab, size=sum(lens)).astype(np.int32)).cuda()
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    out = []
+    for max_rows in (sum(lens), 1200):
+        batch = rpo.rpo_batch_create(model, len(lens), 1, max(lens), 1, 64, max_rows)
+        last = torch.empty(len(lens), mcfg.vocab, device="cuda")
+        rpo.rpo_prefill_prefix(batch, toks, cu, last)
+        out.append(last.cpu())
+    # two bf16 pipelines of two layers: six ulps of the logit scale (measured elsewhere up to 5.5)
+    assert float((out[0] - out[1]).abs().max()) <= 6 * 2.0 ** -8 * float(out[1].abs().max())
+
+
 @pytest.mark.parametrize("head_dim", [2, 10, 16, 24, 32, 48, 64, 80, 200, 256])
 def test_attn_generic_head_dims(rpo, head_dim):
     """The vector-ALU attention: four, two and one group of lanes, up to four channels a lane, heads that are and are
