@@ -1644,7 +1644,7 @@ hipError_t launch_one(const GemmArgs& a, int splits, void* out, hipStream_t s) {
     const bool dma = a.K % kBK == 0 && a.path != 2;
     // The wide two-stage tiles and the decode gate/up ones run on gemm_dma2_kernel (what it does not take goes to the
     // register-staged kernel).
-    constexpr bool kWide = (DST == 2 || SWIGLU == 2) && DBK == 64 && BM >= 128 && EPI != kEpiRope;
+    constexpr bool kWide = (DST == 2 || SWIGLU == 2 || EPI == kEpiLogitsMax) && DBK == 64 && BM >= 128 && EPI != kEpiRope;
     if constexpr (kWide) {
         // The decode gate/up tile leaves room for a third stage in the 160 KiB of LDS: two slabs in flight
         // feed a workgroup that streams its weights from HBM (measured at 512 rows, weights not cached:
@@ -1945,6 +1945,11 @@ static hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
         }
         if (a.block_max && gemm_fuses_max(a) > 0) {
             a.block_max->blocks = gemm_fuses_max(a);
+            // One row of tiles reads every weight row once; up to 128 rows would leave half of a 256-row tile empty.  A
+            // decode step of one layer, us: N = 152064, K = 3584, 72 / 128 rows 375 / 407 -> 288 / 327, 256 rows 497 -> 450; N = 151936,
+            // K = 1536, 72 / 128 rows 203 / 218 -> 163 / 175, 256 rows 261 -> 236.
+            if (a.M <= 128 && dma2_ok(a, 1, 3)) return launch_one<128, 256, 2, 4, kEpiLogitsMax, false, 3, 64, true>(a, 1, a.C, s);
+            if (a.M <= 256) return launch_one<256, 256, 2, 4, kEpiLogitsMax, false, 2, 64, true>(a, 1, a.C, s);
             return launch_one<256, 256, 2, 4, kEpiLogitsMax, false>(a, 1, a.C, s);
         }
         e = launch_gemm_only(a, splits, t, s);

@@ -616,6 +616,33 @@ def test_prefill_chunk_of_whole_rounds_and_the_rest(rpo):
     assert float((out[0] - out[1]).abs().max()) <= 6 * 2.0 ** -8 * float(out[1].abs().max())
 
 
+@pytest.mark.parametrize("rows", [66, 72, 128, 136, 256, 258])
+@pytest.mark.parametrize("d_model,vocab", [(256, 1004), (128, 520)])
+def test_lm_head_row_maxima_on_every_tile(rpo, rows, d_model, vocab):
+    """Logits with their row maxima (128- and 256-row tiles, a vocabulary that ends inside a tile, two K slabs) against
+    the plain logits of the same hidden rows, which another kernel computes."""
+    mcfg = synth.ModelCfg("lm-rows", 1, d_model, 2, 1, 128, 256, vocab, "bf16")
+    w = synth.perturb_gains(synth.make_weights(mcfg, seed=3))
+    model = rpo.rpo_model_create(mcfg, util.to_device(w))
+    rng = np.random.default_rng(rows)
+    ng = 43
+    toks = torch.from_numpy(rng.integers(0, vocab, size=ng * 5).astype(np.int32)).cuda()
+    step = torch.from_numpy(rng.integers(0, vocab, size=ng * 6).astype(np.int32)).cuda()
+    out = []
+    for with_max in (True, False):
+        batch = rpo.rpo_batch_create(model, ng, 6, 5, 2, 64, 512)
+        rpo.rpo_prefill_prefix(batch, toks, (np.arange(ng + 1) * 5).astype(np.int32), torch.empty(ng, vocab, device="cuda"))
+        rpo.rpo_kv_fork(batch)
+        logits = torch.full((ng * 6, vocab), 3.0, device="cuda")
+        row_max = torch.full((ng * 6,), -7.0, device="cuda")
+        rpo.rpo_decode_step(batch, step, rows, None, logits, None, row_max if with_max else None)
+        out.append((logits.cpu(), row_max.cpu()))
+    a, b = out[0][0], out[1][0]
+    assert torch.equal(out[0][1][:rows], a[:rows].max(dim=1).values)
+    assert bool((out[0][1][rows:] == -7.0).all()) and bool((a[rows:] == 3.0).all())
+    assert float((a - b)[:rows].abs().max()) <= 1e-5 * float(b[:rows].abs().max())      # fp32 sums in another order
+
+
 @pytest.mark.parametrize("head_dim", [2, 10, 16, 24, 32, 48, 64, 80, 200, 256])
 def test_attn_generic_head_dims(rpo, head_dim):
     """The vector-ALU attention: four, two and one group of lanes, up to four channels a lane, heads that are and are
