@@ -1807,6 +1807,8 @@ hipError_t launch_generic(const GemmArgs& a, hipStream_t s) {
 
 }  // namespace
 
+bool gemm_takes_norm(const GemmArgs& a) { return a.epilogue == kEpiSwiglu && a.M <= 32 && mfma_ok(a) && skinny_ok(a); }
+
 int gemm_fuses_lse(const GemmArgs& a) {
     if (a.epilogue != kEpiStoreF32 || !mfma_ok(a) || !dma2_ok(a, 1)) return 0;
     if (pick_tile(a).id != kKidGemm256) return 0;
@@ -1931,7 +1933,14 @@ static hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
             a.block_max->blocks = gemm_fuses_max(a);
         }
         const int splits = gemm_skinny_splits(a);
-        e = launch_gemm_skinny(a, epi, splits, s);
+        GemmArgs g = a;
+        g.norm_split = nullptr;
+        if (gemm_skinny_splits_norm(a)) {
+            *a.norm_split = NormFuse{a.norm_split->part, a.N / 16, (const bf16*)a.norm_gain, (bf16*)a.norm_out, a.norm_eps};
+            g.norm_split = a.norm_split;
+            norm_done = true;
+        }
+        e = launch_gemm_skinny(g, epi, splits, s);
         if (e == hipSuccess && splits > 1) {
             e = launch_splitk_reduce(a, splits, s);
             norm_done = want_norm && norm_fusable(a);

@@ -67,6 +67,16 @@ struct LseFuse {
     float k2 = 0.f;                 // log2(e) / temperature
     int blocks = 0;                 // filled in by the launch: column blocks per row
 };
+// RMSNorm taken apart for a few rows: the accumulating projection leaves h = bf16(x * gain) and each row's sums of
+// squares per 16 columns, the SwiGLU projection that reads h multiplies its results by 1 / sqrt(mean(x^2) + eps).
+// (bf16 rounding is relative: h is as precise as the normalised row.)
+struct NormFuse {
+    float* part = nullptr;  // [M, blocks]
+    int blocks = 0;         // filled in by the launch that takes the norm apart; 0: norm_out holds normalised rows as usual
+    const bf16* gain = nullptr;
+    bf16* h = nullptr;
+    float eps = 0.f;
+};
 struct RopeKvArgs;
 struct GemmArgs {
     const void* A;
@@ -97,7 +107,13 @@ struct GemmArgs {
     // Optional, with kEpiStoreF32 only (the LM head of a decode step): if the launch can (gemm_fuses_max),
     // it also writes block_max->part[row, block] = max of the row over that column block.
     LseFuse* block_max = nullptr;
+    // Optional, with kEpiAddF32 and norm_out: the launch may take the norm apart (norm_split->part is given, blocks set).
+    NormFuse* norm_split = nullptr;
+    // Optional, with kEpiSwiglu, where gemm_takes_norm says so: A is the h of a norm taken apart.
+    const NormFuse* norm_in = nullptr;
 };
+// Whether these (SwiGLU) arguments can come with norm_in.
+bool gemm_takes_norm(const GemmArgs& a);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 // The weight-streaming kernel for few rows (bf16, K a multiple of 64, 16-byte aligned rows: checked by
 // launch_gemm).  epi: kEpiStore / kEpiStoreF32 / kEpiAddF32 / kEpiSwiglu, kEpiRope (a.rope, head_dim 128) or
@@ -105,6 +121,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 // splits > 1: fp32 partial sums of that many K ranges to a.ws[splits][M][N] instead.
 hipError_t launch_gemm_skinny(const GemmArgs& a, int epi, int splits, hipStream_t s);
 int gemm_skinny_splits(const GemmArgs& a);
+bool gemm_skinny_splits_norm(const GemmArgs& a);  // honours GemmArgs::norm_split
 // Up to 64 rows: whether that kernel is the faster one, given whether the tiles would split K.
 bool gemm_skinny_takes(const GemmArgs& a, bool tiles_split_k);
 // More than 64 rows: whether that kernel takes the problem in groups of 64 rows (> 0) or not at all (0).

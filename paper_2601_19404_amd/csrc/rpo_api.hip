@@ -457,7 +457,8 @@ GemmArgs gemm_args(rpo_batch* b, const void* A, int64_t lda, const void* W, int6
 
 hipError_t gemm(rpo_batch* b, const void* A, int64_t lda, const void* W, int64_t ldw, void* C,
                 int64_t ldc, int M, int N, int K, int epi, hipStream_t s, const void* norm_gain = nullptr,
-                void* norm_out = nullptr, const RopeKvArgs* rope = nullptr) {
+                void* norm_out = nullptr, const RopeKvArgs* rope = nullptr, NormFuse* norm_split = nullptr,
+                const NormFuse* norm_in = nullptr) {
     const rpo_model* m = b->m;
     GemmArgs g;
     g.A = A;
@@ -478,6 +479,8 @@ hipError_t gemm(rpo_batch* b, const void* A, int64_t lda, const void* W, int64_t
     g.norm_out = norm_out;
     g.norm_eps = m->d.rms_eps;
     g.rope = rope;
+    g.norm_split = norm_split;
+    g.norm_in = norm_in;
     const double es = (double)dtype_size(g.dtype);
     const double out_bytes = epi == kEpiStore ? (double)M * N * es
                              : epi == kEpiStoreF32 ? (double)M * N * 4.0
@@ -570,10 +573,15 @@ hipError_t run_layers(rpo_batch* b, const PassCfg& pc, hipStream_t s) {
             RET_IF(timed(attn_uses_mfma(aa) ? kKidAttnChunk : 0, pc.attn_flops, pc.attn_bytes, s,
                          [&] { return launch_attn_chunk(aa, s); }));
         }
+        // a few rows: the norm between O and gate/up is taken apart (its sums sit in the K-split scratch, which neither uses)
+        NormFuse nf;
+        nf.part = b->at<float>(b->L.gu);
+        const bool few = gemm_takes_norm(gemm_args(b, h, d.d_model, m->w_gate_up[l], d.d_model, act, d.d_ffn, pc.rows,
+                                                   2 * d.d_ffn, d.d_model, kEpiSwiglu));
         RET_IF(gemm(b, attn, qd, m->wo[l], qd, x, d.d_model, pc.rows, d.d_model, qd, kEpiAddF32, s,
-                    m->ffn_norm[l], h));
+                    m->ffn_norm[l], h, nullptr, few ? &nf : nullptr));
         RET_IF(gemm(b, h, d.d_model, m->w_gate_up[l], d.d_model, act, d.d_ffn, pc.rows, 2 * d.d_ffn, d.d_model,
-                    kEpiSwiglu, s));
+                    kEpiSwiglu, s, nullptr, nullptr, nullptr, nullptr, nf.blocks > 0 ? &nf : nullptr));
         const bool last = l + 1 == d.n_layers;
         const void* next_gain = last ? (pc.final_norm_out ? m->final_norm : nullptr) : m->attn_norm[l + 1];
         void* next_out = last ? pc.final_norm_out : h;

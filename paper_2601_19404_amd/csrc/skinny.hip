@@ -74,7 +74,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
                                                               const bf16* __restrict__ W, int64_t ldw,
                                                               void* __restrict__ Cv, int64_t ldc, int M, int N,
                                                               int K, int slabs_per_split, int blocks,
-                                                              int row_groups, RopeKvArgs rk, LseFuse lf) {
+                                                              int row_groups, RopeKvArgs rk, LseFuse lf, NormFuse nf) {
     static_assert(EPI != kEpiLogitsMax || NB == 4, "row maxima are kept per 64 columns");
     constexpr int MB = (MA + 1) / 2;  // 16-column MFMA blocks of activations (MA = 1: rows 0 .. 7 twice)
     constexpr int ROWS = MB * 16, COLS = NB * 16;
@@ -177,6 +177,20 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
 #pragma unroll
     for (int i = 0; i < S - 1; ++i)
         if (i < n_my) issue(i, i);
+    // h of a norm taken apart: the rows' sums of squares (wave w: rows w, w + NW, ..., up to 256 blocks) are asked for
+    // behind the first slabs and used after the last.
+    constexpr bool kNormIn = EPI == kEpiSwiglu && MA <= 4;
+    constexpr int kRows = kNormIn ? ROWS / NW : 1;
+    float sq[kRows][4];
+    if constexpr (kNormIn) {
+#pragma unroll
+        for (int i = 0; i < kRows; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int m = wave + i * NW, c = lane + 64 * q;
+                sq[i][q] = nf.part && m < M && c < nf.blocks ? nf.part[m * nf.blocks + c] : 0.f;
+            }
+    }
     int st = 0;
 #pragma clang loop unroll(disable)
     for (int i = 0; i < n_my; ++i) {
@@ -204,6 +218,16 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
 #pragma unroll
             for (int t = 0; t < NB; ++t) *(f32x4_t*)(dst + m * 16 * LD + t * 16) = acc[m][t];
     }
+    float* inv = part + NW * ROWS * LD;  // [ROWS]
+    if constexpr (kNormIn) {
+        if (nf.part) {
+#pragma unroll
+            for (int i = 0; i < kRows; ++i) {
+                const float ss = wave_sum((sq[i][0] + sq[i][1]) + (sq[i][2] + sq[i][3]));
+                if (lane == 0) inv[wave + i * NW] = 1.0f / sqrtf(ss / (float)K + nf.eps);
+            }
+        }
+    }
     __syncthreads();
 
     // four consecutive columns of row m, summed over the waves in order
@@ -220,7 +244,12 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
             const int m = m0 + it / (NB * 2), q = it % (NB * 2);
             const int c = (q >> 1) * 16 + (q & 1) * 4, oc = (b * NB + (q >> 1)) * 8 + (q & 1) * 4;
             if (m >= M) continue;
-            const f32x4_t gate = total(m - m0, c), up = total(m - m0, 8 + c);
+            f32x4_t gate = total(m - m0, c), up = total(m - m0, 8 + c);
+            if (kNormIn && nf.part) {
+                const float f = inv[m - m0];
+                gate *= f;
+                up *= f;
+            }
             u16x4_t o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16(silu_f(gate[e]) * up[e]).bits;
@@ -308,6 +337,22 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
                 }
             } else {
                 float* dst = (float*)Cv + (int64_t)m * ldc + n;
+                if constexpr (EPI == kEpiAddF32 && NB == 1) {
+                    if (nf.part) {  // the norm that follows, taken apart: whole 16-column blocks, 16-byte rows (launcher)
+                        const f32x4_t x = *(const f32x4_t*)dst + v;
+                        const u16x4_t gain = *(const u16x4_t*)(nf.gain + n);
+                        *(f32x4_t*)dst = x;
+                        u16x4_t o;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16(x[e] * bf16_to_f32(bf16{gain[e]})).bits;
+                        *(u16x4_t*)(nf.h + (int64_t)m * N + n) = o;
+                        float ss = (x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3]);
+                        ss += __shfl_xor(ss, 1, 64);
+                        ss += __shfl_xor(ss, 2, 64);
+                        if (c == 0) nf.part[(int64_t)m * nf.blocks + b] = ss;
+                        continue;
+                    }
+                }
                 if (vec && n + 3 < N) {
                     *(f32x4_t*)dst = EPI == kEpiAddF32 ? *(const f32x4_t*)dst + v : v;
                 } else {
@@ -330,7 +375,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
 template <int MA, int NB, int NW, int S>
 constexpr size_t skinny_lds() {
     constexpr size_t rings = (size_t)NW * S * (2 * NB + MA) * 1024;
-    constexpr size_t sums = (size_t)NW * ((MA + 1) / 2) * 16 * (NB * 16 + 4) * sizeof(float);
+    constexpr size_t rows = (size_t)((MA + 1) / 2) * 16;
+    constexpr size_t sums = (NW * rows * (NB * 16 + 4) + rows) * sizeof(float);  // and a factor per row
     return rings > sums ? rings : sums;
 }
 
@@ -355,7 +401,8 @@ hipError_t launch_one(const GemmArgs& a, int blocks, hipStream_t s, int splits =
         (const bf16*)a.A, a.lda, (const bf16*)a.W, a.ldw, out ? out : a.C, a.ldc, a.M, a.N, a.K,
         ceil_div(a.K / 64, splits), blocks, row_groups,
         (EPI == kEpiRope && a.rope) ? *a.rope : RopeKvArgs{},
-        (EPI == kEpiLogitsMax && a.block_max) ? *a.block_max : LseFuse{});
+        (EPI == kEpiLogitsMax && a.block_max) ? *a.block_max : LseFuse{},
+        (EPI == kEpiAddF32 && a.norm_split) ? *a.norm_split : (EPI == kEpiSwiglu && a.norm_in) ? *a.norm_in : NormFuse{});
     return hipGetLastError();
 }
 
@@ -470,6 +517,14 @@ bool gemm_skinny_takes(const GemmArgs& a, bool tiles_split_k) {
     // N = 32768, K = 3584: 32 rows 38.3, 35.7; 64 rows 38.3, 39.1; K = 6144, 64 rows 76, 85.  A vocabulary (N = 151936, 64
     // rows): K = 1536 117, 114; K = 3584 227, 244.  N = 24000, 20 rows: K = 128 4.6, 5.1; K = 256 the same.
     return few || (some && a.K >= 256) || (a.epilogue == kEpiStoreF32 && a.N > 24576 && a.K < 3072);
+}
+
+// Up to 32 rows: RMSNorm in a launch of its own is 3 to 5 us of a layer's 45 (1.5B shape, 8 rows) to 125 (7B, 16 rows); taken
+// apart between the O and the gate/up projection it costs neither of them anything that shows.  One 16-column block
+// per workgroup, at most 256 of them (the consumer's lanes hold four a row).
+bool gemm_skinny_splits_norm(const GemmArgs& a) {
+    return a.epilogue == kEpiAddF32 && a.norm_split && a.norm_out && a.M <= 32 && a.N % 16 == 0 && a.N <= 4096 && gemm_skinny_splits(a) == 1 && a.ldc % 4 == 0 &&
+           ((uintptr_t)a.C & 15) == 0 && ((uintptr_t)a.norm_out & 7) == 0 && ((uintptr_t)a.norm_gain & 7) == 0;
 }
 
 hipError_t gemm_skinny_load_kernels() {

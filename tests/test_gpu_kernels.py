@@ -616,6 +616,32 @@ def test_prefill_chunk_of_whole_rounds_and_the_rest(rpo):
     assert float((out[0] - out[1]).abs().max()) <= 6 * 2.0 ** -8 * float(out[1].abs().max())
 
 
+@pytest.mark.parametrize("d_model,hq,hk,ffn", [(256, 2, 1, 320), (1536, 12, 2, 1024), (3584, 28, 4, 2080), (4096, 8, 2, 10304), (336, 2, 2, 256)])
+def test_few_rows_take_the_norm_apart(rpo, d_model, hq, hk, ffn):
+    """The RMSNorm between O and gate/up of up to 32 rows (sums of squares per 16 columns, a factor per row) against 40
+    rows of the same batch, where it is a kernel of its own (and widths that keep it: 336 is no multiple of 64)."""
+    mcfg = synth.ModelCfg("norm-apart", 2, d_model, hq, hk, 128, ffn, 512, "bf16")
+    w = synth.perturb_gains(synth.make_weights(mcfg, seed=9))
+    model = rpo.rpo_model_create(mcfg, util.to_device(w))
+    rng = np.random.default_rng(d_model)
+    toks = torch.from_numpy(rng.integers(0, 512, size=20 * 5).astype(np.int32)).cuda()
+    step = torch.from_numpy(rng.integers(0, 512, size=40).astype(np.int32)).cuda()
+
+    def logits(rows):
+        batch = rpo.rpo_batch_create(model, 20, 2, 5, 2, 64, 512)
+        rpo.rpo_prefill_prefix(batch, toks, (np.arange(21) * 5).astype(np.int32), torch.empty(20, 512, device="cuda"))
+        rpo.rpo_kv_fork(batch)
+        out = torch.zeros(40, 512, device="cuda")
+        rpo.rpo_decode_step(batch, step, rows, None, out)
+        return out.cpu()
+
+    ref = logits(40)
+    for rows in (1, 7, 8, 9, 16, 17, 31, 32, 33):
+        got = logits(rows)
+        # two bf16 pipelines of two layers: six ulps of the logit scale
+        assert float((got - ref)[:rows].abs().max()) <= 6 * 2.0 ** -8 * float(ref[:rows].abs().max()), rows
+
+
 @pytest.mark.parametrize("rows", [66, 72, 128, 136, 256, 258])
 @pytest.mark.parametrize("d_model,vocab", [(256, 1004), (128, 520)])
 def test_lm_head_row_maxima_on_every_tile(rpo, rows, d_model, vocab):
