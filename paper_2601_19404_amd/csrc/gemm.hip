@@ -5,10 +5,11 @@
 //    (v_mfma_f32_32x32x16_bf16; in gemm_dma2_kernel v_mfma_f32_16x16x32_bf16).  64-deep K slabs go from global memory straight into LDS
 //    (global_load_lds_dwordx4), two to four stages deep; fragments are double-buffered in registers.
 //    Tile shapes and what they are for (pick_tile): 256x256 (many-tile problems: prefill / log-prob
-//    chunks, wide decode projections), 256x192 / 256x160 (large M with a narrow N, decode gate/up),
-//    128x128 and 64x128 (deep-K decode projections, split along K: the fp32 partial sums go to a
+//    chunks, wide decode projections), 256x192 / 256x160 (large M with a narrow N, decode gate/up), 128x256 (LM head of up
+//    to 128 rows), 128x128 and 64x128 (deep-K decode projections, split along K: the fp32 partial sums go to a
 //    workspace and a reduction kernel applies the epilogue -- deterministic, no floating-point
-//    atomics), 64x64 and 32x128 (shallow-K decode projections, one tile per CU, no K split).
+//    atomics; chunks of up to a few thousand rows, unsplit), 64x64 and 32x128 (shallow-K decode projections and small
+//    chunks, no K split).
 //    (tile, K-split) work items are dealt evenly to the 8 XCDs, neighbouring tiles to the same XCD
 //    (each has its own L2).  The wide two-stage tiles run on gemm_dma2_kernel: fragment reads and loads are
 //    spread between the MFMAs of a k-step (the matrix pipe never waits behind a burst of memory
