@@ -78,6 +78,7 @@ def lib() -> C.CDLL:
     L.rpo_attn_decode.argtypes = [vp, i32, vp, i32, i32, vp, vp, vp]
     L.rpo_gemm_nt.argtypes = [vp, i64, vp, i64, vp, i64, i32, i32, i32, i32, i32, vp, sz, vp]
     L.rpo_gemm_nt_noalloc.argtypes = [vp, i64, vp, i64, vp, i64, i32, i32, i32, i32, i32, vp]
+    L.rpo_gemm_plan.argtypes = [i32, i32, i32, i32, i32, sz, C.POINTER(i32)]
     L.rpo_probe_peaks.argtypes = [vp, vp, sz, vp, C.POINTER(C.c_double), C.POINTER(C.c_double), vp]
     L.rpo_set_kernel_path.argtypes = [C.c_int]
     L.rpo_profile_start.argtypes = [C.c_int, C.c_int]
@@ -86,7 +87,7 @@ def lib() -> C.CDLL:
     for name in ("rpo_model_create", "rpo_batch_create", "rpo_prefill_prefix", "rpo_kv_fork",
                  "rpo_decode_step", "rpo_decode_step_compact", "rpo_sample", "rpo_suffix_logprobs", "grpo_advantages",
                  "rpo_shape_rewards", "rpo_objective_forward", "rpo_cut_pack", "rpo_cache_update", "rpo_gemm_nt",
-                 "rpo_attn_decode", "rpo_gemm_nt_noalloc", "rpo_set_kernel_path", "rpo_profile_start", "rpo_profile_stop", "rpo_probe_peaks"):
+                 "rpo_attn_decode", "rpo_gemm_nt_noalloc", "rpo_gemm_plan", "rpo_set_kernel_path", "rpo_profile_start", "rpo_profile_stop", "rpo_probe_peaks"):
         getattr(L, name).restype = C.c_int
     _lib = L
     return L
@@ -95,7 +96,7 @@ def lib() -> C.CDLL:
 EXPORTS = ("rpo_model_create", "rpo_model_destroy", "rpo_kv_pool_bytes", "rpo_workspace_bytes",
            "rpo_batch_create", "rpo_batch_destroy", "rpo_prefill_prefix", "rpo_kv_fork",
            "rpo_decode_step", "rpo_decode_step_compact", "rpo_sample", "rpo_suffix_logprobs", "grpo_advantages",
-           "rpo_shape_rewards", "rpo_objective_forward", "rpo_cut_pack", "rpo_cache_update", "rpo_last_error", "rpo_gemm_nt", "rpo_attn_decode", "rpo_gemm_nt_noalloc", "rpo_set_kernel_path", "rpo_profile_start",
+           "rpo_shape_rewards", "rpo_objective_forward", "rpo_cut_pack", "rpo_cache_update", "rpo_last_error", "rpo_gemm_nt", "rpo_attn_decode", "rpo_gemm_nt_noalloc", "rpo_gemm_plan", "rpo_set_kernel_path", "rpo_profile_start",
            "rpo_profile_stop", "rpo_probe_peaks")
 
 
@@ -400,6 +401,14 @@ def rpo_gemm_nt_noalloc(a_dev: torch.Tensor, w_dev: torch.Tensor, c_dev: torch.T
     dt = RPO_F32 if a_dev.dtype == torch.float32 else RPO_BF16
     _check(lib().rpo_gemm_nt_noalloc(a_dev.data_ptr(), a_dev.stride(0), w_dev.data_ptr(), w_dev.stride(0),
                                      c_dev.data_ptr(), c_dev.stride(0), M, N, K, dt, epilogue, _stream(stream)))
+
+
+def rpo_gemm_plan(M: int, N: int, K: int, dtype: int, epilogue: int, ws_bytes: int = 0) -> dict:
+    """What rpo_gemm_nt would launch for dense, aligned operands of these sizes; host-only."""
+    out = (C.c_int32 * 4)()
+    _check(lib().rpo_gemm_plan(M, N, K, dtype, epilogue, ws_bytes, out))
+    return dict(kernel=next(n for n, i in KERNEL_IDS.items() if i == out[0]), splits=out[1], first_rows=out[2],
+                waves=bool(out[3]))
 
 
 def rpo_set_kernel_path(path: int) -> None:

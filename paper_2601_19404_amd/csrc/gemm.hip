@@ -1774,15 +1774,28 @@ hipError_t launch_tile(const GemmArgs& a, int splits, hipStream_t s) {
     }
 }
 
+// Which of the generic kernels takes it: waves (8 rows x 4 weight rows each, lanes along K) or 64x64 tiles.  SwiGLU has waves
+// only.  A chip of 256 tiles takes 3.5 us and 0.1 us (fp32 0.098, bf16 0.106) for every value of K whatever their number, a
+// round of 1024 workgroups of waves about 1.75 us + 5.4 ns a value of K in fp32 and 2 us + 20 ns in bf16, whose loads carry
+// half as many bytes (a begun second round costs a whole one).  us, tiles / waves, fp32: 64 x 64 x 1024 101 / 8.4, 64 x
+// 4096 x 16 5.2 / 7.1, x 128 16.1 / 8.0; 1000 x 1024 x 128 17.1 / 22.1, x 512 54 / 39; bf16: 200 x 1000 x 512 58 / 26, 150 x 4096
+// x 32 6.1 / 15.9, 2500 x 128 x 512 58 / 36.  More than two rounds of bf16 waves read what the L2s do not hold again and
+// again once K is deep (64 x 8192 x 1024 136 / 92, x 2048 271 / 345; 1000 x 512 x 2048 272 / 318).
 constexpr int kGenericTiles = 256;
+bool generic_takes_waves(const GemmArgs& a) {
+    if (a.epilogue == kEpiSwiglu) return true;
+    if ((int64_t)ceil_div(a.N, 64) * ceil_div(a.M, 64) > kGenericTiles) return false;
+    double rounds = (double)ceil_div(a.M, kWaveM) * ceil_div(a.N, 4 * kWaveN) / 1024.;
+    if (a.dtype == kF32) return rounds * (1.75 + 0.0054 * a.K) <= 0.098 * a.K;
+    if (rounds > 1. && rounds < 2.) rounds = 2.;
+    return (rounds <= 2. || a.K <= 1024) && rounds * (2. + 0.02 * a.K) <= 0.106 * a.K;
+}
+
 template <typename T, int EPI>
 void launch_generic_epi(const GemmArgs& a, hipStream_t s) {
     const T* A = (const T*)a.A;
     const T* W = (const T*)a.W;
-    // A wave reads 12 values for 32 products, a 64x64 tile 2 for 64: far beyond a chip of tiles those are the faster ones
-    // (us, tiles / waves: 500 x 2048 x 1024 107 / 69, 1000 x 1024 x 1024, both 256 tiles, 127 / 69; 2000 x 2048 x 512, 1024
-    // tiles: 94 with tiles, twice those 69 by the rate of the waves).
-    if (EPI == kEpiSwiglu || ceil_div(a.N, 64) * ceil_div(a.M, 64) <= kGenericTiles) {
+    if (generic_takes_waves(a)) {
         const int cols = EPI == kEpiSwiglu ? a.N / 2 : a.N, per_wg = 4 * (EPI == kEpiSwiglu ? kWaveN / 2 : kWaveN);
         const int row_blocks = ceil_div(a.M, kWaveM);
         gemm_generic_wave_kernel<T, EPI><<<dim3(ceil_div(cols, per_wg), row_blocks < 65535 ? row_blocks : 65535), 256, 0, s>>>(
@@ -1898,6 +1911,17 @@ static int whole_round_rows(const GemmArgs& a) {
     const double split = rounds + (t128 <= 256 ? 0.42 : 0.68) + 10. / (1.45 * (a.K / kBK));
     const double c256 = ceil_div(t256, 256), c192 = ceil_div(ceil_div(a.M, 256) * ceil_div(a.N, 192), 256) * 0.78;
     return split < 0.97 * (c256 < c192 ? c256 : c192) ? rows : 0;
+}
+
+GemmPlan gemm_plan(const GemmArgs& a) {
+    GemmPlan p{gemm_kernel_id(a), 1, 0, 0};
+    if (!mfma_ok(a)) {
+        p.waves = generic_takes_waves(a) ? 1 : 0;
+    } else {
+        p.first_rows = whole_round_rows(a);
+        if (a.ws && a.ws_bytes) p.splits = skinny_ok(a) ? gemm_skinny_splits(a) : pick_splits(a, pick_tile(a));
+    }
+    return p;
 }
 
 static hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s);

@@ -164,6 +164,14 @@ hipError_t gemm_load_kernels();
 hipError_t gemm_skinny_load_kernels();
 // Which kernel launch_gemm picks for these arguments.
 int gemm_kernel_id(const GemmArgs& a);
+// The rest of its choice (host-only; for tests).
+struct GemmPlan {
+    int kernel_id;
+    int splits;      // K ranges whose sums go through the scratch, 1: not split
+    int first_rows;  // rows of the first of two launches, 0: one launch
+    int waves;       // generic kernels: 1 for gemm_generic_wave_kernel
+};
+GemmPlan gemm_plan(const GemmArgs& a);
 // Bytes of fp32 K-split partial sums launch_gemm would write for these arguments if the
 // workspace were unlimited (0 = the problem is not split along K); a.ws / a.ws_bytes are ignored.
 size_t gemm_splitk_scratch_bytes(const GemmArgs& a);

@@ -1155,6 +1155,32 @@ extern "C" int rpo_gemm_nt(const void* a_dev, int64_t lda, const void* w_dev, in
     return RPO_OK;
 }
 
+extern "C" int rpo_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t dtype, int32_t epilogue, size_t ws_bytes,
+                             int32_t* plan_out) {
+    if (!plan_out) return fail(RPO_EINVAL, "rpo_gemm_plan: NULL argument");
+    if (M < 1 || N < 1 || K < 1 || (dtype != RPO_F32 && dtype != RPO_BF16) || epilogue < 0 || epilogue > 3 ||
+        (epilogue == 3 && N % 2))
+        return fail(RPO_EINVAL, "rpo_gemm_plan: bad sizes, dtype or epilogue");
+    GemmArgs g;
+    g.A = g.W = g.C = (void*)(uintptr_t)256;  // aligned; never dereferenced
+    g.lda = g.ldw = K;
+    g.ldc = epilogue == 3 ? N / 2 : N;
+    g.M = M;
+    g.N = N;
+    g.K = K;
+    g.dtype = dtype;
+    g.epilogue = epilogue;
+    g.path = g_kernel_path;
+    g.ws = ws_bytes ? g.C : nullptr;
+    g.ws_bytes = ws_bytes;
+    const GemmPlan p = gemm_plan(g);
+    plan_out[0] = p.kernel_id;
+    plan_out[1] = p.splits;
+    plan_out[2] = p.first_rows;
+    plan_out[3] = p.waves;
+    return RPO_OK;
+}
+
 // ---------------------------------------------------------------------------
 // rpo_gemm_nt without a workspace argument and without any allocation: the K-split partial
 // sums go to a fixed device array that is part of the library's code object.

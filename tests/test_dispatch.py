@@ -1,0 +1,28 @@
+"""Which kernel a GEMM of given sizes goes to (rpo_gemm_plan: the library's own choice, made on the host)."""
+import pytest
+
+from paper_2601_19404_amd import binding as rpo
+
+
+@pytest.fixture(autouse=True)
+def default_path():
+    rpo.rpo_set_kernel_path(0)
+
+
+# measured us of the tiles and of the waves: below, the faster one by 10 % or more
+@pytest.mark.parametrize("M,N,K,waves", [
+    (64, 64, 1024, True), (64, 4096, 16, False), (64, 4096, 128, True), (1000, 1024, 128, False), (1000, 1024, 512, True),
+    (150, 4096, 32, False), (1100, 512, 32, False), (16000, 64, 64, False), (16000, 64, 2048, True), (2000, 2048, 512, False)])
+def test_generic_fp32_goes_to_the_faster_kernel(M, N, K, waves):
+    for epilogue in (0, 1, 2):
+        assert rpo.rpo_gemm_plan(M, N, K, rpo.RPO_F32, epilogue)["waves"] == waves
+    if N % 2 == 0:
+        assert rpo.rpo_gemm_plan(M, N, K, rpo.RPO_F32, 3)["waves"]
+
+
+@pytest.mark.parametrize("M,N,K,waves", [   # K no multiple of 8: not on the matrix cores
+    (64, 64, 1020, True), (150, 4096, 30, False), (150, 4096, 2044, False), (1000, 1024, 2044, False), (1000, 512, 1020, True),
+    (1000, 512, 2044, False), (64, 8192, 2044, False), (2500, 128, 510, True), (200, 1000, 2044, True), (16000, 64, 510, False)])
+def test_generic_bf16_goes_to_the_faster_kernel(M, N, K, waves):
+    plan = rpo.rpo_gemm_plan(M, N, K, rpo.RPO_BF16, 0)
+    assert plan["kernel"] == "gemm_generic" and plan["waves"] == waves
