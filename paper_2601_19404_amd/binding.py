@@ -78,7 +78,7 @@ def lib() -> C.CDLL:
     L.rpo_attn_decode.argtypes = [vp, i32, vp, i32, i32, vp, vp, vp]
     L.rpo_gemm_nt.argtypes = [vp, i64, vp, i64, vp, i64, i32, i32, i32, i32, i32, vp, sz, vp]
     L.rpo_gemm_nt_noalloc.argtypes = [vp, i64, vp, i64, vp, i64, i32, i32, i32, i32, i32, vp]
-    L.rpo_gemm_plan.argtypes = [i32, i32, i32, i32, i32, sz, C.POINTER(i32)]
+    L.rpo_gemm_plan.argtypes = [i32, i32, i32, i32, i32, sz, sz, C.POINTER(i32)]
     L.rpo_probe_peaks.argtypes = [vp, vp, sz, vp, C.POINTER(C.c_double), C.POINTER(C.c_double), vp]
     L.rpo_set_kernel_path.argtypes = [C.c_int]
     L.rpo_profile_start.argtypes = [C.c_int, C.c_int]
@@ -403,12 +403,12 @@ def rpo_gemm_nt_noalloc(a_dev: torch.Tensor, w_dev: torch.Tensor, c_dev: torch.T
                                      c_dev.data_ptr(), c_dev.stride(0), M, N, K, dt, epilogue, _stream(stream)))
 
 
-def rpo_gemm_plan(M: int, N: int, K: int, dtype: int, epilogue: int, ws_bytes: int = 0) -> dict:
+def rpo_gemm_plan(M: int, N: int, K: int, dtype: int, epilogue: int, ws_bytes: int = 0, turn_bytes: int = 0) -> dict:
     """What rpo_gemm_nt would launch for dense, aligned operands of these sizes; host-only."""
-    out = (C.c_int32 * 4)()
-    _check(lib().rpo_gemm_plan(M, N, K, dtype, epilogue, ws_bytes, out))
+    out = (C.c_int32 * 5)()
+    _check(lib().rpo_gemm_plan(M, N, K, dtype, epilogue, ws_bytes, turn_bytes, out))
     return dict(kernel=next(n for n, i in KERNEL_IDS.items() if i == out[0]), splits=out[1], first_rows=out[2],
-                waves=bool(out[3]))
+                waves=bool(out[3]), weights_pass=bool(out[4]))
 
 
 def rpo_set_kernel_path(path: int) -> None:

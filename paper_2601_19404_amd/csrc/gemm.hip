@@ -1821,6 +1821,20 @@ hipError_t launch_generic(const GemmArgs& a, hipStream_t s) {
 
 }  // namespace
 
+// The non-temporal hint is a gain for weights that come from HBM and a loss for those that the caches (32 MB of L2, 256 MB
+// memory-side) still hold, where it keeps them from staying.  A GEMM of 1 to 64 rows over matrices used in turn, with /
+// without the hint: up to 256 MB of them 1.05 to 1.8, from 320 MB on 0.8 to 1.0 (8 rows, N = 2048, K = 1536: 126 MB 4.14 /
+// 3.66 us, 396 MB 3.84 / 4.12).  A decode step: models of 91 MB 213 / 202 us (8 rows), 284 / 259 (64), 183 MB 62 / 60, 85 /
+// 76, 246 MB 252 / 255, 354 / 368, 362 MB 140 / 150, 188 / 202 (the logits and pages of a step pass through the cache as
+// well, hence the lower limit).  A call by itself says nothing of what is read between it and the next: its matrix alone
+// counts.  One matrix over and over, 8 / 24 / 64 rows: 32 MB 1.40 / 1.37 / 1.09, 52 MB 0.98 / 1.04 / 1.06, 62 MB 0.82 / 0.84 /
+// 1.00, 259 MB 0.97 / 1.05 / 1.09, 342 MB 0.87 / 0.90 / 1.01.
+bool gemm_weights_pass(const GemmArgs& a) {
+    if (a.turn_bytes) return a.turn_bytes > (size_t)240 << 20;
+    const size_t bytes = (size_t)a.N * (size_t)a.K * sizeof(bf16);
+    return bytes > (size_t)320 << 20 || (a.M <= 16 && bytes > (size_t)48 << 20);
+}
+
 bool gemm_takes_norm(const GemmArgs& a) { return a.epilogue == kEpiSwiglu && a.M <= 32 && mfma_ok(a) && skinny_ok(a); }
 
 int gemm_fuses_lse(const GemmArgs& a) {
@@ -1881,7 +1895,7 @@ static hipError_t launch_gemm_only(const GemmArgs& a, int splits, const TileCfg&
             return launch_one<256, 160, 4, 1, kEpiSwiglu, 2>(a, 1, a.C, s);
         case kKidGemm128x160:
             // one row of tiles: every weight row is read by one workgroup (K = 3584, N = 37888, 128 rows 57.0 -> 52.3 us)
-            if (a.M <= 128) return launch_one<128, 160, 4, 1, kEpiSwiglu, 2, 4, 64, true>(a, 1, a.C, s);
+            if (a.M <= 128 && gemm_weights_pass(a)) return launch_one<128, 160, 4, 1, kEpiSwiglu, 2, 4, 64, true>(a, 1, a.C, s);
             return launch_one<128, 160, 4, 1, kEpiSwiglu, 2, 4>(a, 1, a.C, s);
         case kKidGemm256x192:
             if (a.epilogue == kEpiSwiglu) return launch_one<256, 192, 4, 2, kEpiSwiglu, 2>(a, 1, a.C, s);
@@ -1914,7 +1928,7 @@ static int whole_round_rows(const GemmArgs& a) {
 }
 
 GemmPlan gemm_plan(const GemmArgs& a) {
-    GemmPlan p{gemm_kernel_id(a), 1, 0, 0};
+    GemmPlan p{gemm_kernel_id(a), 1, 0, 0, gemm_weights_pass(a) ? 1 : 0};
     if (!mfma_ok(a)) {
         p.waves = generic_takes_waves(a) ? 1 : 0;
     } else {
@@ -1982,8 +1996,11 @@ static hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
             // One row of tiles reads every weight row once; up to 128 rows would leave half of a 256-row tile empty.  A
             // decode step of one layer, us: N = 152064, K = 3584, 72 / 128 rows 375 / 407 -> 288 / 327, 256 rows 497 -> 450; N = 151936,
             // K = 1536, 72 / 128 rows 203 / 218 -> 163 / 175, 256 rows 261 -> 236.
-            if (a.M <= 128 && dma2_ok(a, 1, 3)) return launch_one<128, 256, 2, 4, kEpiLogitsMax, false, 3, 64, true>(a, 1, a.C, s);
-            if (a.M <= 256) return launch_one<256, 256, 2, 4, kEpiLogitsMax, false, 2, 64, true>(a, 1, a.C, s);
+            const bool pass = gemm_weights_pass(a);
+            if (a.M <= 128 && dma2_ok(a, 1, 3))
+                return pass ? launch_one<128, 256, 2, 4, kEpiLogitsMax, false, 3, 64, true>(a, 1, a.C, s)
+                            : launch_one<128, 256, 2, 4, kEpiLogitsMax, false, 3>(a, 1, a.C, s);
+            if (a.M <= 256 && pass) return launch_one<256, 256, 2, 4, kEpiLogitsMax, false, 2, 64, true>(a, 1, a.C, s);
             return launch_one<256, 256, 2, 4, kEpiLogitsMax, false>(a, 1, a.C, s);
         }
         e = launch_gemm_only(a, splits, t, s);

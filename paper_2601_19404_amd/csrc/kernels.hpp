@@ -11,8 +11,8 @@ __device__ inline float silu_f(float g) { return g * __builtin_amdgcn_rcpf(1.0f 
 
 // 16 bytes per lane from global memory (uniform base + 32-bit lane offset) straight into LDS at
 // lds_byte_addr + off + 16 * lane.  The compiler does not see the load: every wait for it is written out.
-// ONCE is for data that is read once (weights that no other workgroup reads): the non-temporal hint keeps it from
-// taking the place of other lines on its way.  256 CUs streaming rows of 128 bytes from HBM: 6.15 -> 7.05 TB/s; for
+// ONCE is for data from HBM that is read once (weights that no other workgroup reads): the non-temporal hint keeps it
+// from taking the place of other lines on its way.  256 CUs streaming rows of 128 bytes from HBM: 6.15 -> 7.05 TB/s; for
 // lines that others read as well it is a loss (activations, each read by every CU: 113 -> 59 GB/s per CU).
 template <bool ONCE>
 __device__ inline void dma_load16_at(const void* sbase, uint32_t voff, uint32_t lds_byte_addr, int off) {
@@ -109,9 +109,13 @@ struct GemmArgs {
     LseFuse* block_max = nullptr;
     // Optional, with kEpiAddF32 and norm_out: the launch may take the norm apart (norm_split->part is given, blocks set).
     NormFuse* norm_split = nullptr;
+    // Bytes of weights that a program reads from one use of W to the next, where it is known (a model's); 0: a call by itself.
+    size_t turn_bytes = 0;
     // Optional, with kEpiSwiglu, where gemm_takes_norm says so: A is the h of a norm taken apart.
     const NormFuse* norm_in = nullptr;
 };
+// Whether W comes from HBM each time it is read, i.e. has left the memory-side cache since its last use.
+bool gemm_weights_pass(const GemmArgs& a);
 // Whether these (SwiGLU) arguments can come with norm_in.
 bool gemm_takes_norm(const GemmArgs& a);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
@@ -170,6 +174,7 @@ struct GemmPlan {
     int splits;      // K ranges whose sums go through the scratch, 1: not split
     int first_rows;  // rows of the first of two launches, 0: one launch
     int waves;       // generic kernels: 1 for gemm_generic_wave_kernel
+    int passing;     // weights asked for with the non-temporal hint (where few enough rows leave them to one reader)
 };
 GemmPlan gemm_plan(const GemmArgs& a);
 // Bytes of fp32 K-split partial sums launch_gemm would write for these arguments if the

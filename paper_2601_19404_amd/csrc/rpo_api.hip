@@ -143,6 +143,11 @@ struct rpo_model {
     const void *embed, *lm_head, *final_norm;
     std::vector<const void*> attn_norm, wqkv, wo, ffn_norm, w_gate_up, w_down;
     int qkv_width() const { return (d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim; }
+    // what a decode step reads of the weights: the projections and the LM head
+    size_t weight_bytes() const {
+        const size_t qd = (size_t)d.n_q_heads * d.head_dim;
+        return ((size_t)d.n_layers * ((size_t)qkv_width() + qd + (size_t)3 * d.d_ffn) + d.vocab) * d.d_model * dtype_size(d.dtype);
+    }
 };
 
 namespace {
@@ -452,6 +457,7 @@ GemmArgs gemm_args(rpo_batch* b, const void* A, int64_t lda, const void* W, int6
     g.ws = b->at<void>(b->L.gu);
     g.ws_bytes = kSplitKBytes;
     g.norm_eps = b->m->d.rms_eps;
+    g.turn_bytes = b->m->weight_bytes();
     return g;
 }
 
@@ -475,6 +481,7 @@ hipError_t gemm(rpo_batch* b, const void* A, int64_t lda, const void* W, int64_t
     g.path = g_kernel_path;
     g.ws = b->at<void>(b->L.gu);
     g.ws_bytes = kSplitKBytes;
+    g.turn_bytes = m->weight_bytes();
     g.norm_gain = norm_gain;
     g.norm_out = norm_out;
     g.norm_eps = m->d.rms_eps;
@@ -1156,7 +1163,7 @@ extern "C" int rpo_gemm_nt(const void* a_dev, int64_t lda, const void* w_dev, in
 }
 
 extern "C" int rpo_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t dtype, int32_t epilogue, size_t ws_bytes,
-                             int32_t* plan_out) {
+                             size_t turn_bytes, int32_t* plan_out) {
     if (!plan_out) return fail(RPO_EINVAL, "rpo_gemm_plan: NULL argument");
     if (M < 1 || N < 1 || K < 1 || (dtype != RPO_F32 && dtype != RPO_BF16) || epilogue < 0 || epilogue > 3 ||
         (epilogue == 3 && N % 2))
@@ -1173,11 +1180,13 @@ extern "C" int rpo_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t dtype, int
     g.path = g_kernel_path;
     g.ws = ws_bytes ? g.C : nullptr;
     g.ws_bytes = ws_bytes;
+    g.turn_bytes = turn_bytes;
     const GemmPlan p = gemm_plan(g);
     plan_out[0] = p.kernel_id;
     plan_out[1] = p.splits;
     plan_out[2] = p.first_rows;
     plan_out[3] = p.waves;
+    plan_out[4] = p.passing;
     return RPO_OK;
 }
 

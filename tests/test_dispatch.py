@@ -26,3 +26,13 @@ def test_generic_fp32_goes_to_the_faster_kernel(M, N, K, waves):
 def test_generic_bf16_goes_to_the_faster_kernel(M, N, K, waves):
     plan = rpo.rpo_gemm_plan(M, N, K, rpo.RPO_BF16, 0)
     assert plan["kernel"] == "gemm_generic" and plan["waves"] == waves
+
+
+@pytest.mark.parametrize("M,N,K,turn_mb,weights_pass", [
+    (8, 2048, 1536, 0, False), (8, 4096, 4096, 0, False), (8, 32000, 1024, 0, True), (24, 37888, 3584, 0, False),
+    (64, 50000, 3584, 0, True),                                                                # a matrix by itself
+    (8, 2048, 1536, 183, False), (8, 151936, 1536, 183, False), (64, 2048, 1536, 246, True), (100, 2048, 1536, 2600, True)])
+def test_weights_that_the_caches_hold_carry_no_hint(M, N, K, turn_mb, weights_pass):
+    """Weights that come round again before the caches have lost them (a matrix used over and over, a small model) are
+    asked for as usual: with the non-temporal hint a decode step of a model of 90 MB took 1.1 times as long."""
+    assert rpo.rpo_gemm_plan(M, N, K, rpo.RPO_BF16, 0, 0, turn_mb << 20)["weights_pass"] == weights_pass
