@@ -1093,8 +1093,14 @@ __device__ inline void dma2_epilogue(f32x4_t (&acc)[MI][NI], void* __restrict__ 
     }
 }
 
+// Accumulators and both fragment sets of a wave in 256 registers: two waves per SIMD are asked for, and the compiler keeps all
+// of them in one register file.  Left the choice, it moved some accumulators of the 128x128 tiles between the two files
+// in every slab (129 x 512 x 1024 in two K ranges 11.75 -> 11.2 us, 256 x 512 x 512 accumulating 7.9 -> 7.6).
+template <int BM, int BN, int WM, int WN>
+constexpr int kDma2WavesPerSimd = BM / WM * BN / WN / 64 + (BM / WM + BN / WN) / 2 <= 200 ? 2 : 1;
+
 template <int BM, int BN, int WM, int WN, int EPI, int SWIGLU, int S = 2, bool ONCE = false>
-__global__ __launch_bounds__(WM* WN * 64) void gemm_dma2_kernel(const bf16* __restrict__ A, int64_t lda,
+__global__ __launch_bounds__(WM* WN * 64, (kDma2WavesPerSimd<BM, BN, WM, WN>)) void gemm_dma2_kernel(const bf16* __restrict__ A, int64_t lda,
                                                                 const bf16* __restrict__ W, int64_t ldw,
                                                                 void* __restrict__ Cv, int64_t ldc, int M,
                                                                 int N, int K, int grid_m, int grid_n,
