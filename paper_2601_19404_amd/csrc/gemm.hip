@@ -893,48 +893,6 @@ __device__ inline u32x2_t pack_bf16x4(float a, float b, float c, float d) {
                    (uint32_t)f32_to_bf16(c).bits | (uint32_t)f32_to_bf16(d).bits << 16};
 }
 
-// NB neighbouring 16-column blocks of bf16 results of one row: v[j] are columns col + 16 j + 4 (lane / 16) .. + 3, col a
-// multiple of 16.  Two blocks at a time trade halves between the lane groups (v_permlane16_swap: odd rows of 16 lanes
-// of the one register with even rows of the other), after which a lane holds eight neighbouring columns: 16-byte stores,
-// 64 bytes of a row together.  `row` is the row's first element, nullptr: this row does not exist.
-template <int NB>
-__device__ inline void store_bf16_blocks(u32x2_t (&v)[NB], bf16* row, int col, int n_cols, int64_t ldc, int lane) {
-    const int g = lane >> 4;
-    const bool vec16 = (ldc & 7) == 0 && ((uintptr_t)row & 15) == 0, vec8 = (ldc & 3) == 0 && ((uintptr_t)row & 7) == 0;
-#pragma unroll
-    for (int j = 0; j < NB; j += 2) {
-        if (j + 1 < NB && col + 16 * j + 32 <= n_cols) {  // wave-uniform
-            const u32x2_t lo = __builtin_amdgcn_permlane16_swap(v[j].x, v[j + 1 < NB ? j + 1 : j].x, false, false);
-            const u32x2_t hi = __builtin_amdgcn_permlane16_swap(v[j].y, v[j + 1 < NB ? j + 1 : j].y, false, false);
-            const int c = col + 16 * (j + (g & 1)) + 8 * (g >> 1);
-            if (!row) continue;
-            if (vec16) {
-                *(u32x4_t*)(row + c) = u32x4_t{lo.x, hi.x, lo.y, hi.y};
-            } else if (vec8) {
-                *(u32x2_t*)(row + c) = u32x2_t{lo.x, hi.x};
-                *(u32x2_t*)(row + c + 4) = u32x2_t{lo.y, hi.y};
-            } else {
-                const uint32_t w[4] = {lo.x, hi.x, lo.y, hi.y};
-#pragma unroll
-                for (int e = 0; e < 8; ++e) row[c + e].bits = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-            }
-        } else {
-#pragma unroll
-            for (int b = j; b < (j + 2 < NB ? j + 2 : NB); ++b) {
-                const int c = col + 16 * b + 4 * g;
-                if (!row) continue;
-                if (vec8 && c + 3 < n_cols) {
-                    *(u32x2_t*)(row + c) = v[b];
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (c + e < n_cols) row[c + e].bits = (uint16_t)(v[b][e >> 1] >> (16 * (e & 1)));
-                }
-            }
-        }
-    }
-}
-
 // max and sum over the four lanes that share a row
 __device__ inline float max_over_row(float v) {
     v = fmaxf(v, __shfl_xor(v, 16, 64));
@@ -951,22 +909,60 @@ __device__ inline void dma2_epilogue(f32x4_t (&acc)[MI][NI], void* __restrict__ 
         // interleaved by 16 (SW 2), two apart where by 32 (SW 1).
         constexpr int NB = EPI == kEpiSwiglu ? NI / 2 : NI;
         const int n_cols = EPI == kEpiSwiglu ? N / 2 : N, col = EPI == kEpiSwiglu ? cbase >> 1 : cbase;
+        auto result = [&](int i, int b) __attribute__((always_inline)) {
+            if constexpr (EPI == kEpiSwiglu) {
+                const f32x4_t gt = acc[i][SW == 2 ? 2 * b : 4 * (b / 2) + (b & 1)];
+                const f32x4_t up = acc[i][SW == 2 ? 2 * b + 1 : 4 * (b / 2) + 2 + (b & 1)];
+                return pack_bf16x4(silu_f(gt[0]) * up[0], silu_f(gt[1]) * up[1], silu_f(gt[2]) * up[2], silu_f(gt[3]) * up[3]);
+            } else {
+                return pack_bf16x4(acc[i][b][0], acc[i][b][1], acc[i][b][2], acc[i][b][3]);
+            }
+        };
+        // Whole blocks and rows of 16-byte pieces, the same answer in every lane: straight-line code.  Two neighbouring
+        // blocks trade halves between the lane groups (v_permlane16_swap: odd rows of 16 lanes of the one register with
+        // even rows of the other), after which a lane holds eight neighbouring columns: 16-byte stores, 64 bytes of a row
+        // together.  This code runs once a tile, out of a cold instruction cache: with the alignment asked at every pair
+        // of blocks and three kinds of store behind it, it was up to 6 KB longer and few-slab launches up to 1.4 us (us,
+        // before -> now: 520 x 512 x 256 11.2 -> 9.5, 1024 x 17920 x 256 22.6 -> 20.5, 256 x 17920 x 1536 24.8 -> 24.1,
+        // 512 x 17920 x 1536 32.3 -> 31.0, 32768 x 17920 x 1536 1392 -> 1364).
+        if (__builtin_expect((ldc & 7) == 0 && ((uintptr_t)Cv & 15) == 0 && col + 16 * NB <= n_cols, 1)) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                const int gm = m0 + wm * TM + i * 16 + r_in;
+                bf16* row = (bf16*)Cv + (int64_t)gm * ldc + col;
+#pragma unroll
+                for (int j = 0; j < NB; j += 2) {
+                    const u32x2_t a = result(i, j);
+                    if (j + 1 < NB) {
+                        const u32x2_t b = result(i, j + 1 < NB ? j + 1 : j);
+                        const u32x2_t lo = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);
+                        const u32x2_t hi = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
+                        if (gm < M) *(u32x4_t*)(row + 16 * (j + (g & 1)) + 8 * (g >> 1)) = u32x4_t{lo.x, hi.x, lo.y, hi.y};
+                    } else if (gm < M) {
+                        *(u32x2_t*)(row + 16 * j + 4 * g) = a;
+                    }
+                }
+            }
+            return;
+        }
+        const bool vec8 = (ldc & 3) == 0 && ((uintptr_t)Cv & 7) == 0;
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
             const int gm = m0 + wm * TM + i * 16 + r_in;
-            u32x2_t v[NB];
+            bf16* row = (bf16*)Cv + (int64_t)gm * ldc;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                if constexpr (EPI == kEpiSwiglu) {
-                    const f32x4_t gt = acc[i][SW == 2 ? 2 * b : 4 * (b / 2) + (b & 1)];
-                    const f32x4_t up = acc[i][SW == 2 ? 2 * b + 1 : 4 * (b / 2) + 2 + (b & 1)];
-                    v[b] = pack_bf16x4(silu_f(gt[0]) * up[0], silu_f(gt[1]) * up[1], silu_f(gt[2]) * up[2],
-                                       silu_f(gt[3]) * up[3]);
-                } else {
-                    v[b] = pack_bf16x4(acc[i][b][0], acc[i][b][1], acc[i][b][2], acc[i][b][3]);
+                if (col + 16 * b >= n_cols) break;  // uniform
+                const int c = col + 16 * b + 4 * g;
+                const u32x2_t v = result(i, b);
+                if (vec8 && col + 16 * b + 16 <= n_cols) {  // uniform
+                    if (gm < M) *(u32x2_t*)(row + c) = v;
+                } else if (gm < M) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (c + e < n_cols) row[c + e].bits = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
                 }
             }
-            store_bf16_blocks<NB>(v, gm < M ? (bf16*)Cv + (int64_t)gm * ldc : nullptr, col, n_cols, ldc, lane);
         }
     } else if constexpr (EPI == kEpiLse) {
         const int blk = (n0 / BN) * WN + wn;
@@ -1032,7 +1028,7 @@ __device__ inline void dma2_epilogue(f32x4_t (&acc)[MI][NI], void* __restrict__ 
         const int64_t ld = EPI == kEpiPartial ? (int64_t)N : ldc;
         float* C = (float*)Cv + (EPI == kEpiPartial ? (int64_t)split * M * (int64_t)N : 0);
         const bool vec = (ld & 3) == 0 && ((uintptr_t)C & 15) == 0;
-        if (vec && cbase + TN <= N) {
+        if (__builtin_expect(vec && cbase + TN <= N, 1)) {
             // Every column of the wave's blocks exists (the same answer in every lane): straight-line code, no
             // wait between the writes.  Accumulating: all reads of 32 rows go out before their first write
             // (the compiler may not move a read of C across a write to C; read and written quad by quad, every

@@ -199,7 +199,8 @@ def test_gemm_swiglu_resident_and_three_stage_tiles(rpo, M, F, K):
 @pytest.mark.parametrize("cpad", [8, 4, 1])
 @pytest.mark.parametrize("M,N,K,epi,path", [
     (257, 528, 192, 0, 17), (300, 1003, 128, 0, 17), (140, 400, 256, 0, 27), (700, 1056, 192, 2, 17), (129, 520, 192, 1, 27),
-    (600, 2112, 192, 3, 17), (600, 2112, 192, 3, 27), (600, 2112, 192, 3, 29), (200, 2112, 256, 3, 30), (90, 37888, 256, 3, 0)])
+    (600, 2112, 192, 3, 17), (600, 2112, 192, 3, 27), (600, 2112, 192, 3, 29), (200, 2112, 256, 3, 30), (90, 37888, 256, 3, 0),
+    (200, 2112, 192, 3, 19), (257, 530, 192, 0, 19)])
 def test_gemm_wide_tiles_column_ends_and_row_strides(rpo, M, N, K, epi, path, cpad):
     """The 16-byte stores of two neighbouring 16-column blocks and what stands in for them: columns that end inside
     a block, inside a pair of blocks or between them, row strides that are no multiple of 16 or of 8 bytes."""
