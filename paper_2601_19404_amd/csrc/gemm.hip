@@ -1483,6 +1483,23 @@ TileCfg wide_tile(const GemmArgs& a) {
     return TileCfg{kKidGemm256, 256, 256};
 }
 
+// Whether a deep K split over wide tiles is cheaper than 128x128 tiles, which hold the chunk in one round (two workgroups on
+// some CUs).  A slab of 64 values of K takes a round of 256x192 tiles about 1.16 us and one of 256x256 tiles 1.45, a
+// round of 128x128 tiles 0.5 (half a chip) to 0.63 (all of it) with one and 0.93 with two workgroups per CU; a K split adds
+// its reduction, about 10 us and the partial sums written and read at 4.6 TB/s.  us, wide (split) / 128x128: N = 1536, K = 8960: 700 rows 55.9 / 39.5, 900
+// rows 45.0 / 47.3, 1536 rows 80.9 / 78.3, 2500 rows 105 / 84; N = 3584, K = 18944: 648 rows 164 / 150, 1280 rows 247 / 259, 2100 rows
+// 331 / 281; N = 5120, K = 17408: 900 rows 237 / 256, 1024 rows 247 / 306.
+bool chunk_splits_wide(const GemmArgs& a, int splits) {
+    if (splits == 1 || a.K <= 4096) return false;
+    const auto reduction = [&](int s) { return s == 1 ? 0. : 10. + (double)s * a.M * a.N * 8. / 4.6e6; };
+    const int slabs = a.K / kBK;
+    const TileCfg w = wide_tile(a), n{kKidGemm128, 128, 128};
+    const double wide = (double)ceil_div(ceil_div(a.M, w.bm) * ceil_div(a.N, w.bn) * splits, 256) * ceil_div(slabs, splits) *
+                            (w.bn == 192 ? 1.16 : 1.45) + reduction(splits);
+    const int s128 = pick_splits(a, n), items = ceil_div(a.M, 128) * ceil_div(a.N, 128) * s128;
+    return wide < ceil_div(slabs, s128) * (items <= 256 ? 0.40 + 0.23 * items / 256. : 0.93) + reduction(s128);
+}
+
 TileCfg pick_tile(const GemmArgs& a) {
     if (a.path >= 16) {  // tuning aid: a fixed tile shape
         switch (a.path - 16) {
@@ -1536,21 +1553,19 @@ TileCfg pick_tile(const GemmArgs& a) {
     if (a.epilogue == kEpiSwiglu && a.M > 64 && a.M <= 128 && t256 >= 128) return TileCfg{kKidGemm128, 128, 128};
     // QKV, O and down of chunks of up to a few thousand rows: 256-row tiles leave most CUs idle there, and a K split of few
     // tiles pays for its partial sums and a reduction.  64x64 tiles while two workgroups per CU hold them all, else
-    // 128x128 tiles while those do; a deep K stays with 256x192 tiles where their K splits come out at one workgroup per
-    // CU.  us, 256x192 tiles (split) -> now: N = 2048, K = 1536: 700 rows 29.3 -> 12.5, 1300 rows 30.1 -> 18.4, 2500 rows 53 -> 27;
-    // N = K = 1536 (accumulating): 1060 rows 30.9 -> 15.5, 2500 rows 39.5 -> 24.5; N = 1536, K = 8960: 700 rows 55.9 -> 39.5, 2500
-    // rows 105 -> 84 (900 rows 45.0 stays: 47.3; 1536 rows 82.7 -> 86.1); N = 4608, K = 3584: 700 rows 64.6 -> 37.2, 1536 rows 69.8
-    // -> 59 (1800 rows 69 stays: 540 tiles, 90); N = 3584, K = 18944: 700 rows 165 -> 154, 2100 rows 331 -> 281.
+    // 128x128 tiles while those do, unless a deep K split over wide tiles is the cheaper (chunk_splits_wide).  us, 256x192
+    // tiles (split) -> now: N = 2048, K = 1536: 700 rows 29.3 -> 12.5, 1300 rows 30.1 -> 18.4, 2500 rows 53 -> 27;
+    // N = K = 1536 (accumulating): 1060 rows 30.9 -> 15.5, 2500 rows 39.5 -> 24.5; N = 4608, K = 3584: 700 rows 64.6 -> 37.2, 1536
+    // rows 69.8 -> 59 (1800 rows 69 stays: 540 tiles, 90).
     if (a.M > 512 && (a.epilogue == kEpiStore || a.epilogue == kEpiAddF32) && a.K % kBK == 0 && a.path != 2) {
-        const TileCfg wide = wide_tile(a);
         const int64_t t64 = (int64_t)ceil_div(a.M, 64) * ceil_div(a.N, 64), t128 = (int64_t)ceil_div(a.M, 128) * ceil_div(a.N, 128);
-        const int splits = pick_splits(a, wide), fit = ceil_div(a.M, wide.bm) * ceil_div(a.N, wide.bn) * splits;
+        const int splits = pick_splits(a, wide_tile(a));
         // A QKV projection rotates the fp32 sums where it fits a round of one-head tiles, and where the split's reduction
         // did (the separate rotary kernel rounds them to bf16 first).
         if (a.rope && rope_direct(a) && (t128 <= 256 || splits > 1)) return TileCfg{kKidGemm32, 32, 128};
         if (!a.rope || splits == 1) {
             if (a.K <= 4096 && t64 <= 512) return TileCfg{kKidGemm64x64, 64, 64};
-            if (t128 <= 512 && !(a.K > 4096 && fit >= 250 && fit <= 256)) return TileCfg{kKidGemm128, 128, 128};
+            if (t128 <= 512 && !chunk_splits_wide(a, splits)) return TileCfg{kKidGemm128, 128, 128};
         }
     }
     if (a.M > 512 || (a.M > 64 && t256 >= 128)) {

@@ -36,3 +36,14 @@ def test_weights_that_the_caches_hold_carry_no_hint(M, N, K, turn_mb, weights_pa
     """Weights that come round again before the caches have lost them (a matrix used over and over, a small model) are
     asked for as usual: with the non-temporal hint a decode step of a model of 90 MB took 1.1 times as long."""
     assert rpo.rpo_gemm_plan(M, N, K, rpo.RPO_BF16, 0, 0, turn_mb << 20)["weights_pass"] == weights_pass
+
+
+@pytest.mark.parametrize("M,N,K,kernel,splits", [
+    (900, 5120, 17408, "gemm256x192", 3), (1024, 5120, 17408, "gemm256x192", 3), (1280, 3584, 18944, "gemm256x192", 3),
+    (900, 1536, 8960, "gemm256x192", 8), (700, 1536, 8960, "gemm128", 3), (2500, 1536, 8960, "gemm128", 1),
+    (1920, 3584, 18944, "gemm128", 1), (648, 3584, 18944, "gemm128", 1), (1024, 4096, 4096, "gemm128", 1), (4200, 5120, 17408, "gemm256x192", 1)])
+def test_deep_chunks_split_k_over_wide_tiles_where_that_is_cheaper(M, N, K, kernel, splits):
+    """1024 x 5120 x 17408 took 304 us on 128x128 tiles, two of them on some CUs, against 247 in three K ranges."""
+    for epilogue in (0, 2):
+        plan = rpo.rpo_gemm_plan(M, N, K, rpo.RPO_BF16, epilogue, 96 << 20)
+        assert (plan["kernel"], plan["splits"]) == (kernel, splits)
