@@ -126,7 +126,7 @@ __device__ inline uint64_t last_lane(uint64_t v) {
 
 // Four consecutive logits starting at i (values beyond V read as -inf); one 16-byte load when
 // the row allows it.
-// ONCE: with the non-temporal hint, for logits that nobody reads again.
+// ONCE: with the non-temporal hint, for logits that no cache would keep for another read.
 template <bool ONCE = false>
 __device__ inline float4 load4(const float* z, int i, int V, bool vec) {
     typedef float f32x4_t __attribute__((ext_vector_type(4)));
@@ -296,9 +296,14 @@ hipError_t launch_sample(const SampleArgs& a, hipStream_t s) {
     if (a.n_out_rows <= 0) return hipSuccess;
     if (a.vocab > kSegLen * kMaxSeg) return hipErrorInvalidValue;
     // up to ~4 rows per CU: 16 waves per row (the sweep is ALU work, 24 instructions per logit)
-    // From a block of logits that the memory-side cache would not hold anyway (256 MB) every row is read once, but for the
-    // chosen segment: 151936 logits, 512 rows 66.4 -> 60.6 us, 256 rows 38.1 -> 36.5; 64 rows would be 29.1 -> 30.4.
-    const bool once = !a.row_map && a.n_out_rows >= 256;
+    // The non-temporal hint for logits that the memory-side cache (256 MB) would not keep for the draw anyway.  With the row
+    // maxima given a row is read once, but for the chosen segment; without them it is read for its maximum first, and
+    // the line lies higher.  us, plain / with the hint, a decode step of one thin layer and its draw: 256 rows of 151936 (148
+    // MB) 132 / 145, 768 of 64000 (188 MB) 157 / 163, 512 of 100000 (195 MB) 163 / 172, 448 of 151936 (260 MB) 195 / 188, 512
+    // (297 MB) 228 / 209, 1024 (594 MB) 441 / 397; the draw alone without maxima: 512 of 151936 98.8 / 103, 1024 of 100000 (391 MB)
+    // 130 / 128, 1024 of 151936 197 / 188.
+    const int64_t bytes = (int64_t)a.n_out_rows * a.vocab * 4;
+    const bool once = !a.row_map && bytes >= (a.row_max ? (int64_t)256 << 20 : (int64_t)384 << 20);
     if (a.n_out_rows <= 1024) {
         if (once)
             sample_kernel<16, true><<<a.n_out_rows, 1024, 0, s>>>(a);

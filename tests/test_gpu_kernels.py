@@ -302,6 +302,25 @@ def test_sampler_bit_exact(rpo, vocab, rows, temperature):
     assert tok.cpu().numpy()[1] == vocab - 1 if rows > 1 else True
 
 
+@pytest.mark.parametrize("vocab,rows,with_max", [
+    (151936, 512, True), (151936, 768, False),    # logits that no cache holds: 16 waves per row, with and without the maxima
+    (131077, 600, True), (131077, 800, False),    # the same with rows that are not 16-byte aligned
+    (65540, 1100, True), (98304, 1100, False),    # four waves per row
+    (2100, 300, True), (1003, 1030, True)])       # as many rows of a small vocabulary
+def test_sampler_bit_exact_many_rows(rpo, vocab, rows, with_max):
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    zd = torch.randn(rows, vocab, device="cuda", generator=g) * 1.5
+    seq = np.arange(7, 7 + rows).astype(np.uint64)
+    tok = torch.empty(rows, dtype=torch.int32, device="cuda")
+    lp = torch.empty(rows, dtype=torch.float32, device="cuda")
+    rpo.rpo_sample(zd, rows, vocab, vocab, None, rows, 0.9, 99, torch.from_numpy(seq.astype(np.int64)).cuda(), 6, tok, lp,
+                   row_max_dev=zd.max(dim=1).values.contiguous() if with_max else None)
+    pick = np.unique(np.linspace(0, rows - 1, 24).astype(np.int64))
+    otok, olp = osampler.sample(zd[torch.from_numpy(pick).cuda()].cpu().numpy(), 0.9, 99, seq[pick], 6)
+    np.testing.assert_array_equal(tok.cpu().numpy()[pick], otok)
+    np.testing.assert_allclose(lp.cpu().numpy()[pick], olp, atol=1e-4)
+
+
 @pytest.mark.parametrize("vocab", [1, 255, 1024, 1025, 4096, 4097, 262144])   # segments of 1024, four per lane
 def test_sampler_segments_and_tiny_weights(rpo, vocab):
     """Flat rows spread the draws over every segment; the lower half of the rows lies around the smallest weights
