@@ -1500,7 +1500,20 @@ bool chunk_splits_wide(const GemmArgs& a, int splits) {
     return wide < ceil_div(slabs, s128) * (items <= 256 ? 0.40 + 0.23 * items / 256. : 0.93) + reduction(s128);
 }
 
+// An LM head whose row maxima are asked for, 33 to 64 rows: whether the 128x256 tile takes it, else the few-row kernel.  A decode
+// step of one thin layer, few-row kernel / tile, us: N = 151936, K = 3584, 33 / 48 / 64 rows 267 / 262, 288 / 270, 306 / 277; K = 1536
+// 140 / 141, 152 / 148, 158 / 152; K = 1024 104 / 109, 112 / 114, 117 / 117; N = 128256, K = 5120 338 / 294, 367 / 306, 388 / 317; N = 50304,
+// K = 3584 125 / 113, 137 / 118, 149 / 124.  Fewer tiles than three quarters of the CUs lose (N = 32000, K = 3584, 64 rows 105 / 120),
+// and so do most rows of a multiple of 4 KB, which the tile's loads find on the same few channels (N = 151936, K = 2048 168 /
+// 202, 181 / 208, 189 / 214; N = 65536, K = 4096 144 / 175, 159 / 180, 172 / 185).
+bool lm_head_takes_tile(const GemmArgs& a) {
+    return a.block_max && a.path == 0 && a.epilogue == kEpiStoreF32 && a.M > (a.K > 2048 ? 32 : 40) && a.M <= 64 && a.K >= 1536 &&
+           a.K % 2048 != 0 && ceil_div(a.N, 256) >= 192 && dma2_ok(a, 1, 3) && a.N % 4 == 0 && a.ldc % 4 == 0 &&
+           (uintptr_t)a.C % 16 == 0;
+}
+
 TileCfg pick_tile(const GemmArgs& a) {
+    if (lm_head_takes_tile(a)) return TileCfg{kKidGemm256, 256, 256};
     if (a.path >= 16) {  // tuning aid: a fixed tile shape
         switch (a.path - 16) {
             case kKidGemm256: return TileCfg{kKidGemm256, 256, 256};
@@ -1634,6 +1647,7 @@ bool skinny_ok(const GemmArgs& a) {
         (uint64_t)a.M * (uint64_t)a.lda * sizeof(bf16) >= (1ull << 32))
         return false;
     if (a.M > kSkinnyRows) return gemm_skinny_groups(a) > 0;
+    if (a.block_max) return !lm_head_takes_tile(a);
     const bool tiles_split_k = a.ws && a.ws_bytes && pick_splits(a, pick_tile(a)) > 1;
     return gemm_skinny_takes(a, tiles_split_k);
 }
@@ -2010,7 +2024,7 @@ static hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s) {
         }
         if (a.block_max && gemm_fuses_max(a) > 0) {
             a.block_max->blocks = gemm_fuses_max(a);
-            // One row of tiles reads every weight row once; up to 128 rows would leave half of a 256-row tile empty.  A
+            // One row of tiles reads every weight row once; 33 to 128 rows would leave half of a 256-row tile empty.  A
             // decode step of one layer, us: N = 152064, K = 3584, 72 / 128 rows 375 / 407 -> 288 / 327, 256 rows 497 -> 450; N = 151936,
             // K = 1536, 72 / 128 rows 203 / 218 -> 163 / 175, 256 rows 261 -> 236.
             const bool pass = gemm_weights_pass(a);

@@ -503,7 +503,6 @@ int gemm_skinny_splits(const GemmArgs& a) {
 // Where the tiles of gemm.hip are the faster ones, up to 64 rows.  All figures us with the weights from HBM, tiles
 // against this kernel.
 bool gemm_skinny_takes(const GemmArgs& a, bool tiles_split_k) {
-    if (a.block_max) return true;  // the tile that knows the row maxima is 256 rows tall (64 x 151936 x 3584: 294, 244)
     const bool few = a.M <= 16, some = a.M <= 32;
     // A K split that goes through memory: from 33 rows on the tiles feed a deep K better (N = 3584, K = 18944, 32 / 64
     // rows: 30.6, 29.8 / 31.7, 34.6; N = 4096, K = 12288, 64 rows: 27.2, 26.5; N = 8192, K = 28672, 32 rows: 86, 91;

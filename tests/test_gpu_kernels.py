@@ -689,6 +689,36 @@ def test_lm_head_row_maxima_on_every_tile(rpo, rows, d_model, vocab):
     assert float((a - b)[:rows].abs().max()) <= 1e-5 * float(b[:rows].abs().max())      # fp32 sums in another order
 
 
+@pytest.mark.parametrize("d_model,vocab,rows,tile", [
+    (1536, 49156, 41, True), (1536, 49156, 64, True), (2112, 49156, 33, True), (1536, 49156, 40, False), (1536, 48896, 64, False),
+    (2048, 49156, 64, False), (1472, 49156, 64, False), (1536, 49154, 64, False)])
+def test_lm_head_of_few_rows_takes_the_faster_kernel(rpo, d_model, vocab, rows, tile):
+    """33 to 64 rows: the 128x256 tile for a large vocabulary and a K that is neither small nor a multiple of 2048 (64 rows
+    of 152064 x 3584: 306 us in the few-row kernel, 277 so)."""
+    mcfg = synth.ModelCfg("lm-few", 1, d_model, 2, 1, 128, 256, vocab, "bf16")
+    model = rpo.rpo_model_create(mcfg, synth.make_weights(mcfg, seed=4, device="cuda"))
+    rng = np.random.default_rng(rows)
+    toks = torch.from_numpy(rng.integers(0, vocab, size=16 * 5).astype(np.int32)).cuda()
+    step = torch.from_numpy(rng.integers(0, vocab, size=64).astype(np.int32)).cuda()
+    rpo.rpo_set_kernel_path(0)
+    out = []
+    for with_max in (True, False):
+        batch = rpo.rpo_batch_create(model, 16, 4, 5, 2, 64, 128)
+        rpo.rpo_prefill_prefix(batch, toks, (np.arange(17) * 5).astype(np.int32), torch.empty(16, vocab, device="cuda"))
+        rpo.rpo_kv_fork(batch)
+        logits = torch.full((64, vocab), 3.0, device="cuda")
+        row_max = torch.full((64,), -7.0, device="cuda")
+        rpo.rpo_profile_start(rpo.KERNEL_IDS["gemm256"], 1)
+        rpo.rpo_decode_step(batch, step, rows, None, logits, None, row_max if with_max else None)
+        n = rpo.rpo_profile_stop(rpo.KERNEL_IDS["gemm256"])[0]
+        assert n == (1 if with_max and tile else 0)
+        out.append((logits.cpu(), row_max.cpu()))
+    a, b = out[0][0], out[1][0]
+    assert torch.equal(out[0][1][:rows], a[:rows].max(dim=1).values)
+    assert bool((out[0][1][rows:] == -7.0).all()) and bool((a[rows:] == 3.0).all())
+    assert float((a - b)[:rows].abs().max()) <= 1e-5 * float(b[:rows].abs().max())      # fp32 sums in another order
+
+
 @pytest.mark.parametrize("head_dim", [2, 10, 16, 24, 32, 48, 64, 80, 200, 256])
 def test_attn_generic_head_dims(rpo, head_dim):
     """The vector-ALU attention: four, two and one group of lanes, up to four channels a lane, heads that are and are
