@@ -25,8 +25,6 @@
 // before), the same shapes, 8 / 30 / 64 rows: QKV 4.4 / 5.6 / 7.0 -> 3.8 / 4.9 / 6.4, gate/up 12.4 / 13.8 / 15.9 -> 11.0 / 12.7 /
 // 14.9, down 11.9 / 12.9 / 14.5 -> 10.9 / 12.1 / 14.4; O (K = 3584) 7.7 / 9.9 / 13.2 -> 6.9 / 9.2 / 12.4; gate/up (N = 37888) 48.2 /
 // 51.6 / 57.7 -> 42.7 / 46.9 / 54.6 (6.4 TB/s); LM head (N = 151936, K = 1536) 85.4 / 97.5 / 114 -> 73.0 / 89.8 / 111.
-#include <type_traits>
-
 #include "kernels.hpp"
 
 namespace rpo {
@@ -71,22 +69,18 @@ __device__ inline void wait_loads() {  // all but the newest N loads of this wav
 //   otherwise:  16 (NB blockIdx.x + t) ..
 // kEpiPartial: workgroup (b, z) multiplies K slabs [z slabs_per_split, ...) only and stores fp32 partial sums to
 // Cv[z][M][N] (ldc is not used).
-template <int MA, int NB, int NW, int S, int EPI, bool GROUPS>
+template <int MA, int NB, int NW, int S, int EPI, bool GROUPS, bool ONCE>
 __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __restrict__ A, int64_t lda,
                                                               const bf16* __restrict__ W, int64_t ldw,
                                                               void* __restrict__ Cv, int64_t ldc, int M, int N,
                                                               int K, int slabs_per_split, int blocks,
-                                                              int row_groups, int weights_pass, RopeKvArgs rk, LseFuse lf,
-                                                              NormFuse nf) {
+                                                              int row_groups, RopeKvArgs rk, LseFuse lf, NormFuse nf) {
     static_assert(EPI != kEpiLogitsMax || NB == 4, "row maxima are kept per 64 columns");
     constexpr int MB = (MA + 1) / 2;  // 16-column MFMA blocks of activations (MA = 1: rows 0 .. 7 twice)
     constexpr int ROWS = MB * 16, COLS = NB * 16;
     constexpr int LD = COLS + 4;      // fp32 row of the partial sums, 16-byte pieces
     constexpr int INST = 2 * NB + MA;  // loads per slab; each fills 1 KiB of LDS (8 rows x 128 bytes)
     constexpr int STAGE = INST * 1024;
-    // One workgroup reads a weight row: with weights that come from HBM (weights_pass) the hint takes 8 / 30 rows of K = 3584,
-    // N = 37888 from 48.1 to 42.7 / 51.5 to 46.9 us = 6.4 / 5.8 TB/s.  Not where 64 rows of activations, read by every workgroup, outweigh them (down, K = 8960: 14.5 -> 14.9 us).
-    constexpr bool kOnce = !GROUPS && !(EPI == kEpiPartial && MA == 8);
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // rings [NW][S][STAGE], then partial sums
     float* part = (float*)smem;                                          // [NW][ROWS][LD]
 
@@ -148,19 +142,13 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const bf16* __rest
         sl += slab0;
         const bf16* wb = W + sl * 64;
         const bf16* ab = A + sl * 64;
-        auto loads = [&](auto once) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < INST; ++j) {
-                if (j < 2 * NB)
-                    dma_load16_at<decltype(once)::value>(wb, off[j], ring + st * STAGE, j * 1024);
-                else
-                    dma_load16_at<false>(ab, off[j], ring + st * STAGE, j * 1024);
-            }
-        };
-        if (kOnce && weights_pass)  // uniform
-            loads(std::true_type{});
-        else
-            loads(std::false_type{});
+        for (int j = 0; j < INST; ++j) {
+            if (j < 2 * NB)
+                dma_load16_at<ONCE>(wb, off[j], ring + st * STAGE, j * 1024);
+            else
+                dma_load16_at<false>(ab, off[j], ring + st * STAGE, j * 1024);
+        }
     };
     const int sw = r & 7;
     const int ar = MA == 1 ? (r & 7) : r;
@@ -392,14 +380,14 @@ constexpr size_t skinny_lds() {
 }
 
 // PER_CU workgroups share a CU's 160 KiB of LDS; the ring is as deep as that allows, at most four slabs.
-template <int MA, int NB, int NW, int PER_CU, int EPI, bool GROUPS = false>
-hipError_t launch_one(const GemmArgs& a, int blocks, hipStream_t s, int splits = 1, void* out = nullptr) {
+template <int MA, int NB, int NW, int PER_CU, int EPI, bool GROUPS, bool ONCE>
+hipError_t launch_kernel(const GemmArgs& a, int blocks, hipStream_t s, int splits, void* out) {
     constexpr int kFit = 160 / PER_CU / (NW * (2 * NB + MA));
     constexpr int S = kFit < 4 ? kFit : 4;
     static_assert(S >= 2, "the ring needs two slabs");
     constexpr size_t lds = skinny_lds<MA, NB, NW, S>();
     static_assert(lds * PER_CU <= 160 * 1024, "LDS");
-    auto kern = gemm_skinny_kernel<MA, NB, NW, S, EPI, GROUPS>;
+    auto kern = gemm_skinny_kernel<MA, NB, NW, S, EPI, GROUPS, ONCE>;
     static bool attr_set = false;  // one flag per template instance
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -410,11 +398,21 @@ hipError_t launch_one(const GemmArgs& a, int blocks, hipStream_t s, int splits =
     const int grid = GROUPS ? ceil_div(blocks, 8) * 8 * row_groups : blocks;
     kern<<<dim3((unsigned)grid, (unsigned)splits), dim3(NW * 64), lds, s>>>(
         (const bf16*)a.A, a.lda, (const bf16*)a.W, a.ldw, out ? out : a.C, a.ldc, a.M, a.N, a.K,
-        ceil_div(a.K / 64, splits), blocks, row_groups, gemm_weights_pass(a) ? 1 : 0,
+        ceil_div(a.K / 64, splits), blocks, row_groups,
         (EPI == kEpiRope && a.rope) ? *a.rope : RopeKvArgs{},
         (EPI == kEpiLogitsMax && a.block_max) ? *a.block_max : LseFuse{},
         (EPI == kEpiAddF32 && a.norm_split) ? *a.norm_split : (EPI == kEpiSwiglu && a.norm_in) ? *a.norm_in : NormFuse{});
     return hipGetLastError();
+}
+
+// One workgroup reads a weight row: weights from HBM come with the non-temporal hint (8 / 30 rows of K = 3584, N = 37888 48.1
+// -> 42.7 / 51.5 -> 46.9 us = 6.4 / 5.8 TB/s).  Not where 64 rows of activations, read by every workgroup, outweigh them
+// (down, K = 8960: 14.5 -> 14.9 us).  A kernel of its own: both kinds of load in one cost 0.1 us a launch.
+template <int MA, int NB, int NW, int PER_CU, int EPI, bool GROUPS = false>
+hipError_t launch_one(const GemmArgs& a, int blocks, hipStream_t s, int splits = 1, void* out = nullptr) {
+    if constexpr (!GROUPS && !(EPI == kEpiPartial && MA == 8))
+        if (gemm_weights_pass(a)) return launch_kernel<MA, NB, NW, PER_CU, EPI, GROUPS, true>(a, blocks, s, splits, out);
+    return launch_kernel<MA, NB, NW, PER_CU, EPI, GROUPS, false>(a, blocks, s, splits, out);
 }
 
 template <int MA, int EPI>
@@ -539,7 +537,7 @@ bool gemm_skinny_splits_norm(const GemmArgs& a) {
 
 hipError_t gemm_skinny_load_kernels() {
     hipFuncAttributes attr;
-    return hipFuncGetAttributes(&attr, (const void*)gemm_skinny_kernel<1, 1, 8, 4, kEpiStore, false>);
+    return hipFuncGetAttributes(&attr, (const void*)gemm_skinny_kernel<1, 1, 8, 4, kEpiStore, false, false>);
 }
 
 hipError_t launch_gemm_skinny(const GemmArgs& a, int epi, int splits, hipStream_t s) {
