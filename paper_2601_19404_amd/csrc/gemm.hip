@@ -5,11 +5,11 @@
 //    (v_mfma_f32_32x32x16_bf16; in gemm_dma2_kernel v_mfma_f32_16x16x32_bf16).  64-deep K slabs go from global memory straight into LDS
 //    (global_load_lds_dwordx4), two to four stages deep; fragments are double-buffered in registers.
 //    Tile shapes and what they are for (pick_tile): 256x256 (many-tile problems: prefill / log-prob
-//    chunks, wide decode projections), 256x192 / 256x160 (large M with a narrow N, decode gate/up), 128x256 (LM head of up
-//    to 128 rows), 128x128 and 64x128 (deep-K decode projections, split along K: the fp32 partial sums go to a
-//    workspace and a reduction kernel applies the epilogue -- deterministic, no floating-point
-//    atomics; chunks of up to a few thousand rows, unsplit), 64x64 and 32x128 (shallow-K decode projections and small
-//    chunks, no K split).
+//    chunks, wide decode projections), 256x192 / 256x160 (large M with a narrow N, decode gate/up), 128x160 (decode
+//    gate/up), 128x256 (LM head of 33 to 128 rows), 128x128 and 64x128 (deep-K decode projections and chunks of up to a few
+//    thousand rows, split along K where their tiles are too few for the chip: the fp32 partial sums go to a workspace
+//    and a reduction kernel applies the epilogue -- deterministic, no floating-point atomics), 64x64 and 32x128
+//    (shallow-K decode projections and small chunks, no K split).
 //    (tile, K-split) work items are dealt evenly to the 8 XCDs, neighbouring tiles to the same XCD
 //    (each has its own L2).  The wide two-stage tiles run on gemm_dma2_kernel: fragment reads and loads are
 //    spread between the MFMAs of a k-step (the matrix pipe never waits behind a burst of memory
@@ -18,10 +18,10 @@
 //    launch has many rounds of tiles one resident workgroup per CU walks its share of them, the
 //    next tile's first loads in flight during the epilogue.
 //  * Epilogues ride on the accumulators: residual add, SwiGLU (the kernel reads the weight rows
-//    in the order [32 gate | 32 up | 32 gate | ...], so a wave holds matching gate and up
-//    columns), rotary embedding + KV page write (QKV projection of a decode step), log-sum-exp
-//    and row maxima (LM head).  All but the rotary one and the plain bf16 store multiply with
-//    the MFMA operands swapped, which leaves a lane with one row and runs of four columns.
+//    in the order [32 gate | 32 up | 32 gate | ...], the 160- and 192-wide tiles by 16, so a wave holds matching
+//    gate and up columns), rotary embedding + KV page write (QKV projection of a decode step and of small chunks),
+//    log-sum-exp and row maxima (LM head).  All but the rotary one and the plain bf16 store of the narrow tiles
+//    multiply with the MFMA operands swapped, which leaves a lane with one row and runs of four columns.
 //  * gemm_mfma_kernel: the same tiling with register-staged LDS fills, for K that is not a
 //    multiple of 64 (and selectable for comparison).
 //  * skinny.hip: up to 64 rows, and narrow projections of up to 512 in groups of 64, K a multiple of 64 (the rules
@@ -227,42 +227,11 @@ __device__ inline void gemm_epilogue(f32x16_t (&acc)[MI][NI], void* __restrict__
 // Epilogue for accumulators computed with the MFMA operands swapped (the direct-to-LDS kernel): lane l
 // holds ROW (l % 32) of each 32x32 block and, per register quad q, the four consecutive columns
 // 8 q + 4 (l / 32) .. + 3 -- so the result leaves in 16-byte (fp32) or 8-byte (bf16) pieces.
-template <int MI, int NI, int TM, int TN, int EPI, int SW>
+template <int MI, int NI, int TM, int TN, int EPI>
 __device__ inline void gemm_epilogue_t(f32x16_t (&acc)[MI][NI], void* __restrict__ Cv, int64_t ldc, int M, int N,
                                        int m0, int n0, int wm, int wn, int lane, int split) {
     typedef unsigned short u16x4_t __attribute__((ext_vector_type(4)));
     const int r_in = lane & 31, c_in = (lane >> 5) * 4;
-    if (EPI == kEpiSwiglu && SW == 2) {
-        // gate and up of output column (block's virtual column)/2 + 8 q + column-in-quad sit in
-        // registers 4 q + t and 4 (q + 2) + t of the same block (q = 0, 1)
-        bf16* C = (bf16*)Cv;
-        const bool vec = (ldc & 3) == 0 && ((uintptr_t)Cv & 7) == 0;
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-            const int gm = m0 + wm * TM + i * 32 + r_in;
-            if (gm >= M) continue;
-#pragma unroll
-            for (int j = 0; j < NI; ++j) {
-                const int vn = n0 + wn * TN + j * 32;
-                if (vn >= N) continue;  // N = 2F is a multiple of 32: blocks are whole
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    u16x4_t o;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        o[t] = f32_to_bf16(silu_f(acc[i][j][4 * q + t]) * acc[i][j][4 * (q + 2) + t]).bits;
-                    bf16* dst = C + (int64_t)gm * ldc + (vn >> 1) + 8 * q + c_in;
-                    if (vec) {
-                        *(u16x4_t*)dst = o;
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) dst[t].bits = o[t];
-                    }
-                }
-            }
-        }
-        return;
-    }
     if (EPI == kEpiSwiglu) {
         // blocks (j, j + 1) = (gate, up) of output columns (n0 + wn*TN + j*32)/2 + column in block
         bf16* C = (bf16*)Cv;
@@ -291,33 +260,6 @@ __device__ inline void gemm_epilogue_t(f32x16_t (&acc)[MI][NI], void* __restrict
                     }
                 }
             }
-        }
-        return;
-    }
-    if (EPI == kEpiStore) {
-        bf16* C = (bf16*)Cv;
-        const bool vec = (ldc & 3) == 0 && ((uintptr_t)Cv & 7) == 0;
-#pragma unroll
-        for (int i = 0; i < MI; ++i) {
-            const int gm = m0 + wm * TM + i * 32 + r_in;
-            if (gm >= M) continue;
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int gn = n0 + wn * TN + j * 32 + 8 * q + c_in;
-                    bf16* dst = C + (int64_t)gm * ldc + gn;
-                    if (vec && gn + 3 < N) {
-                        u16x4_t o;
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) o[t] = f32_to_bf16(acc[i][j][4 * q + t]).bits;
-                        *(u16x4_t*)dst = o;
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < 4; ++t)
-                            if (gn + t < N) dst[t] = f32_to_bf16(acc[i][j][4 * q + t]);
-                    }
-                }
         }
         return;
     }
@@ -414,9 +356,8 @@ constexpr int kDmaBK = 64, kDmaStages = 2;
 // Column n of the (virtual) output -> row of W.  SwiGLU mode interleaves gate and up rows
 // in blocks of 32: virtual columns [64q, 64q+32) are gate rows 32q.., [64q+32, 64q+64) up rows.
 // Mode 2 interleaves in blocks of 16 instead (virtual columns [32q, 32q+16) are gate rows 16q..,
-// [32q+16, 32q+32) up rows): with the transposed accumulators a lane then holds the gate and the
-// up value of an output in one 32x32 block (registers 4 q + t and 4 (q + 2) + t), whatever the
-// number of blocks per wave.
+// [32q+16, 32q+32) up rows): a lane of gemm_dma2_kernel then holds the gate and the up value of an
+// output in neighbouring 16-column blocks, for any even number of blocks per wave.
 template <int SWIGLU>
 __device__ inline int weight_row(int n, int F) {
     if (SWIGLU == 0) return n;
@@ -859,7 +800,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_dma_kernel(const bf16* __res
         }
     } else {
         if constexpr (kTrans)
-            gemm_epilogue_t<MI, NI, TM, TN, EPI, SWIGLU>(acc, Cv, ldc, M, N, m0, n0, wm, wn, lane, tc.split);
+            gemm_epilogue_t<MI, NI, TM, TN, EPI>(acc, Cv, ldc, M, N, m0, n0, wm, wn, lane, tc.split);
         else
             gemm_epilogue<MI, NI, TM, TN, EPI>(acc, Cv, ldc, M, N, m0, n0, wm, wn, lane, tc.split);
     }
@@ -1035,12 +976,12 @@ __device__ inline void dma2_epilogue(f32x4_t (&acc)[MI][NI], void* __restrict__ 
             // quad would wait a full memory round trip: o-projection of an 8192-row chunk 69 -> 51 us).  The reads are
             // waited for on every path (rows beyond M read the last row): a read left pending in some lanes would
             // make the compiler wait for it, and with it for all slabs in flight, at the head of the slab loop.
-            constexpr int RB = MI % 2 == 0 ? 2 : 1;
+            static_assert(MI % 2 == 0, "two row blocks at a time");
 #pragma unroll
-            for (int i = 0; i < MI; i += RB) {
-                f32x4_t c[RB][NI];
+            for (int i = 0; i < MI; i += 2) {
+                f32x4_t c[2][NI];
 #pragma unroll
-                for (int k = 0; k < RB; ++k)
+                for (int k = 0; k < 2; ++k)
 #pragma unroll
                     for (int j = 0; j < NI; ++j) {
                         if (EPI == kEpiAddF32) {
@@ -1052,7 +993,7 @@ __device__ inline void dma2_epilogue(f32x4_t (&acc)[MI][NI], void* __restrict__ 
                     }
                 if (EPI == kEpiAddF32) {
 #pragma unroll
-                    for (int k = 0; k < RB; ++k)
+                    for (int k = 0; k < 2; ++k)
 #pragma unroll
                         for (int j = 0; j < NI; ++j) {
                             c[k][j] += acc[i + k][j];
@@ -1060,7 +1001,7 @@ __device__ inline void dma2_epilogue(f32x4_t (&acc)[MI][NI], void* __restrict__ 
                         }
                 }
 #pragma unroll
-                for (int k = 0; k < RB; ++k) {
+                for (int k = 0; k < 2; ++k) {
                     const int gm = m0 + wm * TM + (i + k) * 16 + r_in;
                     if (gm >= M) continue;
 #pragma unroll
