@@ -1914,6 +1914,7 @@ static hipError_t launch_gemm_rows(const GemmArgs& a, hipStream_t s);
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
+    if (a.norm_in && !gemm_takes_norm(a)) return hipErrorInvalidValue;  // A is not normalised, and no other kernel would do it
     const int rows = mfma_ok(a) ? whole_round_rows(a) : 0;
     if (rows == 0) return launch_gemm_rows(a, s);
     GemmArgs head = a, tail = a;

@@ -465,26 +465,9 @@ hipError_t gemm(rpo_batch* b, const void* A, int64_t lda, const void* W, int64_t
                 int64_t ldc, int M, int N, int K, int epi, hipStream_t s, const void* norm_gain = nullptr,
                 void* norm_out = nullptr, const RopeKvArgs* rope = nullptr, NormFuse* norm_split = nullptr,
                 const NormFuse* norm_in = nullptr) {
-    const rpo_model* m = b->m;
-    GemmArgs g;
-    g.A = A;
-    g.lda = lda;
-    g.W = W;
-    g.ldw = ldw;
-    g.C = C;
-    g.ldc = ldc;
-    g.M = M;
-    g.N = N;
-    g.K = K;
-    g.dtype = m->d.dtype;
-    g.epilogue = epi;
-    g.path = g_kernel_path;
-    g.ws = b->at<void>(b->L.gu);
-    g.ws_bytes = kSplitKBytes;
-    g.turn_bytes = m->weight_bytes();
+    GemmArgs g = gemm_args(b, A, lda, W, ldw, C, ldc, M, N, K, epi);
     g.norm_gain = norm_gain;
     g.norm_out = norm_out;
-    g.norm_eps = m->d.rms_eps;
     g.rope = rope;
     g.norm_split = norm_split;
     g.norm_in = norm_in;
