@@ -34,9 +34,11 @@ int rpo_gemm_nt(const void *a_dev, int64_t lda, const void *w_dev, int64_t ldw, 
 
 /* What rpo_gemm_nt would launch for dense, aligned operands of these sizes and ws_bytes of scratch (0: none), or a model
  * whose projections and LM head are turn_bytes long (0: a call by itself), so that tests can check the choice; runs on
- * the host alone.  plan_out, 5 values: the kernel id (as rpo_profile_start's), the K ranges whose sums go through the
+ * the host alone.  plan_out, 6 values: the kernel id (as rpo_profile_start's), the K ranges whose sums go through the
  * scratch (1: K is not split), the rows of the first of two launches (0: one launch), 1 where the generic kernel deals K
- * to the lanes of a wave (0: it works in tiles), 1 where the weights count as coming from HBM.  Errors: RPO_EINVAL. */
+ * to the lanes of a wave (0: it works in tiles), 1 where the weights count as coming from HBM, 1 where an RMSNorm between
+ * an accumulating (epilogue 2) and a SwiGLU (3) projection would be taken apart as far as this one is concerned.
+ * Errors: RPO_EINVAL. */
 int rpo_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t dtype, int32_t epilogue, size_t ws_bytes, size_t turn_bytes,
                   int32_t *plan_out);
 

@@ -405,10 +405,10 @@ def rpo_gemm_nt_noalloc(a_dev: torch.Tensor, w_dev: torch.Tensor, c_dev: torch.T
 
 def rpo_gemm_plan(M: int, N: int, K: int, dtype: int, epilogue: int, ws_bytes: int = 0, turn_bytes: int = 0) -> dict:
     """What rpo_gemm_nt would launch for dense, aligned operands of these sizes; host-only."""
-    out = (C.c_int32 * 5)()
+    out = (C.c_int32 * 6)()
     _check(lib().rpo_gemm_plan(M, N, K, dtype, epilogue, ws_bytes, turn_bytes, out))
     return dict(kernel=next(n for n, i in KERNEL_IDS.items() if i == out[0]), splits=out[1], first_rows=out[2],
-                waves=bool(out[3]), weights_pass=bool(out[4]))
+                waves=bool(out[3]), weights_pass=bool(out[4]), norm_apart=bool(out[5]))
 
 
 def rpo_set_kernel_path(path: int) -> None:

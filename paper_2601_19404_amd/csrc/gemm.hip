@@ -1900,7 +1900,14 @@ static int whole_round_rows(const GemmArgs& a) {
 }
 
 GemmPlan gemm_plan(const GemmArgs& a) {
-    GemmPlan p{gemm_kernel_id(a), 1, 0, 0, gemm_weights_pass(a) ? 1 : 0};
+    GemmPlan p{gemm_kernel_id(a), 1, 0, 0, gemm_weights_pass(a) ? 1 : 0, gemm_takes_norm(a) ? 1 : 0};
+    if (mfma_ok(a) && skinny_ok(a)) {
+        NormFuse nf;
+        GemmArgs n = a;
+        n.norm_split = &nf;
+        n.norm_gain = n.norm_out = a.C;
+        if (gemm_skinny_splits_norm(n)) p.norm_apart = 1;
+    }
     if (!mfma_ok(a)) {
         p.waves = generic_takes_waves(a) ? 1 : 0;
     } else {

@@ -175,6 +175,7 @@ struct GemmPlan {
     int first_rows;  // rows of the first of two launches, 0: one launch
     int waves;       // generic kernels: 1 for gemm_generic_wave_kernel
     int passing;     // weights asked for with the non-temporal hint (where few enough rows leave them to one reader)
+    int norm_apart;  // kEpiAddF32: leaves an RMSNorm taken apart if asked for one; kEpiSwiglu: takes one
 };
 GemmPlan gemm_plan(const GemmArgs& a);
 // Bytes of fp32 K-split partial sums launch_gemm would write for these arguments if the

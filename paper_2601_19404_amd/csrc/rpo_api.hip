@@ -1170,6 +1170,7 @@ extern "C" int rpo_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t dtype, int
     plan_out[2] = p.first_rows;
     plan_out[3] = p.waves;
     plan_out[4] = p.passing;
+    plan_out[5] = p.norm_apart;
     return RPO_OK;
 }
 

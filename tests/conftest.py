@@ -21,3 +21,12 @@ def pytest_collection_modifyitems(config, items):
     for item in items:
         if "gpu" in item.keywords:
             item.add_marker(skip)
+
+
+@pytest.fixture(autouse=True)
+def default_kernel_path(request):
+    """The switch of rpo_set_kernel_path is process-wide: every GPU test starts without a forced path, whichever test ran
+    before it (a model test would otherwise compare a forced kernel with itself)."""
+    if "gpu" in request.keywords:
+        from paper_2601_19404_amd import binding
+        binding.rpo_set_kernel_path(0)

@@ -590,8 +590,11 @@ def test_prefill_rotary_tiles(rpo, prefix_lens):
     batch = rpo.rpo_batch_create(model, 2, 1, max(prefix_lens), 1, 64, sum(prefix_lens))
     prefixes = [rng.integers(0, mcfg.vocab, size=n).astype(np.int32) for n in prefix_lens]
     last = torch.empty(2, mcfg.vocab, device="cuda")
+    rpo.rpo_profile_start(rpo.KERNEL_IDS["gemm32"], 1)
     rpo.rpo_prefill_prefix(batch, torch.from_numpy(np.concatenate(prefixes)).cuda(),
                            np.concatenate([[0], np.cumsum(prefix_lens)]).astype(np.int32), last)
+    # up to 256 tiles of 128 rows and one head; beyond (the third case) wider tiles and a rotary kernel
+    assert rpo.rpo_profile_stop(rpo.KERNEL_IDS["gemm32"])[0] == (1 if sum(prefix_lens) <= 2048 else 0)
     got = last.cpu().numpy()
     for g in range(2):
         _, ref = T.prefill(util.oracle_shape(mcfg, storage="bf16"), synth.weights_to_numpy(w), prefixes[g])
@@ -600,7 +603,8 @@ def test_prefill_rotary_tiles(rpo, prefix_lens):
         assert np.abs(got[g] - ref).max() <= 6 * 2.0 ** -8 * np.abs(ref).max()
 
 
-@pytest.mark.parametrize("M,N,K", [(4609, 3584, 5120), (5000, 3584, 6144), (11000, 1536, 8960), (11264, 1540, 8960)])
+@pytest.mark.parametrize("M,N,K", [(4609, 3584, 5120), (5000, 3584, 6144), (11000, 1536, 8960), (11264, 1540, 8960),
+                                   (4609, 3584, 8960), (4700, 3584, 18944)])
 def test_gemm_whole_rounds_and_the_rest(rpo, M, N, K):
     """Accumulating projections whose last round of 256x256 tiles is mostly empty: the remaining rows (one, a few, more
     than a tile) in a launch of their own, at the right place of A and C."""
@@ -610,6 +614,7 @@ def test_gemm_whole_rounds_and_the_rest(rpo, M, N, K):
     c0 = torch.randn(M, N + 4, generator=g, device="cuda")
     c = c0.clone()
     rpo.rpo_set_kernel_path(0)
+    assert 0 < rpo.rpo_gemm_plan(M, N, K, rpo.RPO_BF16, 2, 96 << 20)["first_rows"] < M          # two launches
     rpo.rpo_gemm_nt(a, w, c[:, :N], 2, torch.empty(96 << 20, dtype=torch.uint8, device="cuda"))
     ref = a.double() @ w.double().t()
     assert bool(((c[:, :N].double() - c0[:, :N].double() - ref).abs() <= 2e-6 * ref.abs() + 2e-5 * K ** 0.5 * 0.1).all())
@@ -618,8 +623,11 @@ def test_gemm_whole_rounds_and_the_rest(rpo, M, N, K):
 
 def test_prefill_chunk_of_whole_rounds_and_the_rest(rpo):
     """The same inside a model, where the norm of all rows follows: a prefill in one chunk (4750 rows: the down
-    projection in two launches) against chunks of one sequence, which are too small for it."""
+    projection in two launches) against chunks of one sequence, which are too small for it, and both against the oracle
+    for the last sequence, whose last rows are the second launch's."""
     mcfg = synth.ModelCfg("whole-rounds", 2, 3584, 28, 4, 128, 5120, 512, "bf16")
+    plan = [rpo.rpo_gemm_plan(rows, 3584, 5120, rpo.RPO_BF16, 2, 96 << 20)["first_rows"] for rows in (4750, 1193)]
+    assert 0 < plan[0] < 4750 and plan[1] == 0
     lens = [1190, 1187, 1180, 1193]
     rng = np.random.default_rng(5)
     w = synth.perturb_gains(synth.make_weights(mcfg, seed=5, device="cuda"))
@@ -634,6 +642,10 @@ def test_prefill_chunk_of_whole_rounds_and_the_rest(rpo):
         out.append(last.cpu())
     # two bf16 pipelines of two layers: six ulps of the logit scale (measured elsewhere up to 5.5)
     assert float((out[0] - out[1]).abs().max()) <= 6 * 2.0 ** -8 * float(out[1].abs().max())
+    ref = torch.from_numpy(T.prefill(util.oracle_shape(mcfg, storage="bf16"), synth.weights_to_numpy(w),
+                                     toks[int(cu[3]):].cpu().numpy())[1])
+    for o in out:
+        assert float((o[3].double() - ref).abs().max()) <= 6 * 2.0 ** -8 * float(ref.abs().max())
 
 
 @pytest.mark.parametrize("d_model,hq,hk,ffn", [(256, 2, 1, 320), (1536, 12, 2, 1024), (3584, 28, 4, 2080), (4096, 8, 2, 10304), (336, 2, 2, 256)])
@@ -656,10 +668,21 @@ def test_few_rows_take_the_norm_apart(rpo, d_model, hq, hk, ffn):
         return out.cpu()
 
     ref = logits(40)
+    shape, w_np, seqs = util.oracle_shape(mcfg, storage="bf16"), synth.weights_to_numpy(w), toks.cpu().numpy().reshape(20, 5)
+    exact = {}
+    for r in (0, 6, 31):
+        kv, _ = T.prefill(shape, w_np, seqs[r // 2])
+        exact[r] = torch.from_numpy(T.decode_step(shape, w_np, int(step[r]), kv))
     for rows in (1, 7, 8, 9, 16, 17, 31, 32, 33):
+        apart = all(rpo.rpo_gemm_plan(rows, *nk, rpo.RPO_BF16, epi, 96 << 20)["norm_apart"]
+                    for epi, nk in ((2, (d_model, hq * 128)), (3, (2 * ffn, d_model))))
+        assert apart == (rows <= 32 and d_model % 64 == 0 and d_model <= 4096), rows
         got = logits(rows)
         # two bf16 pipelines of two layers: six ulps of the logit scale
         assert float((got - ref)[:rows].abs().max()) <= 6 * 2.0 ** -8 * float(ref[:rows].abs().max()), rows
+        for r, x in exact.items():
+            if r < rows:
+                assert float((got[r].double() - x).abs().max()) <= 6 * 2.0 ** -8 * float(x.abs().max()), (rows, r)
 
 
 @pytest.mark.parametrize("rows", [66, 72, 128, 136, 256, 258])
@@ -696,7 +719,8 @@ def test_lm_head_of_few_rows_takes_the_faster_kernel(rpo, d_model, vocab, rows, 
     """33 to 64 rows: the 128x256 tile for a large vocabulary and a K that is neither small nor a multiple of 2048 (64 rows
     of 152064 x 3584: 306 us in the few-row kernel, 277 so)."""
     mcfg = synth.ModelCfg("lm-few", 1, d_model, 2, 1, 128, 256, vocab, "bf16")
-    model = rpo.rpo_model_create(mcfg, synth.make_weights(mcfg, seed=4, device="cuda"))
+    w = synth.make_weights(mcfg, seed=4, device="cuda")
+    model = rpo.rpo_model_create(mcfg, w)
     rng = np.random.default_rng(rows)
     toks = torch.from_numpy(rng.integers(0, vocab, size=16 * 5).astype(np.int32)).cuda()
     step = torch.from_numpy(rng.integers(0, vocab, size=64).astype(np.int32)).cuda()
@@ -717,6 +741,13 @@ def test_lm_head_of_few_rows_takes_the_faster_kernel(rpo, d_model, vocab, rows, 
     assert torch.equal(out[0][1][:rows], a[:rows].max(dim=1).values)
     assert bool((out[0][1][rows:] == -7.0).all()) and bool((a[rows:] == 3.0).all())
     assert float((a - b)[:rows].abs().max()) <= 1e-5 * float(b[:rows].abs().max())      # fp32 sums in another order
+    if tile:
+        shape, w_np = util.oracle_shape(mcfg, storage="bf16"), synth.weights_to_numpy(w)
+        for r in (0, rows - 1):
+            kv, _ = T.prefill(shape, w_np, toks.cpu().numpy().reshape(16, 5)[r // 4])
+            x = torch.from_numpy(T.decode_step(shape, w_np, int(step[r]), kv))
+            # one layer with the same bf16 roundings: six ulps of the logit scale
+            assert float((a[r].double() - x).abs().max()) <= 6 * 2.0 ** -8 * float(x.abs().max())
 
 
 @pytest.mark.parametrize("head_dim", [2, 10, 16, 24, 32, 48, 64, 80, 200, 256])
