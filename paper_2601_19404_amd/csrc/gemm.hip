@@ -1798,13 +1798,13 @@ hipError_t launch_generic(const GemmArgs& a, hipStream_t s) {
 // without the hint: up to 256 MB of them 1.05 to 1.8, from 320 MB on 0.8 to 1.0 (8 rows, N = 2048, K = 1536: 126 MB 4.14 /
 // 3.66 us, 396 MB 3.84 / 4.12).  A decode step: models of 91 MB 213 / 202 us (8 rows), 284 / 259 (64), 183 MB 62 / 60, 85 /
 // 76, 246 MB 252 / 255, 354 / 368, 362 MB 140 / 150, 188 / 202 (the logits and pages of a step pass through the cache as
-// well, hence the lower limit).  A call by itself says nothing of what is read between it and the next: its matrix alone
-// counts.  One matrix over and over, 8 / 24 / 64 rows: 32 MB 1.40 / 1.37 / 1.09, 52 MB 0.98 / 1.04 / 1.06, 62 MB 0.82 / 0.84 /
-// 1.00, 259 MB 0.97 / 1.05 / 1.09, 342 MB 0.87 / 0.90 / 1.01.
+// well, hence the lower limit).  A call by itself says nothing of what is read between it and the next, so only a matrix
+// that the cache cannot hold counts: one over and over, 1 / 8 / 64 rows, 128 MB (N = K = 8192) 0.92 / 0.93 / 1.25, 200 MB (N =
+// 5120, K = 20480) 1.30 / 1.42 / 1.41, 259 MB (N = 37888, K = 3584) 0.94 / 0.96 / 1.07, 342 MB 0.88 / 0.87 / 1.01; two or more
+// of these in turn would gain 0.84 to 1.0.
 bool gemm_weights_pass(const GemmArgs& a) {
     if (a.turn_bytes) return a.turn_bytes > (size_t)240 << 20;
-    const size_t bytes = (size_t)a.N * (size_t)a.K * sizeof(bf16);
-    return bytes > (size_t)320 << 20 || (a.M <= 16 && bytes > (size_t)48 << 20);
+    return (size_t)a.N * (size_t)a.K * sizeof(bf16) > (size_t)320 << 20;
 }
 
 bool gemm_takes_norm(const GemmArgs& a) { return a.epilogue == kEpiSwiglu && a.M <= 32 && mfma_ok(a) && skinny_ok(a); }

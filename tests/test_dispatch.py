@@ -29,7 +29,7 @@ def test_generic_bf16_goes_to_the_faster_kernel(M, N, K, waves):
 
 
 @pytest.mark.parametrize("M,N,K,turn_mb,weights_pass", [
-    (8, 2048, 1536, 0, False), (8, 4096, 4096, 0, False), (8, 32000, 1024, 0, True), (24, 37888, 3584, 0, False),
+    (8, 2048, 1536, 0, False), (8, 4096, 4096, 0, False), (8, 5120, 20480, 0, False), (24, 37888, 3584, 0, False),
     (64, 50000, 3584, 0, True),                                                                # a matrix by itself
     (8, 2048, 1536, 183, False), (8, 151936, 1536, 183, False), (64, 2048, 1536, 246, True), (100, 2048, 1536, 2600, True)])
 def test_weights_that_the_caches_hold_carry_no_hint(M, N, K, turn_mb, weights_pass):
