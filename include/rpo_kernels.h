@@ -106,14 +106,17 @@ int rpo_set_kernel_path(int path);
  * bytes; decode attention: K/V bytes with a group's shared prefix counted once per group;
  * sampler: the logits rows read once).  Kernel ids:
  * (MFMA GEMM tile shapes <BM, BN, waves along M, waves along N>)
- *   1  <256,256,2,4> (prefill-sized problems and wide decode projections), every epilogue but SwiGLU
+ *   1  <256,256,2,4> (prefill-sized problems, LM heads), every epilogue but SwiGLU; also the <128,256,2,4>
+ *      tile of an LM head of 33 to 128 rows with its row maxima
  *   12 <256,256,2,4> with the fused SwiGLU epilogue: the gate/up projection of prefill and
  *      log-prob chunks, one instantiation, the heaviest kernel of a rollout step
- *   3  <128,128,2,2> (decode-sized problems, deep K)
- *   4  <64,128,1,2> (the same for M <= 64, where kernel 15 does not take them)
- *   5  <32,128,1,4> / <64,128,1,4> (decode QKV projection of more rows than kernel 15 takes: rotary
- *      embedding and KV page write in the epilogue; 64 rows once the 32-row tiles would outnumber the CUs)
- *   6  <64,64,2,2> (decode-sized problems, shallow K, no K split)
+ *   3  <128,128,2,2> (decode-sized problems with a deep K, gate/up of 65 to 128 rows, chunks of up to a few
+ *      thousand rows)
+ *   4  <64,128,1,2> (up to 64 rows, where kernel 15 does not take them)
+ *   5  <32,128,1,4> / <64,128,1,4> / <128,128,2,2> (QKV projection of a decode step of more rows than kernel 15 takes,
+ *      and of small chunks: rotary embedding and KV page write in the epilogue, the rows of a tile such that
+ *      one round of workgroups holds them)
+ *   6  <64,64,2,2> (decode-sized problems and small chunks with a shallow K, no K split)
  *      (all epilogues of a tile shape together; a K-split launch includes its reduction)
  *   11 <256,192,4,2> (large M with a narrow N: fewer idle CUs in the last round of workgroups)
  *   13 <256,160,4,1> (gate/up projection of a decode step, where one round holds its tiles, and of a small
@@ -121,7 +124,7 @@ int rpo_set_kernel_path(int path);
  *   14 <128,160,4,1> (gate/up projection of a decode step, where one round holds its tiles)
  *   15 gemm_skinny_kernel (up to 64 rows, and narrow projections of up to 512 in groups of 64; every
  *      epilogue; a K-split launch includes its reduction)
- *   7  gemm_generic_kernel      8  attn_decode_mfma_kernel (+ merge)   9  attn_chunk_mfma_kernel
+ *   7  gemm_generic_wave_kernel / gemm_generic_kernel      8  attn_decode_mfma_kernel (+ merge)   9  attn_chunk_mfma_kernel
  *   10 sample_kernel
  * The timing state and rpo_set_kernel_path's switch are process-wide and unsynchronised: use them
  * from the one thread that issues the compute calls, and not while another thread is inside one.

@@ -146,8 +146,8 @@ hipError_t probe_mfma(float* scratch, int iters, int reps, double* tflops, hipSt
 enum KernelId : int {
     kKidNone = 0,
     // tile shapes of gemm_dma_kernel / gemm_mfma_kernel <BM, BN, waves along M, waves along N>
-    kKidGemm256 = 1,        // <256,256,2,4> (many-tile problems)
-    kKidGemm128 = 3,        // <128,128,2,2> (decode-sized problems with a deep K, K split; chunks of up to a few thousand rows)
+    kKidGemm256 = 1,        // <256,256,2,4> (many-tile problems), and <128,256,2,4> (LM head of 33 to 128 rows)
+    kKidGemm128 = 3,        // <128,128,2,2> (decode-sized problems with a deep K, K split; gate/up of 65 to 128 rows; chunks of up to a few thousand rows)
     kKidGemm64 = 4,         // <64,128,1,2>  (the same for M <= 64, where the few-row kernel does not take them)
     kKidGemm32 = 5,         // <32,128,1,4>  (QKV projection of more rows than the few-row kernel takes and of chunks: one head per tile of 32, 64 or 128 rows, no K split)
     kKidGemm64x64 = 6,      // <64,64,2,2>   (decode-sized problems and small chunks with a shallow K, no K split)
