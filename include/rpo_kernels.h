@@ -67,7 +67,8 @@ int rpo_attn_decode(struct rpo_batch *b, int32_t layer, const void *q_dev, int32
  * (a few MB), so that no later one does.  Arguments as rpo_gemm_nt.  A problem whose K split needs more than 16 MiB of partial
  * sums (splits * M * N * 4 bytes; only skinny problems with a deep K are split) is rejected with
  * RPO_ENOMEM and nothing is enqueued, unless it is a gate/up problem of more than 256 rows that the tiles
- * which never split hold in a few rounds: those take it (rpo_gemm_nt without a workspace does the same).  All calls on one GPU share the array: calls that may run
+ * which never split hold in a few rounds, or a problem of more than 512 rows (epilogues 0 and 2) that 128x128 tiles hold
+ * in one: those take it (rpo_gemm_nt with 16 MiB of workspace does the same).  All calls on one GPU share the array: calls that may run
  * concurrently on one GPU (different streams, different threads) race on it; calls on one
  * stream are safe.  Nothing in the array needs clearing between calls (every partial sum is
  * written before it is read).  Errors: RPO_EINVAL, RPO_ENOMEM, RPO_EHIP. */

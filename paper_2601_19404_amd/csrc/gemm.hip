@@ -1832,6 +1832,11 @@ size_t gemm_splitk_scratch_bytes(const GemmArgs& a) {
     return splits > 1 ? (size_t)splits * a.M * a.N * sizeof(float) : 0;
 }
 
+bool gemm_narrow_tiles_hold(const GemmArgs& a) {
+    return mfma_ok(a) && a.path == 0 && a.M > 512 && (a.epilogue == kEpiStore || a.epilogue == kEpiAddF32) && a.K % kBK == 0 &&
+           (int64_t)ceil_div(a.M, 128) * ceil_div(a.N, 128) <= 512;
+}
+
 hipError_t gemm_load_kernels() {
     hipFuncAttributes attr;
     const hipError_t e = hipFuncGetAttributes(&attr, (const void*)gemm_splitk_reduce_kernel<kEpiStore>);

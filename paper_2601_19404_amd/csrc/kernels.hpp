@@ -181,6 +181,9 @@ GemmPlan gemm_plan(const GemmArgs& a);
 // Bytes of fp32 K-split partial sums launch_gemm would write for these arguments if the
 // workspace were unlimited (0 = the problem is not split along K); a.ws / a.ws_bytes are ignored.
 size_t gemm_splitk_scratch_bytes(const GemmArgs& a);
+// Whether these arguments are a chunk of more than 512 rows that 128x128 tiles hold in one round: launch_gemm then finds a way
+// with any amount of scratch, a K split that fits it or none.
+bool gemm_narrow_tiles_hold(const GemmArgs& a);
 
 // ---- elementwise ---------------------------------------------------------------
 // x[r, :] = embed[tokens[idx(r)], :] as fp32, idx(r) = tok_index ? tok_index[r] : r;

@@ -1234,7 +1234,8 @@ extern "C" int rpo_gemm_nt_noalloc(const void* a_dev, int64_t lda, const void* w
             return RPO_OK;
         }
     }
-    if (need > kScratchBytes)
+    // a chunk whose cheapest K split is too long for the array: the tiles that need a shorter one or none
+    if (need > kScratchBytes && !gemm_narrow_tiles_hold(g))
         return fail(RPO_ENOMEM,
                     "rpo_gemm_nt_noalloc: this problem splits K and needs %zu bytes of partial sums; the static "
                     "scratch holds %zu (use rpo_gemm_nt with a workspace)", need, kScratchBytes);

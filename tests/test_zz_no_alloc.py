@@ -68,6 +68,25 @@ def test_noalloc_gate_up_beyond_the_scratch_on_unsplit_tiles():
     assert (got.float() - exact).norm() / exact.norm() < 4e-3     # half a last place of bf16
 
 
+@pytest.mark.parametrize("M,N,K,epi", [(772, 3072, 8192, 2), (846, 3072, 8192, 0), (640, 3584, 4160, 2)])
+def test_noalloc_chunk_beyond_the_scratch_on_narrow_tiles(M, N, K, epi):
+    """The cheapest K split of the first two takes four ranges of wide tiles, 38 MB and more: the tiles that do with what the
+    array holds take them, as rpo_gemm_nt does with 16 MiB."""
+    from paper_2601_19404_amd import binding as rpo
+    rpo.lib()
+    rpo.rpo_set_kernel_path(0)
+    free = rpo.rpo_gemm_plan(M, N, K, rpo.RPO_BF16, epi, 1 << 30)
+    assert (free["splits"] * M * N * 4 > 16 << 20) == (K == 8192)
+    a, w = _operands(M, N, K, seed=7)
+    got, ref = (torch.zeros(M, N, device="cuda", dtype=torch.float32 if epi == 2 else torch.bfloat16) for _ in range(2))
+    rpo.rpo_gemm_nt_noalloc(a, w, got, epi)
+    rpo.rpo_gemm_nt(a, w, ref, epi, torch.empty(16 << 20, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert torch.equal(ref, got)
+    exact = a.float() @ w.float().t()
+    assert (got.float() - exact).norm() / exact.norm() < (1e-4 if epi == 2 else 4e-3)     # fp32 sums; half a last place of bf16
+
+
 def test_noalloc_gemm_rejects_what_the_scratch_cannot_hold():
     from paper_2601_19404_amd import binding as rpo
     rpo.lib()
