@@ -886,6 +886,7 @@ __device__ inline void dma2_epilogue(f32x4_t (&acc)[MI][NI], void* __restrict__ 
             }
             return;
         }
+        // Anything else (other strides, the last columns): whole blocks in 8-byte pieces, single values where a block ends.
         const bool vec8 = (ldc & 3) == 0 && ((uintptr_t)Cv & 7) == 0;
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
@@ -1426,10 +1427,10 @@ TileCfg wide_tile(const GemmArgs& a) {
 
 // Whether a deep K split over wide tiles is cheaper than 128x128 tiles, which hold the chunk in one round (two workgroups on
 // some CUs).  A slab of 64 values of K takes a round of 256x192 tiles about 1.16 us and one of 256x256 tiles 1.45, a
-// round of 128x128 tiles 0.5 (half a chip) to 0.63 (all of it) with one and 0.93 with two workgroups per CU; a K split adds
-// its reduction, about 10 us and the partial sums written and read at 4.6 TB/s.  us, wide (split) / 128x128: N = 1536, K = 8960: 700 rows 55.9 / 39.5, 900
-// rows 45.0 / 47.3, 1536 rows 80.9 / 78.3, 2500 rows 105 / 84; N = 3584, K = 18944: 648 rows 164 / 150, 1280 rows 247 / 259, 2100 rows
-// 331 / 281; N = 5120, K = 17408: 900 rows 237 / 256, 1024 rows 247 / 306.
+// round of 128x128 tiles 0.5 (half a chip) to 0.63 (all of it) with one and 0.93 with two workgroups per CU; a K split
+// adds its reduction, about 10 us and the partial sums written and read at 4.6 TB/s.  us, wide (split) / 128x128: N = 1536,
+// K = 8960: 700 rows 55.9 / 39.5, 900 rows 45.0 / 47.3, 1536 rows 80.9 / 78.3, 2500 rows 105 / 84; N = 3584, K = 18944: 648
+// rows 164 / 150, 1280 rows 247 / 259, 2100 rows 331 / 281; N = 5120, K = 17408: 900 rows 237 / 256, 1024 rows 247 / 306.
 bool chunk_splits_wide(const GemmArgs& a, int splits) {
     if (splits == 1 || a.K <= 4096) return false;
     const auto reduction = [&](int s) { return s == 1 ? 0. : 10. + (double)s * a.M * a.N * 8. / 4.6e6; };
